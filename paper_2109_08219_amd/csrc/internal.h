@@ -83,6 +83,7 @@ struct Ctl {
   uint32_t uniq_idx;  // position of a unique entry found by a tail pass
   uint32_t tpub[4];   // threshold t' and its bin, published by block 0 of the tail (coherent stores)
   uint32_t rkmax;     // refinement: largest delegate key in the cut bin
+  uint32_t padr[32];
   uint32_t rknmin;    // refinement: complement of the smallest delegate key in the cut bin
   uint64_t tstamp[kPhases + 2];  // device real-time clock: tail start, each phase's completion
   uint64_t max1;  // largest delegate composite = largest element (the k = 1 answer)
@@ -94,8 +95,13 @@ struct Ctl {
   uint32_t brank[2];  // rank still sought inside it
   uint32_t bdone[2];  // the range is one composite: the selection is done
   uint32_t bticket[2][kPasses];  // its pass tickets (histograms: histW over the delegates, histC)
+  // fill levels, each on a 128-byte line of its own: atomics of different
+  // workgroups on one line are served one at a time (11.5 ns each)
+  uint32_t padq[32];
   uint32_t nq;    // subranges to re-read
+  uint32_t padc[32];
   uint32_t nc;    // survivors
+  uint32_t pado[32];
   uint32_t nout;  // compacted outputs (large-survivor path)
   uint32_t err;   // nonzero: an internal consistency check failed
   uint32_t cap_q; // capacity of the qualifying-subrange list

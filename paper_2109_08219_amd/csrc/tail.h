@@ -250,6 +250,11 @@ __device__ __forceinline__ uint64_t get64(const uint32_t* p) {
   return ((uint64_t)ld_coh(p + 1) << 32) | ld_coh(p);
 }
 
+// The j-th bin of a block's histogram flush: blocks start 32 bins (one
+// 128-byte line) apart, since all of them flush at about the same time and a
+// line serves one workgroup's atomics after the other's.
+__device__ __forceinline__ int flush_bin(int j) { return (j + (int)(blockIdx.x & 63u) * 32) & (kBins - 1); }
+
 // ---- multi-block radix select over a buffer written earlier in this kernel --
 // Phases ph[0..kPasses): one per digit.  Returns the rank-th largest composite
 // of (key[i], idx[i]), i < count, identically in every block.
@@ -305,7 +310,8 @@ __device__ inline uint64_t tail_select(const uint32_t* key, const uint32_t* idx,
     }
     __syncthreads();
     if (mine)
-      for (int i = threadIdx.x; i < kBins; i += kTailThreads) {
+      for (int j = threadIdx.x; j < kBins; j += kTailThreads) {
+        const int i = flush_bin(j);
         const uint32_t v = sm.u.st.hist[i];
         if (v) atomicAdd(&hist[p][i], v);
       }
@@ -655,7 +661,8 @@ __device__ __forceinline__ void hist_pending_flush(uint32_t* h, uint32_t& pbin, 
 // Block-uniform.
 __device__ __forceinline__ void hist_flush(uint32_t* h, uint32_t* g) {
   __syncthreads();
-  for (int i = threadIdx.x; i < kBins; i += kTailThreads) {
+  for (int j = threadIdx.x; j < kBins; j += kTailThreads) {
+    const int i = flush_bin(j);
     const uint32_t v = h[i];
     if (v) {
       atomicAdd(&g[i], v);
@@ -947,7 +954,8 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs a) {
       }
       __syncthreads();
       if (mine) {
-        for (int i = threadIdx.x; i < kBins; i += kTailThreads) {
+        for (int j = threadIdx.x; j < kBins; j += kTailThreads) {
+          const int i = flush_bin(j);
           const uint32_t v = sm.u.st.hist[i];
           if (v) atomicAdd(&ctl->histH[i], v);
         }
