@@ -79,7 +79,11 @@ typedef enum {
  *   out_vals device, k elements of `dtype`: the k largest, sorted as above
  *   out_idx  device, k uint32 positions into keys (out_vals[r] == keys[out_idx[r]]),
  *            or NULL
- *   stream   hipStream_t or NULL */
+ *   stream   hipStream_t or NULL
+ * Beyond one workgroup's sizes (n > 2^16 or k > 2048, n >= 2^14, k > 1) calls
+ * without explicit options or counters split the work by a sample of the keys
+ * (filter pass, buckets sorted independently); the result is the same, and
+ * exact, whatever the sample. */
 int topk_select(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals,
                 uint32_t* out_idx, void* stream);
 
@@ -249,7 +253,8 @@ int drtopk_plan(uint64_t n, uint32_t k, int dtype, drtopk_options_t* out);
 
 /* Phase timing with HIP events, for measurement runs.  While enabled, every
  * top-k call records events on its own stream around the delegate pass (the
- * one pass that streams all of V) and around everything after it.
+ * one pass that streams all of V; without a delegate vector the sample and the
+ * filter pass) and around everything after it.
  * drtopk_timing_read synchronises on those events, returns the summed
  * milliseconds of each phase and the number of calls since the last read,
  * and resets the counters.  Enabling costs two event pairs per call. */

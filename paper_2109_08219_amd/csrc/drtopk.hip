@@ -25,6 +25,7 @@
 #include "drtopk.h"
 #include "host.h"
 #include "batched.h"
+#include "sample_host.h"
 #include "wide_host.h"
 
 namespace drtopk {
@@ -392,6 +393,18 @@ int enqueue_plan(const Plan& p, const void* keys, void* ws, void* out_vals, uint
   return DRTOPK_OK;
 }
 
+// Whether a call with the planner's choices (no explicit options, no counters
+// asked for) takes the sampled path: wherever it can be planned, since it was
+// the faster one at every size measured (n = 2^20, k = 1024 uint32: 28.6
+// against 39.1 us; n = 3 * 10^6, k = 100: 29.9 / 46.3; n = 2^24, k = 2^21:
+// 129 / 641, its median: 60 / 262; n = 2^30, k = 1024: 666 / 676, k = 131072:
+// 673 / 799; float64, n = 2^28, k = 131072: 375 / 799).  k = 1 stays with the
+// delegate pass, which alone answers it.  `total` is the workspace of the
+// other path, which the footprint and the no-allocation limit are stated in.
+bool take_sampled(const SPlan& sp, size_t total) {
+  return sp.on && sp.k > 1 && sp.total <= total && g_cap_override.load(std::memory_order_relaxed) == 0;
+}
+
 // Runs the whole path; `after` runs under the workspace lock after the
 // enqueue, with the plan, the workspace pointer and the stream.  pos_in_ws:
 // with out_idx NULL the output positions go to a workspace segment
@@ -399,13 +412,18 @@ int enqueue_plan(const Plan& p, const void* keys, void* ws, void* out_vals, uint
 template <typename F>
 int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals, uint32_t* out_idx,
                void* out_kth, bool kth_only, const drtopk_options_t* opt, void* stream, F&& after,
-               bool filter_only = false, bool pos_in_ws = false) {
+               bool filter_only = false, bool pos_in_ws = false, bool counters = false) {
   int st = check_args(keys, n, k, dtype);
   if (st) return st;
   Plan p;
   const bool ws_pos = pos_in_ws && !out_idx && !kth_only;
   st = make_plan(keys, n, k, dtype, opt, &p, ws_pos);
   if (st) return st;
+  SPlan sp;
+  if (!opt && !counters && p.mode != 3) {
+    sample_plan(keys, n, k, dtype, kth_only, ws_pos, &sp);
+    sp.on = take_sampled(sp, p.total);
+  }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DRTOPK_EDEVICE;
   Workspace* ws = workspace_entry(dev, stream);
@@ -413,12 +431,16 @@ int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_va
   std::lock_guard<std::mutex> g(ws->mu);
   st = ensure_record(ws);
   if (st) return st;
-  st = ensure_bytes(ws, p.total);
+  st = ensure_bytes(ws, sp.on ? sp.total : p.total);
   if (st) return st;
   p.rec = ws->rec;
-  if (ws_pos) out_idx = at<uint32_t>(ws->ptr, p.off_pos);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  st = enqueue_plan(p, keys, ws->ptr, out_vals, out_idx, out_kth, kth_only, filter_only, s);
+  if (sp.on) p.off_pos = sp.off_pos;
+  if (ws_pos) out_idx = at<uint32_t>(ws->ptr, p.off_pos);
+  if (sp.on)
+    st = sample_enqueue(sp, keys, ws->ptr, out_vals, out_idx, out_kth, s, true);
+  else
+    st = enqueue_plan(p, keys, ws->ptr, out_vals, out_idx, out_kth, kth_only, filter_only, s);
   if (st) return st;
   return after(p, ws->ptr, s);
 }
@@ -427,13 +449,19 @@ int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_va
 // ws, hipStream_t)` runs under the workspace lock after the enqueue.
 template <typename F>
 int run_wide(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals, uint32_t* out_idx, void* out_kth,
-             bool kth_only, const drtopk_options_t* opt, void* stream, F&& after, bool pos_in_ws = false) {
+             bool kth_only, const drtopk_options_t* opt, void* stream, F&& after, bool pos_in_ws = false,
+             bool counters = false) {
   int st = check_args(keys, n, k, dtype);
   if (st) return st;
   WPlan p;
   const bool ws_pos = pos_in_ws && !out_idx && !kth_only;
   st = wide_plan(n, k, dtype, (reinterpret_cast<uintptr_t>(keys) & 15u) == 0, opt, &p, ws_pos);
   if (st) return st;
+  SPlan sp;
+  if (!opt && !counters) {
+    sample_plan(keys, n, k, dtype, kth_only, ws_pos, &sp);
+    sp.on = take_sampled(sp, p.total);
+  }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DRTOPK_EDEVICE;
   Workspace* ws = workspace_entry(dev, stream);
@@ -441,11 +469,15 @@ int run_wide(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals
   std::lock_guard<std::mutex> g(ws->mu);
   st = ensure_record(ws);
   if (st) return st;
-  st = ensure_bytes(ws, p.total);
+  st = ensure_bytes(ws, sp.on ? sp.total : p.total);
   if (st) return st;
+  if (sp.on) p.off_pos = sp.off_pos;
   if (ws_pos) out_idx = at<uint32_t>(ws->ptr, p.off_pos);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  st = wide_enqueue(p, keys, ws->ptr, ws->rec, out_vals, out_idx, out_kth, kth_only, s);
+  if (sp.on)
+    st = sample_enqueue(sp, keys, ws->ptr, out_vals, out_idx, out_kth, s, false);
+  else
+    st = wide_enqueue(p, keys, ws->ptr, ws->rec, out_vals, out_idx, out_kth, kth_only, s);
   if (st) return st;
   return after(p, ws->ptr, s);
 }
@@ -743,9 +775,11 @@ int topk_select_ex(const void* keys, uint64_t n, uint32_t k, int dtype, void* ou
   try {
     if (wide_dtype(dtype))
       return run_wide(keys, n, k, dtype, out_vals, out_idx, nullptr, false, opt, stream,
-                      [&](const WPlan& p, void* ws, hipStream_t s) { return fill_stats_wide(p, ws, s, stats); });
+                      [&](const WPlan& p, void* ws, hipStream_t s) { return fill_stats_wide(p, ws, s, stats); }, false,
+                      stats != nullptr);
     return run_common(keys, n, k, dtype, out_vals, out_idx, nullptr, false, opt, stream,
-                      [&](const Plan& p, void* ws, hipStream_t s) { return fill_stats(p, ws, s, stats); });
+                      [&](const Plan& p, void* ws, hipStream_t s) { return fill_stats(p, ws, s, stats); }, false, false,
+                      stats != nullptr);
   } catch (...) {
     return DRTOPK_EDEVICE;
   }
@@ -775,6 +809,10 @@ int topk_select_noalloc(const void* keys, uint64_t n, uint32_t k, int dtype, voi
     if (!base) return DRTOPK_EDEVICE;
     void* ws = static_cast<char*>(base) + kScratchRec;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    SPlan sp;
+    if (wide || p.mode != 3) sample_plan(keys, n, k, dtype, false, false, &sp);
+    if (take_sampled(sp, wide ? wp.total : p.total))
+      return sample_enqueue(sp, keys, ws, out_vals, out_idx, nullptr, s, false);
     if (wide) return wide_enqueue(wp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, false, s);
     p.rec = static_cast<uint32_t*>(base);
     p.marks = false;  // no timing events

@@ -1,0 +1,216 @@
+// The sampled path: planner and kernel sequence.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+
+#include "host.h"
+#include "sample.h"
+#include "sample_host.h"
+#include "wide_host.h"
+
+namespace drtopk {
+
+namespace {
+
+constexpr uint32_t kSLevel2 = 4096;  // samples of the second level
+
+size_t salign(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Fewest samples r such that at least r of them fall among the k largest with
+// probability below exp(-24), for lam = k * m / n expected (Chernoff's bound of
+// the Poisson tail): tighter than Bernstein's inequality when few are expected.
+uint32_t small_rank(double lam) {
+  uint32_t r = (uint32_t)lam + 1;
+  while (r * std::log(r / (2.718281828459045 * lam)) + lam < 24.0) ++r;
+  return r + 1;
+}
+
+// Candidates at or above the r-th sample, but for six standard deviations.
+double span_cap(double span, double gap) { return (span + 6.0 * std::sqrt(span) + 10.0) * gap; }
+
+template <typename K>
+void plan_for(SPlan& p) {
+  typedef STraits<K> T;
+  typedef typename T::Comp C;
+  const double n = (double)p.n, k = (double)p.k;
+  SWin w = {};
+  uint64_t cap1 = 0, cap = 0;
+  double cap_top = 0, gap = 0;
+  // the r-th of 16 m samples, of which the top 16 of each 256 are kept, when
+  // r is at most a fifth of what is kept
+  for (uint32_t m = 4096; m >= 1024 && !p.top; m /= 4) {
+    if (p.n < 32 * (uint64_t)m) continue;
+    gap = n / (16.0 * m);
+    const double lam = k / gap;
+    sample_window(n, k, 16.0 * m, false, &w);
+    if (lam < 64) {
+      const uint32_t r = small_rank(lam);
+      if (r < w.r) w.r = r;
+    }
+    if (w.r > m / 5) break;
+    p.top = true;
+    p.m = m;
+    cap_top = span_cap(w.r, gap);
+  }
+  if (!p.top) {
+    p.m = 8192;
+    if (p.n < 2 * (uint64_t)p.m) return;
+    gap = n / p.m;
+    sample_window(n, k, p.m, p.kth_only, &w);
+    cap_top = span_cap(w.r, gap);
+  }
+  if (cap_top <= T::kCap) {  // one workgroup sorts all candidates
+    p.plain = 1;
+    w.a = 0;
+    w.B = p.bmax = 1;
+    cap = T::kCap;
+  } else if (gap <= 2.0 * T::kTarget) {
+    sample_buckets(gap, T::kTarget, T::kMaxB, &w);
+    cap = (uint64_t)span_cap(w.r - w.a, gap);
+    p.bmax = w.B;
+  } else if (p.top) {
+    p.levels = 2;
+    cap1 = (uint64_t)cap_top;
+    if (cap1 > p.n) cap1 = p.n;
+    if (cap1 > (1u << 24)) return;
+    SWin w2 = {};
+    sample_window((double)cap1, k, kSLevel2, false, &w2);
+    cap = (uint64_t)span_cap(w2.r, (double)cap1 / kSLevel2);
+    if (cap > cap1) cap = cap1;
+    const uint64_t b = 4 * cap / T::kTarget + 32;
+    p.bmax = b < (uint64_t)T::kMaxB ? (uint32_t)b : (uint32_t)T::kMaxB;
+  } else {
+    return;
+  }
+  p.win = w;
+  if (cap > p.n) cap = p.n;
+  // rows: one per workgroup, and any two rows of a workgroup but its last hold a stage
+  if (!p.plain && 256 + 2 * cap / T::kStage > (uint64_t)kSMaxRows) return;
+  p.cap1 = (uint32_t)cap1;
+  p.cap = (uint32_t)cap;
+  p.pitch = (p.bmax + 1 + 31) & ~31u;
+  size_t off = 0;
+  auto seg = [&](size_t bytes) {
+    const size_t o = off;
+    off = salign(off + bytes);
+    return o;
+  };
+  p.off_ctl = seg(sizeof(SCtl));
+  const size_t ms = p.m > kSLevel2 ? p.m : kSLevel2;
+  p.off_smp = seg(ms * sizeof(C));
+  p.off_sorted = seg(ms * sizeof(C));
+  if (p.levels == 2) p.off_c1 = seg((size_t)p.cap1 * sizeof(C));
+  p.off_cand = seg((size_t)p.cap * sizeof(C));
+  if (!p.plain) {
+    p.off_rows = seg(kSMaxRows * sizeof(SRow));
+    p.off_offs = seg((size_t)kSMaxRows * p.pitch * sizeof(uint16_t));
+  }
+  p.off_pos = off;
+  p.total = off;
+  p.on = true;
+}
+
+template <typename K>
+void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint32_t* out_idx, K* out_kth,
+                 hipStream_t s, PhaseMarks& pm) {
+  typedef STraits<K> T;
+  typedef typename T::Comp C;
+  const K* keys = static_cast<const K*>(keys_v);
+  const SCodec<K> cd{(K)p.codec_a, (K)p.codec_c};
+  SCtl* ctl = at<SCtl>(ws, p.off_ctl);
+  C* smp = at<C>(ws, p.off_smp);
+  C* sorted = at<C>(ws, p.off_sorted);
+  C* c1 = at<C>(ws, p.off_c1);
+  C* cand = at<C>(ws, p.off_cand);
+  SRow* rows = at<SRow>(ws, p.off_rows);
+  uint16_t* offs = at<uint16_t>(ws, p.off_offs);
+  const int kth = p.kth_only ? 1 : 0;
+  auto rank = [&](uint32_t m) {
+    const dim3 g(m / kSRankPer), t(kSRankThreads);
+    if (m == 1024) hipLaunchKernelGGL((k_srank<C, 2>), g, t, 0, s, smp, sorted);
+    else if (m == 4096) hipLaunchKernelGGL((k_srank<C, 8>), g, t, 0, s, smp, sorted);
+    else hipLaunchKernelGGL((k_srank<C, 16>), g, t, 0, s, smp, sorted);
+  };
+  pm.start(s);  // the timed pass: the sample and the one pass over the input
+  if (p.top)
+    hipLaunchKernelGGL((k_sgather<K, false, true>), dim3(p.m / kSKeep), dim3(256), 0, s, keys, (const C*)nullptr, p.n,
+                       0u, p.k, p.m * 16, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
+  else
+    hipLaunchKernelGGL((k_sgather<K, false, false>), dim3(p.m / 256), dim3(256), 0, s, keys, (const C*)nullptr, p.n,
+                       0u, p.k, p.m, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
+  rank(p.m);
+  if (p.plain || p.levels == 2) {
+    constexpr uint64_t load = (uint64_t)64 * (16 / sizeof(K)) * (kSFilterThreads / 64);
+    uint64_t* al = p.plain ? &ctl->alloc : &ctl->alloc1;
+    C* o = p.plain ? cand : c1;
+    const uint32_t c = p.plain ? p.cap : p.cap1;
+    if (p.n < 8 * load * 512)
+      hipLaunchKernelGGL((k_sfilter<K, 2>), dim3(grid_for(p.n, 2 * load, 1024)), dim3(kSFilterThreads), 0, s, keys,
+                         p.n, p.head, cd, p.L, p.win.r, p.m, sorted, al, o, c);
+    else
+      hipLaunchKernelGGL((k_sfilter<K, 8>), dim3(grid_for(p.n, 8 * load, 1024)), dim3(kSFilterThreads), 0, s, keys,
+                         p.n, p.head, cd, p.L, p.win.r, p.m, sorted, al, o, c);
+  } else {
+    const unsigned g = grid_for(p.n, T::kStage, 256);
+    hipLaunchKernelGGL((k_spart<K, false>), dim3(g), dim3(kSPartThreads), 0, s, keys, (const C*)nullptr, p.n, p.head,
+                       0u, p.k, p.m, cd, p.L, sorted, ctl, cand, p.cap, rows, offs, p.pitch);
+  }
+  pm.mid(s);
+  if (p.levels == 2) {
+    hipLaunchKernelGGL((k_sgather<K, true, false>), dim3(kSLevel2 / 256), dim3(256), 0, s, keys, c1, p.n, p.cap1, p.k,
+                       kSLevel2, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
+    rank(kSLevel2);
+    const unsigned g = grid_for(p.cap1, T::kStage, 256);
+    hipLaunchKernelGGL((k_spart<K, true>), dim3(g), dim3(kSPartThreads), 0, s, keys, c1, p.n, 0u, p.cap1, p.k,
+                       kSLevel2, cd, p.L, sorted, ctl, cand, p.cap, rows, offs, p.pitch);
+  }
+  if (p.plain)
+    hipLaunchKernelGGL((k_sbucket<K, true>), dim3(1), dim3(kSBucketThreads), 0, s, keys, p.n, p.k, kth, p.levels, cd,
+                       p.L, ctl, cand, p.cap1, p.cap, rows, offs, p.pitch, out_vals, out_idx, out_kth);
+  else
+    hipLaunchKernelGGL((k_sbucket<K, false>), dim3(p.bmax), dim3(kSBucketThreads), 0, s, keys, p.n, p.k, kth, p.levels,
+                       cd, p.L, ctl, cand, p.cap1, p.cap, rows, offs, p.pitch, out_vals, out_idx, out_kth);
+}
+
+}  // namespace
+
+void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, bool pos_in_ws, SPlan* out) {
+  SPlan p;
+  p.n = n;
+  p.k = k;
+  p.kth_only = kth_only;
+  p.wide = wide_dtype(dtype);
+  const int base = dtype & ~DRTOPK_SMALLEST;
+  const bool fl = base == DRTOPK_F32 || base == DRTOPK_F64;
+  const bool raw = base == DRTOPK_U32 || base == DRTOPK_U64;
+  const uint64_t top = p.wide ? 0x8000000000000000ull : 0x80000000ull;
+  p.codec_a = fl ? top - 1 : 0;
+  p.codec_c = raw ? 0 : top;
+  if (dtype & DRTOPK_SMALLEST) p.codec_c = ~p.codec_c;
+  p.L = 1;
+  while (p.L < 32 && ((n - 1) >> p.L)) ++p.L;
+  const uint32_t word = p.wide ? 8 : 4;
+  p.head = (uint32_t)(((16 - (reinterpret_cast<uintptr_t>(keys) & 15u)) & 15u) / word);
+  if ((reinterpret_cast<uintptr_t>(keys) & (word - 1)) == 0) {
+    if (p.wide) plan_for<uint64_t>(p);
+    else plan_for<uint32_t>(p);
+  }
+  if (p.on && pos_in_ws) p.total = salign(p.off_pos + (size_t)k * 4);
+  *out = p;
+}
+
+int sample_enqueue(const SPlan& p, const void* keys, void* ws, void* out_vals, uint32_t* out_idx, void* out_kth,
+                   hipStream_t s, bool marks) {
+  PhaseMarks pm;
+  if (marks) pm.begin(s);
+  if (p.wide)
+    enqueue_for<uint64_t>(p, keys, ws, static_cast<uint64_t*>(out_vals), out_idx, static_cast<uint64_t*>(out_kth), s,
+                          pm);
+  else
+    enqueue_for<uint32_t>(p, keys, ws, static_cast<uint32_t*>(out_vals), out_idx, static_cast<uint32_t*>(out_kth), s,
+                          pm);
+  pm.end(s);
+  return hipGetLastError() == hipSuccess ? (int)DRTOPK_OK : (int)DRTOPK_EDEVICE;
+}
+
+}  // namespace drtopk

@@ -1,0 +1,65 @@
+// The window of the sampled path: which sample ranks bound the elements that
+// can be in the answer, and how they are divided into buckets.  Shared by the
+// planner and the kernels.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace drtopk {
+
+// The window of sample ranks of one level: elements above the a-th sample are
+// counted only, those from it down to the r-th sample are the candidates.
+// Buckets: with P = 0, every s samples from rank a on; otherwise P equal
+// intervals of composite space (a power of two) between every eighth sample,
+// and kSTop intervals above the first sample when the window is open (a = 0).
+struct SWin {
+  uint32_t r, a, s, P, B, pad[3];
+};
+constexpr uint32_t kSTop = 8;
+constexpr uint32_t kSGroup = 8;
+
+// Window for rank k of `count` elements under m samples: the number of
+// samples among the k largest is bounded both ways but for a probability below
+// 2 * exp(-24) (Bernstein's inequality).
+__host__ __device__ inline void sample_window(double count, double k, double m, bool kth, SWin* w) {
+  const double lam = k * m / count, v = lam * (1.0 - k / count);
+#ifdef __HIP_DEVICE_COMPILE__
+  const double x = 8.0 + (double)sqrtf((float)(64.0 + 48.0 * v));
+#else
+  const double x = 8.0 + __builtin_sqrt(64.0 + 48.0 * v);
+#endif
+  const double hi = lam + x + 2.0, lo = lam - x - 2.0;
+  w->r = hi < m ? (uint32_t)hi : (uint32_t)m + 1;  // m + 1: no cut, every element is a candidate
+  w->a = kth && lo >= 1.0 ? (uint32_t)lo : 0u;
+}
+// Buckets are planned for `target` elements.  Gaps between neighbouring samples
+// are as uneven as exponential variables (one in 55 holds four times the
+// mean), so where a bucket would be less than four gaps it is an interval
+// between samples eight gaps apart instead (four times the mean: 1 in 10^7
+// where the density is smooth).
+__host__ __device__ inline void sample_buckets(double gap, uint32_t target, uint32_t bmax, SWin* w) {
+  const uint32_t q0 = w->a ? w->a : 1u, top = w->a ? 0u : kSTop;
+  const uint32_t groups = (w->r - q0 + kSGroup - 1) / kSGroup;
+  uint32_t P = 0;
+  if (4.0 * gap > (double)target) {
+    P = 4;
+    while (P < 64 && 8.0 * gap > (double)target * P) P <<= 1;
+    while (P > 1 && top + (uint64_t)groups * P > bmax) P >>= 1;
+    if (top + (uint64_t)groups * P > bmax || P < 4) P = 0;
+  }
+  w->P = P;
+  if (P) {
+    w->s = 0;
+    w->B = top + groups * P;
+    return;
+  }
+  const double per = (double)target / gap;
+  uint32_t s = per > 1.0 ? (per < 1e6 ? (uint32_t)per : 1000000u) : 1u;
+  const uint32_t span = w->r - w->a;
+  if ((uint64_t)s * bmax < span) s = (span + bmax - 1) / bmax;
+  w->s = s;
+  w->B = (span + s - 1) / s;
+}
+
+}  // namespace drtopk
