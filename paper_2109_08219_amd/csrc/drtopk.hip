@@ -393,16 +393,29 @@ int enqueue_plan(const Plan& p, const void* keys, void* ws, void* out_vals, uint
   return DRTOPK_OK;
 }
 
+constexpr size_t kSampledFree = size_t(4) << 20;
+
 // Whether a call with the planner's choices (no explicit options, no counters
 // asked for) takes the sampled path: wherever it can be planned, since it was
 // the faster one at every size measured (n = 2^20, k = 1024 uint32: 28.6
 // against 39.1 us; n = 3 * 10^6, k = 100: 29.9 / 46.3; n = 2^24, k = 2^21:
 // 129 / 641, its median: 60 / 262; n = 2^30, k = 1024: 666 / 676, k = 131072:
-// 673 / 799; float64, n = 2^28, k = 131072: 375 / 799).  k = 1 stays with the
-// delegate pass, which alone answers it.  `total` is the workspace of the
-// other path, which the footprint and the no-allocation limit are stated in.
+// 673 / 799; float64, n = 2^28, k = 131072: 375 / 799).  k = 1 of 32-bit keys
+// stays with the delegate pass, which alone answers it.  `total` is the workspace of the
+// other path: the no-allocation limit is stated in it, so the sampled path
+// needs no more than that or a small part of that limit.
 bool take_sampled(const SPlan& sp, size_t total) {
-  return sp.on && sp.k > 1 && sp.total <= total && g_cap_override.load(std::memory_order_relaxed) == 0;
+  return sp.on && (sp.k > 1 || sp.wide) && sp.total <= (total > kSampledFree ? total : kSampledFree) &&
+         g_cap_override.load(std::memory_order_relaxed) == 0;
+}
+
+// Workspace of a call: the larger of the sampled path's, where it is taken,
+// and `total`, the other path's.
+size_t larger_workspace(uint64_t n, uint32_t k, int dtype, size_t total) {
+  alignas(16) static const uint32_t aligned[4] = {0, 0, 0, 0};
+  SPlan sp;
+  sample_plan(aligned, n, k, dtype, false, false, &sp);
+  return take_sampled(sp, total) && sp.total > total ? sp.total : total;
 }
 
 // Runs the whole path; `after` runs under the workspace lock after the
@@ -420,7 +433,7 @@ int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_va
   st = make_plan(keys, n, k, dtype, opt, &p, ws_pos);
   if (st) return st;
   SPlan sp;
-  if (!opt && !counters && p.mode != 3) {
+  if (!opt && !counters) {
     sample_plan(keys, n, k, dtype, kth_only, ws_pos, &sp);
     sp.on = take_sampled(sp, p.total);
   }
@@ -810,7 +823,7 @@ int topk_select_noalloc(const void* keys, uint64_t n, uint32_t k, int dtype, voi
     void* ws = static_cast<char*>(base) + kScratchRec;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     SPlan sp;
-    if (wide || p.mode != 3) sample_plan(keys, n, k, dtype, false, false, &sp);
+    sample_plan(keys, n, k, dtype, false, false, &sp);
     if (take_sampled(sp, wide ? wp.total : p.total))
       return sample_enqueue(sp, keys, ws, out_vals, out_idx, nullptr, s, false);
     if (wide) return wide_enqueue(wp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, false, s);
@@ -887,7 +900,7 @@ int drtopk_footprint(uint64_t n, uint32_t k, int dtype, uint64_t* bytes) {
     WPlan wp;
     st = wide_plan(n, k, dtype, true, nullptr, &wp);
     if (st) return st;
-    *bytes = 8 * n + 12ull * k + 8 + wp.total;
+    *bytes = 8 * n + 12ull * k + 8 + larger_workspace(n, k, dtype, wp.total);
     return DRTOPK_OK;
   }
   // a batched problem: its descriptor, work items and arrival counter, plus
@@ -897,7 +910,7 @@ int drtopk_footprint(uint64_t n, uint32_t k, int dtype, uint64_t* bytes) {
     Plan p;
     st = make_plan(dummy, n, k, dtype, nullptr, &p);
     if (st) return st;
-    ws = p.total;
+    ws = larger_workspace(n, k, dtype, p.total);
   } else {
     BatchDesc d{};
     d.n = n;

@@ -37,12 +37,13 @@ typedef unsigned __int128 su128;
 typedef uint32_t su32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSBins = 2048;
-constexpr int kSMaxRows = 1024;      // rows of the offset table
+constexpr int kSMaxRows = 1024;      // most rows of the offset table
 constexpr int kSPartThreads = 1024;
 constexpr int kSBucketThreads = 512;
 constexpr int kSRankThreads = 512;
 constexpr int kSRankPer = 32;        // samples ranked by one workgroup
 constexpr int kSFilterThreads = 256;
+constexpr uint32_t kSSplit = 256;    // samples of a workgroup's own sort or threshold
 
 template <typename K>
 struct STraits;
@@ -58,7 +59,7 @@ template <>
 struct STraits<uint64_t> {
   typedef su128 Comp;
   static constexpr int kStage = 4096;
-  static constexpr int kCap = 3840;
+  static constexpr int kCap = 3584;
   static constexpr int kMaxB = 1536;
   static constexpr int kTarget = 1024;
 };
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ k
                                                          uint32_t m, SCodec<K> cd, int L,
                                                          const typename STraits<K>::Comp* __restrict__ sorted,
                                                          SCtl* ctl, typename STraits<K>::Comp* __restrict__ out,
-                                                         uint32_t cap, SRow* __restrict__ rows,
+                                                         uint32_t cap, uint32_t maxrows, SRow* __restrict__ rows,
                                                          uint16_t* __restrict__ offs, uint32_t pitch) {
   typedef typename STraits<K>::Comp C;
   typedef typename std::conditional<ARR, C, K>::type R;
@@ -492,7 +493,7 @@ __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ k
     if (threadIdx.x == 0) hist[B] = cnt;
     __syncthreads();
     const uint32_t row = s_row, base = s_base;
-    if (row < (uint32_t)kSMaxRows) {
+    if (row < maxrows) {
       if (threadIdx.x == 0) rows[row] = SRow{base, s_above};
       for (uint32_t b = threadIdx.x; b <= B; b += T) offs[(size_t)row * pitch + b] = (uint16_t)hist[b];
     }
@@ -611,28 +612,98 @@ __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ k
 // ---------------------------------------------------------------------------
 // Bucket sort.
 
-template <typename K>
-struct SBucketShared {
-  typedef typename STraits<K>::Comp C;
-  C buf[STraits<K>::kCap];
-  uint32_t hist[kSBins + 1];
-  uint32_t pre[kSMaxRows + 1];  // bucket elements in the rows before this one
-  uint32_t src[kSMaxRows];      // candidate index of the row's segment
-  C red[kSBucketThreads / 64][2];
-  uint32_t s_w[kSBucketThreads / 64];
+// LDS of a workgroup of T threads that sorts up to CAP composites.
+template <typename C, uint32_t CAP, int T>
+struct SSortShared {
+  C buf[CAP];
+  uint32_t hist[kSBins + 16];  // linear bins, or 8 pieces of each of kSSplit + 1 gaps
+  C red[T / 64][2];
+  C split[kSSplit];
+  uint32_t rank[kSSplit];
+  uint32_t s_w[T / 64];
   uint32_t misc[8];
 };
 
+// Sorts kSSplit LDS composites descending in place, by all-pairs ranks (T a
+// multiple of kSSplit; `rank`: kSSplit words).  TIES: equal ones keep their
+// order; otherwise all are distinct.
+template <typename C, int T, bool TIES>
+__device__ __forceinline__ void ssplit_sort(C* split, uint32_t* rank) {
+  constexpr uint32_t S = kSSplit, parts = T / S, per = S / parts;
+  const uint32_t i = threadIdx.x % S, j0 = threadIdx.x / S * per;
+  if (threadIdx.x < S) rank[threadIdx.x] = 0;
+  __syncthreads();
+  const C x = split[i];
+  uint32_t r = 0;
+#pragma unroll 16
+  for (uint32_t j = j0; j < j0 + per; ++j) {
+    const C y = split[j];
+    r += y > x || (TIES && y == x && j < i) ? 1u : 0u;
+  }
+  if constexpr (parts == 1) rank[i] = r;
+  else atomicAdd(&rank[i], r);
+  __syncthreads();
+  if (threadIdx.x < S) {
+    const uint32_t q = rank[threadIdx.x];
+    split[q] = x;
+  }
+  __syncthreads();
+}
+
+template <typename C>
+__device__ __forceinline__ C sshfl_xor(C v, int o) {
+  uint32_t w[sizeof(C) / 4];
+  __builtin_memcpy(w, &v, sizeof(C));
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(C) / 4; ++i) w[i] = (uint32_t)__shfl_xor((int)w[i], o);
+  __builtin_memcpy(&v, w, sizeof(C));
+  return v;
+}
+
+// Largest and smallest over the workgroup, held by every thread.  red: T / 64
+// pairs, free before and after.
+template <typename C, int T>
+__device__ __forceinline__ void sblock_minmax(C& mx, C& mn, C (*red)[2]) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const C a = sshfl_xor(mx, o), b = sshfl_xor(mn, o);
+    mx = a > mx ? a : mx;
+    mn = b < mn ? b : mn;
+  }
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6][0] = mx;
+    red[threadIdx.x >> 6][1] = mn;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) {
+    const C a = red[w][0], b = red[w][1];
+    mx = a > mx ? a : mx;
+    mn = b < mn ? b : mn;
+  }
+}
+
+// Bin of a distance from the largest composite, finest at the top: 2^MB pieces
+// of every octave.
+template <typename C>
+__device__ __forceinline__ uint32_t slog_bin(C d) {
+  constexpr uint32_t MB = sizeof(C) == 8 ? 5 : 4;  // 1920 or 1488 bins
+  const uint32_t w = sbits(d);
+  if (w <= MB) return (uint32_t)d;
+  return ((w - MB) << MB) + ((uint32_t)(d >> (w - MB - 1)) & ((1u << MB) - 1));
+}
+
 // Sorts the N (<= CAP) composites held N = e * T + thread in c[] descending
-// and calls emit(slot, composite) for each.  Linear bins over [min, max], a
-// scatter into LDS bin by bin, then each element's rank inside its bin; when
-// a bin is crowded (keys in far-apart clusters) a bitonic network instead.
-template <typename K, int E, typename F>
-__device__ __forceinline__ void sbucket_sort(SBucketShared<K>& sm, typename STraits<K>::Comp (&c)[E], uint32_t N,
-                                             F&& emit) {
-  typedef typename STraits<K>::Comp C;
-  constexpr int T = kSBucketThreads;
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// and calls emit(slot, composite) for each of the first `need` slots (and
+// perhaps a few after them).  Linear bins over [min, max] (logarithmic from the
+// top when at most a quarter is needed: the top of both float and integer keys
+// is then spread over many bins whatever lies below), a scatter into LDS bin by
+// bin, then each element's rank inside its bin; bins that start past `need`
+// are left alone.  When a bin that counts is crowded (keys in far-apart
+// clusters, floats of both signs) bins between samples instead.
+template <typename C, uint32_t CAP, int T, int E, typename F>
+__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint64_t need, F&& emit) {
   C mx = 0, mn = ~(C)0;
 #pragma unroll
   for (int e = 0; e < E; ++e)
@@ -641,110 +712,147 @@ __device__ __forceinline__ void sbucket_sort(SBucketShared<K>& sm, typename STra
       mn = c[e] < mn ? c[e] : mn;
     }
   for (int b = threadIdx.x; b <= kSBins; b += T) sm.hist[b] = 0;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    C a = mx, b = mn;
-    uint32_t* pa = reinterpret_cast<uint32_t*>(&a);
-    uint32_t* pb = reinterpret_cast<uint32_t*>(&b);
-#pragma unroll
-    for (uint32_t i = 0; i < sizeof(C) / 4; ++i) {
-      pa[i] = (uint32_t)__shfl_xor((int)pa[i], o);
-      pb[i] = (uint32_t)__shfl_xor((int)pb[i], o);
-    }
-    mx = a > mx ? a : mx;
-    mn = b < mn ? b : mn;
-  }
-  if (lane == 0) { sm.red[wave][0] = mx; sm.red[wave][1] = mn; }
   if (threadIdx.x == 0) sm.misc[0] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < T / 64; ++w) {
-    const C a = sm.red[w][0], b = sm.red[w][1];
-    mx = a > mx ? a : mx;
-    mn = b < mn ? b : mn;
-  }
+  sblock_minmax<C, T>(mx, mn, sm.red);
   const uint32_t bl = sbits((C)(mx - mn));
   const int sh = bl > 11 ? (int)bl - 11 : 0;
+  const bool logb = need <= N / 4;
   uint32_t at[E];
 #pragma unroll
   for (int e = 0; e < E; ++e)
     if (e * T + threadIdx.x < N) {
-      const uint32_t b = kSBins - 1 - (uint32_t)((c[e] - mn) >> sh);
-      const uint32_t q = atomicAdd(&sm.hist[b], 1u);
-      at[e] = (b << 16) | q;
-      if (q >= 96u) sm.misc[0] = 1;
+      const uint32_t b = logb ? slog_bin<C>(mx - c[e]) : (uint32_t)((mx - c[e]) >> sh);
+      at[e] = (b << 16) | atomicAdd(&sm.hist[b], 1u);
     }
   __syncthreads();
-  const bool crowded = sm.misc[0] != 0;
-  if (!crowded) {
-    constexpr int BP = kSBins / T;
-    uint32_t h[BP], sum = 0;
+  constexpr int BP = kSBins / T;
+  uint32_t h[BP], sum = 0;
 #pragma unroll
-    for (int j = 0; j < BP; ++j) {
-      h[j] = sm.hist[threadIdx.x * BP + j];
-      sum += h[j];
-    }
-    uint32_t tot;
-    uint32_t ex = sblock_scan<T>(sum, sm.s_w, &tot);
+  for (int j = 0; j < BP; ++j) {
+    h[j] = sm.hist[threadIdx.x * BP + j];
+    sum += h[j];
+  }
+  uint32_t tot;
+  uint32_t ex = sblock_scan<T>(sum, sm.s_w, &tot);
 #pragma unroll
-    for (int j = 0; j < BP; ++j) {
-      sm.hist[threadIdx.x * BP + j] = ex;
-      ex += h[j];
-    }
-    if (threadIdx.x == 0) sm.hist[kSBins] = N;
-    __syncthreads();
+  for (int j = 0; j < BP; ++j) {
+    sm.hist[threadIdx.x * BP + j] = ex;
+    if (h[j] > 96u && ex < need) sm.misc[0] = 1;
+    ex += h[j];
+  }
+  if (threadIdx.x == 0) sm.hist[kSBins] = N;
+  __syncthreads();
+  if (!sm.misc[0]) {
 #pragma unroll
     for (int e = 0; e < E; ++e)
-      if (e * T + threadIdx.x < N) sm.buf[sm.hist[at[e] >> 16] + (at[e] & 0xFFFFu)] = c[e];
+      if (e * T + threadIdx.x < N) {
+        const uint32_t lo = sm.hist[at[e] >> 16];
+        if (lo < need) sm.buf[lo + (at[e] & 0xFFFFu)] = c[e];
+      }
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e)
       if (e * T + threadIdx.x < N) {
         const uint32_t b = at[e] >> 16;
         const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
-        uint32_t rk = lo;
-        for (uint32_t j = lo; j < hi; ++j) rk += sm.buf[j] > c[e] ? 1u : 0u;
-        emit(rk, c[e]);
+        if (lo < need) {
+          uint32_t rk = lo;
+          for (uint32_t j = lo; j < hi; ++j) rk += sm.buf[j] > c[e] ? 1u : 0u;
+          emit(rk, c[e]);
+        }
       }
     __syncthreads();
     return;
   }
-  // bitonic network over the next power of two; slots past CAP hold no
-  // element and rank lowest, so comparisons with them are skipped
-  constexpr uint32_t CAP = STraits<K>::kCap;
+  // 256 of the elements, evenly spread over the threads' order, sorted by
+  // their ranks, bound the bins instead (all elements are distinct, so the bins
+  // are even whatever the keys)
+  constexpr uint32_t S = kSSplit;
+  __syncthreads();
+  if (threadIdx.x == 0) sm.misc[0] = 0;
 #pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (e * T + threadIdx.x < N) sm.buf[e * T + threadIdx.x] = c[e];
-  __syncthreads();
-  uint32_t P = 2;
-  while (P < N) P <<= 1;
-  for (uint32_t i = N + threadIdx.x; i < (P < CAP ? P : CAP); i += T) sm.buf[i] = 0;
-  __syncthreads();
-  // ascending halves of a bitonic merge would need the slots past CAP to move
-  // up, so the network is the all-descending one: each merge first compares
-  // mirrored pairs, then halves
-  for (uint32_t size = 2; size <= P; size <<= 1) {
-    for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-      for (uint32_t i = threadIdx.x; i < (P >> 1); i += T) {
-        const uint32_t lo = 2 * i - (i & (stride - 1));
-        const uint32_t hi = stride == size >> 1 ? (lo | (size - 1)) - (lo & (size - 1)) : lo + stride;
-        if (hi < CAP) {
-          const C x = sm.buf[lo], y = sm.buf[hi];
-          if (x < y) { sm.buf[lo] = y; sm.buf[hi] = x; }
-        }
-      }
-      __syncthreads();
+  for (int e = 0; e < E; ++e) {
+    const uint32_t i = e * T + threadIdx.x;
+    if (i < N) {
+      // sample q is element (q * N) / S: element i is one of them, perhaps of
+      // several q when N < S (any of those will do)
+      const uint32_t q = (uint32_t)(((uint64_t)i * S + N - 1) / N);
+      if (q < S && (uint32_t)((uint64_t)q * N / S) == i)
+        for (uint32_t j = q; j < S && (uint32_t)((uint64_t)j * N / S) == i; ++j) sm.split[j] = c[e];
     }
   }
-  for (uint32_t i = threadIdx.x; i < N; i += T) emit(i, sm.buf[i]);
+  constexpr uint32_t SUB = 8, NB = (S + 1) * SUB;
+  for (uint32_t b = threadIdx.x; b < NB; b += T) sm.hist[b] = 0;
+  ssplit_sort<C, T, true>(sm.split, sm.rank);
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (e * T + threadIdx.x < N) {
+      uint32_t b = 0;  // splitters above c
+#pragma unroll
+      for (uint32_t w = S / 2; w >= 1; w >>= 1)
+        if (sm.split[b + w - 1] > c[e]) b += w;
+      if (b == S - 1 && sm.split[S - 1] > c[e]) b = S;
+      // up to eight equal pieces of the gap [lo, hi] that holds c
+      const C hi = b ? sm.split[b - 1] : mx, lo = b < S ? sm.split[b] : mn;
+      const uint32_t w = sbits((C)(hi - lo));
+      b = b * SUB + SUB - 1 - (uint32_t)((c[e] - lo) >> (w > 3 ? w - 3 : 0));
+      at[e] = (b << 16) | atomicAdd(&sm.hist[b], 1u);
+    }
   __syncthreads();
+  constexpr uint32_t PB = (NB + T - 1) / T;
+  uint32_t g[PB], gs = 0, all;
+#pragma unroll
+  for (uint32_t j = 0; j < PB; ++j) {
+    const uint32_t b = threadIdx.x * PB + j;
+    g[j] = b < NB ? sm.hist[b] : 0u;
+    gs += g[j];
+  }
+  uint32_t gx = sblock_scan<T>(gs, sm.s_w, &all);
+#pragma unroll
+  for (uint32_t j = 0; j < PB; ++j) {
+    const uint32_t b = threadIdx.x * PB + j;
+    if (b <= NB) sm.hist[b] = gx;
+    gx += g[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (e * T + threadIdx.x < N) {
+      const uint32_t lo = sm.hist[at[e] >> 16];
+      if (lo < need) sm.buf[lo + (at[e] & 0xFFFFu)] = c[e];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (e * T + threadIdx.x < N) {
+      const uint32_t b = at[e] >> 16;
+      const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
+      if (lo < need) {
+        uint32_t rk = lo;
+        for (uint32_t j = lo; j < hi; ++j) rk += sm.buf[j] > c[e] ? 1u : 0u;
+        emit(rk, c[e]);
+      }
+    }
+  __syncthreads();
+}
+
+template <typename K>
+struct SBucketShared : SSortShared<typename STraits<K>::Comp, STraits<K>::kCap, kSBucketThreads> {
+  uint32_t pre[kSMaxRows + 1];  // bucket elements in the rows before this one
+  uint32_t src[kSMaxRows];      // candidate index of the row's segment
+};
+
+template <typename K, int E, typename F>
+__device__ __forceinline__ void sbucket_sort(SBucketShared<K>& sm, typename STraits<K>::Comp (&c)[E], uint32_t N,
+                                             uint64_t need, F&& emit) {
+  ssort<typename STraits<K>::Comp, STraits<K>::kCap, kSBucketThreads, E>(sm, c, N, need, emit);
 }
 
 // f(get(i)) for the workgroup's i < count, four elements a thread at a time so
 // that their loads overlap.
-template <typename C, typename G, typename F>
+template <typename C, int TT, typename G, typename F>
 __device__ __forceinline__ void sbucket_each(uint64_t count, G&& get, F&& f) {
-  constexpr uint64_t T = kSBucketThreads;
+  constexpr uint64_t T = TT;
   uint64_t i = threadIdx.x;
   for (; i + 3 * T < count; i += 4 * T) {
     C x[4];
@@ -758,16 +866,13 @@ __device__ __forceinline__ void sbucket_each(uint64_t count, G&& get, F&& f) {
 
 // Collects the elements get(i), i < count, lying in [lo, hi] (N of them, at
 // most CAP, known to the caller) into registers in sort order's layout.
-template <typename K, int E, typename G>
-__device__ __forceinline__ uint32_t sbucket_collect(SBucketShared<K>& sm, typename STraits<K>::Comp (&c)[E],
-                                                    uint64_t count, typename STraits<K>::Comp lo,
-                                                    typename STraits<K>::Comp hi, G&& get) {
-  typedef typename STraits<K>::Comp C;
-  constexpr int T = kSBucketThreads;
-  constexpr uint32_t CAP = STraits<K>::kCap;
+template <typename C, uint32_t CAP, int T, int E, typename G>
+__device__ __forceinline__ uint32_t sbucket_collect(SSortShared<C, CAP, T>& sm, C (&c)[E],
+                                                    uint64_t count, C lo,
+                                                    C hi, G&& get) {
   if (threadIdx.x == 0) sm.misc[1] = 0;
   __syncthreads();
-  sbucket_each<C>(count, get, [&](C x) {
+  sbucket_each<C, T>(count, get, [&](C x) {
     if (x >= lo && x <= hi) {
       const uint32_t s = atomicAdd(&sm.misc[1], 1u);
       if (s < CAP) sm.buf[s] = x;
@@ -784,16 +889,14 @@ __device__ __forceinline__ uint32_t sbucket_collect(SBucketShared<K>& sm, typena
 
 // Histogram of the elements get(i) in [mn, mx] over kSBins linear bins
 // (descending: bin 0 holds mx), prefix-summed.  Returns the shift.
-template <typename K, typename G>
-__device__ __forceinline__ int sbucket_hist(SBucketShared<K>& sm, uint64_t count, typename STraits<K>::Comp mn,
-                                            typename STraits<K>::Comp mx, G&& get) {
-  typedef typename STraits<K>::Comp C;
-  constexpr int T = kSBucketThreads;
+template <typename C, uint32_t CAP, int T, typename G>
+__device__ __forceinline__ int sbucket_hist(SSortShared<C, CAP, T>& sm, uint64_t count, C mn,
+                                            C mx, G&& get) {
   const uint32_t bl = sbits((C)(mx - mn));
   const int sh = bl > 11 ? (int)bl - 11 : 0;
   for (int b = threadIdx.x; b <= kSBins; b += T) sm.hist[b] = 0;
   __syncthreads();
-  sbucket_each<C>(count, get, [&](C x) {
+  sbucket_each<C, T>(count, get, [&](C x) {
     if (x >= mn && x <= mx) atomicAdd(&sm.hist[(uint32_t)((mx - x) >> sh)], 1u);
   });
   __syncthreads();
@@ -817,16 +920,15 @@ __device__ __forceinline__ int sbucket_hist(SBucketShared<K>& sm, uint64_t count
 }
 
 // The element of 1-based rank `rank` among get(i), i < count (all distinct).
-template <typename K, typename G>
-__device__ __forceinline__ typename STraits<K>::Comp sbucket_select(SBucketShared<K>& sm, uint64_t count,
+template <typename C, uint32_t CAP, int T, typename G>
+__device__ __forceinline__ C sbucket_select(SSortShared<C, CAP, T>& sm, uint64_t count,
                                                                     uint64_t rank, G&& get) {
-  typedef typename STraits<K>::Comp C;
   C mn = 0, mx = ~(C)0;
   for (;;) {
-    const int sh = sbucket_hist<K>(sm, count, mn, mx, get);
+    const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
     if (threadIdx.x == 0) sm.misc[2] = 0;
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < (uint32_t)kSBins; b += kSBucketThreads)
+    for (uint32_t b = threadIdx.x; b < (uint32_t)kSBins; b += T)
       if (sm.hist[b] < rank && rank <= sm.hist[b + 1]) sm.misc[2] = b;
     __syncthreads();
     const uint32_t b = sm.misc[2];
@@ -842,10 +944,10 @@ __device__ __forceinline__ typename STraits<K>::Comp sbucket_select(SBucketShare
 // One workgroup per bucket.  B buckets from the rows (PLAIN false), or the
 // candidate buffer as the only bucket (PLAIN true).
 template <typename K, bool PLAIN>
-__global__ __launch_bounds__(kSBucketThreads, 4) void k_sbucket(
+__global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_sbucket(
     const K* __restrict__ keys, uint64_t n, uint32_t k, int kth_only, int levels, SCodec<K> cd, int L,
     const SCtl* __restrict__ ctl, const typename STraits<K>::Comp* __restrict__ cand, uint32_t cap1, uint32_t cap,
-    const SRow* __restrict__ rows, const uint16_t* __restrict__ offs, uint32_t pitch, K* __restrict__ out_vals,
+    uint32_t maxrows, const SRow* __restrict__ rows, const uint16_t* __restrict__ offs, uint32_t pitch, K* __restrict__ out_vals,
     uint32_t* __restrict__ out_idx, K* __restrict__ out_kth) {
   typedef typename STraits<K>::Comp C;
   constexpr int T = kSBucketThreads;
@@ -877,7 +979,7 @@ __global__ __launch_bounds__(kSBucketThreads, 4) void k_sbucket(
     count = nc;
     total = nc;
   } else {
-    bad = bad || nrows > (uint32_t)kSMaxRows;
+    bad = bad || nrows > maxrows;
     const uint32_t b = blockIdx.x;
     const uint32_t B = ctl->win.B;
     if (!bad) {
@@ -926,17 +1028,17 @@ __global__ __launch_bounds__(kSBucketThreads, 4) void k_sbucket(
     auto get = [&](uint64_t i) { return scomp<K>(senc<K>(keys[i], cd), (uint32_t)i, L, posmask); };
     if (kth_only) {
       if (blockIdx.x == 0) {
-        const C x = sbucket_select<K>(sm, n, k, get);
+        const C x = sbucket_select<C, CAP, T>(sm, n, k, get);
         if (threadIdx.x == 0) emit((uint64_t)k - 1, x);
       }
       return;
     }
     for (uint64_t j = blockIdx.x; j * CAP < k; j += gridDim.x) {
       const uint64_t r0 = j * CAP, r1 = r0 + CAP < k ? r0 + CAP : k;
-      const C hi = sbucket_select<K>(sm, n, r0 + 1, get);
-      const C lo = sbucket_select<K>(sm, n, r1, get);
-      const uint32_t N = sbucket_collect<K, E>(sm, c, n, lo, hi, get);
-      sbucket_sort<K, E>(sm, c, N, [&](uint32_t rk, C x) { emit(r0 + rk, x); });
+      const C hi = sbucket_select<C, CAP, T>(sm, n, r0 + 1, get);
+      const C lo = sbucket_select<C, CAP, T>(sm, n, r1, get);
+      const uint32_t N = sbucket_collect<C, CAP, T, E>(sm, c, n, lo, hi, get);
+      sbucket_sort<K, E>(sm, c, N, N, [&](uint32_t rk, C x) { emit(r0 + rk, x); });
     }
     return;
   }
@@ -955,7 +1057,7 @@ __global__ __launch_bounds__(kSBucketThreads, 4) void k_sbucket(
 #pragma unroll
     for (int e = 0; e < E; ++e)
       if (e * T + threadIdx.x < count) c[e] = get(e * T + threadIdx.x);
-    sbucket_sort<K, E>(sm, c, count, [&](uint32_t rk, C x) { emit(start + rk, x); });
+    sbucket_sort<K, E>(sm, c, count, k - start, [&](uint32_t rk, C x) { emit(start + rk, x); });
     return;
   }
   // a bucket larger than the LDS: descending runs of at most CAP elements,
@@ -964,37 +1066,16 @@ __global__ __launch_bounds__(kSBucketThreads, 4) void k_sbucket(
   C top = ~(C)0;  // elements above it are written
   while (done < count && start + done < k) {
     C mn = ~(C)0, mx = 0;
-    sbucket_each<C>(count, get, [&](C x) {
+    sbucket_each<C, T>(count, get, [&](C x) {
       if (x <= top) {
         mx = x > mx ? x : mx;
         mn = x < mn ? x : mn;
       }
     });
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      C p = mx, q = mn;
-      uint32_t* pp = reinterpret_cast<uint32_t*>(&p);
-      uint32_t* pq = reinterpret_cast<uint32_t*>(&q);
-#pragma unroll
-      for (uint32_t i = 0; i < sizeof(C) / 4; ++i) {
-        pp[i] = (uint32_t)__shfl_xor((int)pp[i], o);
-        pq[i] = (uint32_t)__shfl_xor((int)pq[i], o);
-      }
-      mx = p > mx ? p : mx;
-      mn = q < mn ? q : mn;
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { sm.red[threadIdx.x >> 6][0] = mx; sm.red[threadIdx.x >> 6][1] = mn; }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < T / 64; ++w) {
-      const C p = sm.red[w][0], q = sm.red[w][1];
-      mx = p > mx ? p : mx;
-      mn = q < mn ? q : mn;
-    }
+    sblock_minmax<C, T>(mx, mn, sm.red);
     C cut = mn;
     for (;;) {
-      const int sh = sbucket_hist<K>(sm, count, mn, mx, get);
+      const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
       // the most leading bins whose elements fit
       if (threadIdx.x == 0) sm.misc[3] = 0;
       __syncthreads();
@@ -1009,12 +1090,130 @@ __global__ __launch_bounds__(kSBucketThreads, 4) void k_sbucket(
       if (nb || sh == 0) break;
       mn = cut;  // the first bin alone is too large: look inside it
     }
-    const uint32_t N = sbucket_collect<K, E>(sm, c, count, cut, mx, get);
-    sbucket_sort<K, E>(sm, c, N, [&](uint32_t rk, C x) { emit(start + done + rk, x); });
+    const uint32_t N = sbucket_collect<C, CAP, T, E>(sm, c, count, cut, mx, get);
+    sbucket_sort<K, E>(sm, c, N, k - start - done, [&](uint32_t rk, C x) { emit(start + done + rk, x); });
     done += N;
     if (N == 0 || cut == 0) break;
     top = cut - 1;
   }
+}
+
+// ---------------------------------------------------------------------------
+// The whole problem in one workgroup.  n <= CAP: every element goes into the
+// sort.  Otherwise the r-th of 256 samples cuts the input to between k and
+// CAP elements in one streaming pass, the survivors collected in LDS and
+// sorted; when the sample misjudges that, the k-th element is found by
+// histograms of the input instead.  k <= CAP.
+template <typename K>
+struct SOne {
+  typedef typename STraits<K>::Comp C;
+  static constexpr uint32_t kCap = 65536 / sizeof(C);
+};
+
+template <typename K, int T>
+__global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t n, uint32_t k, uint32_t r,
+                                            int kth_only, SCodec<K> cd, int L, K* __restrict__ out_vals,
+                                            uint32_t* __restrict__ out_idx, K* __restrict__ out_kth) {
+  typedef typename STraits<K>::Comp C;
+  constexpr uint32_t CAP = T == 1024 ? SOne<K>::kCap : 1024;
+  constexpr int E = (int)(CAP / T);
+  constexpr int V = 16 / (int)sizeof(K), U = 4;
+  __shared__ SSortShared<C, CAP, T> sm;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t posmask = (uint32_t)((1ull << L) - 1);
+  auto get = [&](uint64_t i) { return scomp<K>(senc<K>(keys[i], cd), (uint32_t)i, L, posmask); };
+  C c[E];
+  uint32_t N = n;
+  if (r == 0) {
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e * T + threadIdx.x < n) c[e] = get(e * T + threadIdx.x);
+  } else {
+    const uint32_t head0 = (uint32_t)(((16 - (reinterpret_cast<uintptr_t>(keys) & 15u)) & 15u) / sizeof(K));
+    const uint32_t head = head0 < n ? head0 : n;
+    const uint32_t loads = (n - head) / V;  // whole 16-byte pieces
+    su32x4 nx[U];
+    auto load = [&](uint32_t g0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t g = g0 + u * T + threadIdx.x;
+        if (g < loads) nx[u] = *reinterpret_cast<const su32x4*>(keys + head + (size_t)g * V);
+      }
+    };
+    load(0);  // in flight while the samples are ranked
+    if (threadIdx.x < kSSplit) {
+      const uint32_t i = threadIdx.x;
+      const uint32_t lo = (uint32_t)((uint64_t)i * n / kSSplit), hi = (uint32_t)((uint64_t)(i + 1) * n / kSSplit);
+      sm.split[i] = get(lo + (uint32_t)(((uint64_t)shash(i) * (hi - lo)) >> 32));
+    }
+    if (threadIdx.x == 0) sm.misc[4] = 0;
+    ssplit_sort<C, T, false>(sm.split, sm.rank);
+    const C t = r <= kSSplit ? sm.split[r - 1] : (C)0;
+    const K tkey = (K)(t >> L);
+    const uint32_t tpos = scomp_pos<C>(t, posmask);
+    for (uint32_t g0 = 0; g0 < loads; g0 += U * T) {
+      K v[U][V];
+#pragma unroll
+      for (int u = 0; u < U; ++u) __builtin_memcpy(v[u], &nx[u], 16);
+      load(g0 + U * T);
+      uint64_t bal[U][V];
+      uint32_t cnt = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t g = g0 + u * T + threadIdx.x, p = head + g * V;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          v[u][e] = senc<K>(v[u][e], cd);
+          bal[u][e] = __ballot(g < loads && (v[u][e] > tkey || (v[u][e] == tkey && p + e <= tpos)));
+          cnt += (uint32_t)__popcll(bal[u][e]);
+        }
+      }
+      if (cnt == 0) continue;
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&sm.misc[4], cnt);
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t p = head + (g0 + u * T + threadIdx.x) * V;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          const uint32_t at = base + mbcnt(bal[u][e]);
+          if (__builtin_amdgcn_inverse_ballot_w64(bal[u][e]) && at < CAP)
+            sm.buf[at] = scomp<K>(v[u][e], p + e, L, posmask);
+          base += (uint32_t)__popcll(bal[u][e]);
+        }
+      }
+    }
+    if (threadIdx.x < 64) {  // fewer than V keys before the pieces and after them
+      const uint32_t rest = n - head - loads * V;
+      const uint32_t p = lane < head ? lane : head + loads * V + (lane - head);
+      const K e = lane < head + rest ? senc<K>(keys[p], cd) : (K)0;
+      if (lane < head + rest && (e > tkey || (e == tkey && p <= tpos))) {
+        const uint32_t at = atomicAdd(&sm.misc[4], 1u);
+        if (at < CAP) sm.buf[at] = scomp<K>(e, p, L, posmask);
+      }
+    }
+    __syncthreads();
+    N = sm.misc[4];
+    if (N < k || N > CAP) {
+      const C kth = sbucket_select<C, CAP, T>(sm, n, k, get);
+      N = sbucket_collect<C, CAP, T, E>(sm, c, n, kth, ~(C)0, get);
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * T + threadIdx.x < N) c[e] = sm.buf[e * T + threadIdx.x];
+    }
+    __syncthreads();
+  }
+  ssort<C, CAP, T, E>(sm, c, N, k, [&](uint32_t slot, C x) {
+    if (slot >= k) return;
+    const K v = sdec<K>((K)(x >> L), cd);
+    if (!kth_only) {
+      if (out_vals) out_vals[slot] = v;
+      if (out_idx) out_idx[slot] = scomp_pos<C>(x, posmask);
+    }
+    if (out_kth && slot == k - 1) *out_kth = v;
+  });
 }
 
 }  // namespace drtopk

@@ -18,6 +18,7 @@ struct SPlan {
   bool wide = false;      // 8-byte keys
   uint32_t head = 0;      // keys before the first 16-byte boundary
   bool kth_only = false;
+  bool one = false;       // one workgroup takes the whole problem
   int levels = 1;         // 2: the first filter's candidates are sampled and partitioned again
   int plain = 0;          // one bucket: the candidates are sorted by one workgroup
   uint64_t n = 0;
@@ -28,6 +29,7 @@ struct SPlan {
   SWin win = {};          // level 1's window
   uint32_t bmax = 1;      // most buckets of the partitioned level
   uint32_t cap1 = 0, cap = 0;    // candidates kept by level 1, by the partitioned level
+  uint32_t rows = 0;      // rows of the offset table
   uint32_t pitch = 0;            // entries of a row of the offset table
   uint64_t codec_a = 0, codec_c = 0;
   size_t off_ctl = 0, off_smp = 0, off_sorted = 0, off_c1 = 0, off_cand = 0, off_rows = 0, off_offs = 0;

@@ -1,5 +1,4 @@
-"""The sampled path (plain topk_select / kth_select calls beyond one workgroup)
-element by element against the oracle: its smallest inputs, tile and stage
+"""The sampled path (plain topk_select / kth_select calls) element by element against the oracle: its smallest inputs, tile and stage
 remainders, unaligned heads, open and two-sided windows, one bucket, many
 buckets and two levels, keys clustered on few values, ties and all-equal keys,
 every bit pattern of a float, and inputs whose sampled positions misjudge the
@@ -68,6 +67,19 @@ def test_against_oracle(kind):
         compare(x, dt, k, j % 3 != 1, f"{kind} n={n} k={k} off={off}", off)
 
 
+@pytest.mark.parametrize("kind", KINDS)
+def test_one_workgroup(kind):
+    # the sizes one workgroup takes: every element sorted (its LDS exactly full
+    # and beyond), the cut by 256 samples, heads and remainders of 16-byte loads,
+    # few and most of the elements wanted
+    cases = [(1, 1), (3, 2), (257, 256), (1024, 3), (1025, 1025), (4096, 4095), (4097, 5), (8192, 8192), (8193, 100),
+             (40001, 2), (65536, 1500), (65535, 2500)]
+    for j, (n, k) in enumerate(cases):
+        x, dt = keys_of(kind, n, 9100 + j)
+        off = 0 if x.dtype.itemsize == 8 else j % 4
+        compare(x, dt, k, j % 3 != 1, f"{kind} n={n} k={k} off={off}", off)
+
+
 # sample i of M lies in stratum [i n / M, (i + 1) n / M) at this hash of i
 def sampled_positions(n, M):
     h = np.arange(M, dtype=np.uint64)
@@ -92,6 +104,15 @@ def test_misjudged_samples(wide, high):
         p = sampled_positions(n, M)
         x[p] ^= np.array(1 << (63 if wide else 31), x.dtype)
         compare(x, dt, k, True, f"misjudged {dt} k={k} high={high}")
+
+
+@pytest.mark.parametrize("high", [True, False])
+def test_misjudged_samples_of_one_workgroup(high):
+    n, k = 50000, 300
+    x, _ = synth.keys("uniform_u32", n, 33)
+    x = x >> 1 if high else x | (1 << 31)
+    x[sampled_positions(n, 256)] ^= np.uint32(1 << 31)
+    compare(x, "u32", k, True, f"misjudged one workgroup high={high}")
 
 
 @pytest.mark.parametrize("dtype", ["f32", "i64"])
