@@ -409,34 +409,63 @@ bool take_sampled(const SPlan& sp, size_t total) {
          g_cap_override.load(std::memory_order_relaxed) == 0;
 }
 
+// The sampled path's plan of a call; not on if it does not take the call.
+// `other()` gives the other path's workspace, asked for only when it decides.
+template <typename F>
+SPlan sampled_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, const SPayload& pay,
+                   F&& other) {
+  SPlan sp;
+  sample_plan(keys, n, k, dtype, kth_only, &sp);
+  sp.on = take_sampled(sp, sp.on && sp.total > kSampledFree ? other() : 0);
+  sp.pay = pay;
+  return sp;
+}
+
+// Enqueues a call that the sampled path takes.  One workgroup needs no
+// workspace, so such a call touches no shared state.
+int run_sampled(const SPlan& sp, const void* keys, void* out_vals, uint32_t* out_idx, void* out_kth, void* stream) {
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (sp.one) return sample_enqueue(sp, keys, nullptr, out_vals, out_idx, out_kth, s, false);
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return DRTOPK_EDEVICE;
+  Workspace* ws = workspace_entry(dev, stream);
+  if (!ws) return DRTOPK_ENOMEM;
+  std::lock_guard<std::mutex> g(ws->mu);
+  const int st = ensure_bytes(ws, sp.total);
+  if (st) return st;
+  return sample_enqueue(sp, keys, ws->ptr, out_vals, out_idx, out_kth, s, !sp.wide);
+}
+
 // Workspace of a call: the larger of the sampled path's, where it is taken,
 // and `total`, the other path's.
 size_t larger_workspace(uint64_t n, uint32_t k, int dtype, size_t total) {
   alignas(16) static const uint32_t aligned[4] = {0, 0, 0, 0};
   SPlan sp;
-  sample_plan(aligned, n, k, dtype, false, false, &sp);
+  sample_plan(aligned, n, k, dtype, false, &sp);
   return take_sampled(sp, total) && sp.total > total ? sp.total : total;
 }
 
-// Runs the whole path; `after` runs under the workspace lock after the
+// Runs the whole path.  Calls that the sampled path takes end there, payloads
+// (pay) included; otherwise `after` runs under the workspace lock after the
 // enqueue, with the plan, the workspace pointer and the stream.  pos_in_ws:
 // with out_idx NULL the output positions go to a workspace segment
 // (Plan::off_pos) that `after` may read on the stream.
 template <typename F>
 int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals, uint32_t* out_idx,
                void* out_kth, bool kth_only, const drtopk_options_t* opt, void* stream, F&& after,
-               bool filter_only = false, bool pos_in_ws = false, bool counters = false) {
+               bool filter_only = false, bool pos_in_ws = false, bool counters = false, SPayload pay = {}) {
   int st = check_args(keys, n, k, dtype);
   if (st) return st;
   Plan p;
   const bool ws_pos = pos_in_ws && !out_idx && !kth_only;
+  if (!opt && !counters) {
+    const SPlan sp = sampled_plan(keys, n, k, dtype, kth_only, pay, [&] {
+      return make_plan(keys, n, k, dtype, opt, &p, ws_pos) == DRTOPK_OK ? p.total : (size_t)0;
+    });
+    if (sp.on) return run_sampled(sp, keys, out_vals, out_idx, out_kth, stream);
+  }
   st = make_plan(keys, n, k, dtype, opt, &p, ws_pos);
   if (st) return st;
-  SPlan sp;
-  if (!opt && !counters) {
-    sample_plan(keys, n, k, dtype, kth_only, ws_pos, &sp);
-    sp.on = take_sampled(sp, p.total);
-  }
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DRTOPK_EDEVICE;
   Workspace* ws = workspace_entry(dev, stream);
@@ -444,16 +473,12 @@ int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_va
   std::lock_guard<std::mutex> g(ws->mu);
   st = ensure_record(ws);
   if (st) return st;
-  st = ensure_bytes(ws, sp.on ? sp.total : p.total);
+  st = ensure_bytes(ws, p.total);
   if (st) return st;
   p.rec = ws->rec;
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (sp.on) p.off_pos = sp.off_pos;
   if (ws_pos) out_idx = at<uint32_t>(ws->ptr, p.off_pos);
-  if (sp.on)
-    st = sample_enqueue(sp, keys, ws->ptr, out_vals, out_idx, out_kth, s, true);
-  else
-    st = enqueue_plan(p, keys, ws->ptr, out_vals, out_idx, out_kth, kth_only, filter_only, s);
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  st = enqueue_plan(p, keys, ws->ptr, out_vals, out_idx, out_kth, kth_only, filter_only, s);
   if (st) return st;
   return after(p, ws->ptr, s);
 }
@@ -463,18 +488,20 @@ int run_common(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_va
 template <typename F>
 int run_wide(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals, uint32_t* out_idx, void* out_kth,
              bool kth_only, const drtopk_options_t* opt, void* stream, F&& after, bool pos_in_ws = false,
-             bool counters = false) {
+             bool counters = false, SPayload pay = {}) {
   int st = check_args(keys, n, k, dtype);
   if (st) return st;
   WPlan p;
   const bool ws_pos = pos_in_ws && !out_idx && !kth_only;
-  st = wide_plan(n, k, dtype, (reinterpret_cast<uintptr_t>(keys) & 15u) == 0, opt, &p, ws_pos);
-  if (st) return st;
-  SPlan sp;
+  const bool vec = (reinterpret_cast<uintptr_t>(keys) & 15u) == 0;
   if (!opt && !counters) {
-    sample_plan(keys, n, k, dtype, kth_only, ws_pos, &sp);
-    sp.on = take_sampled(sp, p.total);
+    const SPlan sp = sampled_plan(keys, n, k, dtype, kth_only, pay, [&] {
+      return wide_plan(n, k, dtype, vec, opt, &p, ws_pos) == DRTOPK_OK ? p.total : (size_t)0;
+    });
+    if (sp.on) return run_sampled(sp, keys, out_vals, out_idx, out_kth, stream);
   }
+  st = wide_plan(n, k, dtype, vec, opt, &p, ws_pos);
+  if (st) return st;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DRTOPK_EDEVICE;
   Workspace* ws = workspace_entry(dev, stream);
@@ -482,15 +509,11 @@ int run_wide(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals
   std::lock_guard<std::mutex> g(ws->mu);
   st = ensure_record(ws);
   if (st) return st;
-  st = ensure_bytes(ws, sp.on ? sp.total : p.total);
+  st = ensure_bytes(ws, p.total);
   if (st) return st;
-  if (sp.on) p.off_pos = sp.off_pos;
   if (ws_pos) out_idx = at<uint32_t>(ws->ptr, p.off_pos);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (sp.on)
-    st = sample_enqueue(sp, keys, ws->ptr, out_vals, out_idx, out_kth, s, false);
-  else
-    st = wide_enqueue(p, keys, ws->ptr, ws->rec, out_vals, out_idx, out_kth, kth_only, s);
+  st = wide_enqueue(p, keys, ws->ptr, ws->rec, out_vals, out_idx, out_kth, kth_only, s);
   if (st) return st;
   return after(p, ws->ptr, s);
 }
@@ -823,7 +846,7 @@ int topk_select_noalloc(const void* keys, uint64_t n, uint32_t k, int dtype, voi
     void* ws = static_cast<char*>(base) + kScratchRec;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     SPlan sp;
-    sample_plan(keys, n, k, dtype, false, false, &sp);
+    sample_plan(keys, n, k, dtype, false, &sp);
     if (take_sampled(sp, wide ? wp.total : p.total))
       return sample_enqueue(sp, keys, ws, out_vals, out_idx, nullptr, s, false);
     if (wide) return wide_enqueue(wp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, false, s);
@@ -1142,6 +1165,7 @@ int topk_select_payload(const void* keys, uint64_t n, uint32_t k, int dtype, con
     // the gather is enqueued under the workspace lock, so with out_idx NULL it
     // reads the positions from the workspace before any later call on the
     // stream can overwrite them
+    const SPayload pay{payload, out_payload, (uint32_t)payload_bytes, 0};
     auto gather = [&](size_t off_pos, void* ws, hipStream_t s) {
       const uint32_t* idx = out_idx ? out_idx : at<uint32_t>(ws, off_pos);
       const unsigned g = grid_for(k, 256, 1024);
@@ -1155,9 +1179,10 @@ int topk_select_payload(const void* keys, uint64_t n, uint32_t k, int dtype, con
     };
     if (wide_dtype(dtype))
       return run_wide(keys, n, k, dtype, out_vals, out_idx, nullptr, false, nullptr, stream,
-                      [&](const WPlan& p, void* ws, hipStream_t s) { return gather(p.off_pos, ws, s); }, true);
+                      [&](const WPlan& p, void* ws, hipStream_t s) { return gather(p.off_pos, ws, s); }, true, false, pay);
     return run_common(keys, n, k, dtype, out_vals, out_idx, nullptr, false, nullptr, stream,
-                      [&](const Plan& p, void* ws, hipStream_t s) { return gather(p.off_pos, ws, s); }, false, true);
+                      [&](const Plan& p, void* ws, hipStream_t s) { return gather(p.off_pos, ws, s); }, false, true,
+                      false, pay);
   } catch (...) {
     return DRTOPK_EDEVICE;
   }

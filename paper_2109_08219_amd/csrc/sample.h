@@ -41,8 +41,10 @@ constexpr int kSMaxRows = 1024;      // most rows of the offset table
 constexpr int kSPartThreads = 1024;
 constexpr int kSBucketThreads = 512;
 constexpr int kSRankThreads = 512;
-constexpr int kSRankPer = 32;        // samples ranked by one workgroup
-constexpr int kSFilterThreads = 256;
+constexpr int kSRankPer = 16;        // samples ranked by one workgroup
+constexpr int kSFilterThreads = 1024;
+constexpr uint32_t kSCells = 1024;   // cells of k_spart's bucket lookup
+constexpr uint32_t kSCrowd = 128;    // elements of a bin that are still ranked one against the other
 constexpr uint32_t kSSplit = 256;    // samples of a workgroup's own sort or threshold
 
 template <typename K>
@@ -50,17 +52,21 @@ struct STraits;
 template <>
 struct STraits<uint32_t> {
   typedef uint64_t Comp;
-  static constexpr int kStage = 8192;   // candidates staged by a workgroup of k_spart
+  static constexpr int kStage = 12288;  // candidates staged by a workgroup of k_spart
+  static constexpr int kTile = 8192;    // elements it reads at a time
   static constexpr int kCap = 7680;     // elements sorted by a workgroup of k_sbucket (two fit a CU)
   static constexpr int kMaxB = 3072;    // most buckets
+  static constexpr int kList = 65536;   // candidates that every bucket's workgroup may read
   static constexpr int kTarget = 2048;  // elements a bucket is planned for
 };
 template <>
 struct STraits<uint64_t> {
   typedef su128 Comp;
-  static constexpr int kStage = 4096;
+  static constexpr int kStage = 6144;
+  static constexpr int kTile = 4096;
   static constexpr int kCap = 3584;
   static constexpr int kMaxB = 1536;
+  static constexpr int kList = 32768;
   static constexpr int kTarget = 1024;
 };
 
@@ -77,6 +83,17 @@ template <typename K>
 __device__ __forceinline__ K sdec(K u, SCodec<K> cd) {
   const K x = u ^ cd.c;
   return x ^ (ssign(x) & cd.a);
+}
+
+// A value that every lane holds, in scalar registers.
+template <typename T>
+__device__ __forceinline__ T suniform(T v) {
+  uint32_t w[sizeof(T) / 4];
+  __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(T) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
 }
 
 __device__ __forceinline__ uint32_t sbits(uint64_t x) { return x ? 64u - (uint32_t)__clzll((long long)x) : 0u; }
@@ -99,7 +116,8 @@ struct SCtl {
   uint64_t alloc;   // partitioned level: rows << 32 | candidates
   uint64_t pad1[15];
   SWin win;         // window of the partitioned level
-  uint32_t pad2[24];
+  uint32_t rare;    // a bucket kernel without the rare ways met one
+  uint32_t pad2[23];
 };
 
 struct SRow {
@@ -125,21 +143,26 @@ __device__ __forceinline__ uint32_t shash(uint32_t x) {
 // The launch also clears the state of the kernels after it.
 constexpr uint32_t kSKeep = 16;
 
+// With TOP the workgroup has four threads per sample, each counting the larger
+// ones in a quarter of the 256.
 template <typename K, bool ARR, bool TOP>
-__global__ __launch_bounds__(256) void k_sgather(const K* __restrict__ keys,
+__global__ __launch_bounds__(TOP ? 1024 : 256) void k_sgather(const K* __restrict__ keys,
                                                  const typename STraits<K>::Comp* __restrict__ arr, uint64_t n,
                                                  uint32_t cap1, uint32_t k, uint32_t M, SCodec<K> cd, int L,
                                                  SWin win, int kth, uint32_t bmax, SCtl* ctl,
                                                  typename STraits<K>::Comp* __restrict__ smp,
                                                  typename STraits<K>::Comp* __restrict__ sorted) {
   typedef typename STraits<K>::Comp C;
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  uint32_t i = blockIdx.x * 256 + (threadIdx.x & 255u);
+  // M is a power of two here: a permutation that scatters neighbouring strata
+  // over the workgroups, so that a sorted input's top samples do not meet in one
+  if constexpr (TOP) i = (i * 0x9E3779B1u) & (M - 1);
   uint64_t count = n;
   if constexpr (ARR) {
     count = (uint32_t)ctl->alloc1;
     if (count > cap1 || count < k) return;  // level 1 misjudged: the bucket kernel answers from the input
   }
-  if (i == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     if constexpr (ARR) {
       SWin w = {};
       sample_window((double)count, (double)k, (double)M, kth != 0, &w);
@@ -148,16 +171,19 @@ __global__ __launch_bounds__(256) void k_sgather(const K* __restrict__ keys,
     } else {
       ctl->alloc1 = 0;
       ctl->alloc = 0;
+      ctl->rare = 0;
       ctl->win = win;
     }
   }
   const uint32_t posmask = (uint32_t)((1ull << L) - 1);
-  const uint64_t lo = (uint64_t)i * count / M, hi = (uint64_t)(i + 1) * count / M;
   C x = 0;
-  if (hi > lo) {
-    const uint64_t p = lo + (uint64_t)(((uint64_t)shash(i) * (hi - lo)) >> 32);
-    if constexpr (ARR) x = arr[p];
-    else x = scomp<K>(senc<K>(keys[p], cd), (uint32_t)p, L, posmask);
+  if (!TOP || threadIdx.x < 256) {
+    const uint64_t lo = (uint64_t)i * count / M, hi = (uint64_t)(i + 1) * count / M;
+    if (hi > lo) {
+      const uint64_t p = lo + (uint64_t)(((uint64_t)shash(i) * (hi - lo)) >> 32);
+      if constexpr (ARR) x = arr[p];
+      else x = scomp<K>(senc<K>(keys[p], cd), (uint32_t)p, L, posmask);
+    }
   }
   if constexpr (ARR) {
     // with fewer elements than samples the empty strata are composites 0,
@@ -168,29 +194,51 @@ __global__ __launch_bounds__(256) void k_sgather(const K* __restrict__ keys,
     smp[i] = x;
   } else {
     __shared__ C s[256];
-    s[threadIdx.x] = x;
+    __shared__ uint32_t part[4][256];
+    const uint32_t me = threadIdx.x & 255u, quarter = threadIdx.x >> 8;
+    if (threadIdx.x < 256) s[me] = x;
     __syncthreads();
+    x = s[me];
     uint32_t rk = 0;
 #pragma unroll 16
-    for (uint32_t j = 0; j < 256; ++j) rk += s[j] > x ? 1u : 0u;
-    if (rk < kSKeep) smp[blockIdx.x * kSKeep + rk] = x;
+    for (uint32_t j = 0; j < 64; ++j) rk += s[quarter * 64 + j] > x ? 1u : 0u;
+    part[quarter][me] = rk;
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      rk = part[0][me] + part[1][me] + part[2][me] + part[3][me];
+      if (rk < kSKeep) smp[blockIdx.x * kSKeep + rk] = x;
+    }
   }
 }
 
 // All-pairs ranks: a wave holds J * 64 samples in registers and compares them
 // with one sample at a time, a scalar operand, so 64 comparisons are one
-// vector compare and a scalar bit count.  J * 512 = m samples.
+// vector compare and a scalar bit count.  J * 512 = m samples.  The workgroup's
+// own 16 samples reach the scalar side by lane reads: scalar loads in the loop
+// had it wait for memory once per four (m = 4096: 6.7 us with 32 samples a
+// workgroup, the launch 2 of them).
+template <typename C>
+__device__ __forceinline__ C sread_lane(C v, int lane) {
+  uint32_t w[sizeof(C) / 4];
+  __builtin_memcpy(w, &v, sizeof(C));
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(C) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readlane((int)w[i], lane);
+  __builtin_memcpy(&v, w, sizeof(C));
+  return v;
+}
+
 template <typename C, int J>
 __global__ __launch_bounds__(kSRankThreads) void k_srank(const C* __restrict__ smp, C* __restrict__ sorted) {
   __shared__ uint32_t cnt[kSRankPer][kSRankThreads / 64];
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint32_t i0 = blockIdx.x * kSRankPer;
+  const C own = smp[i0 + lane % kSRankPer];
   C v[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) v[j] = smp[(j * (kSRankThreads / 64) + wave) * 64 + lane];
-  const uint32_t i0 = blockIdx.x * kSRankPer;
-#pragma unroll 4
+#pragma unroll
   for (int ii = 0; ii < kSRankPer; ++ii) {
-    const C x = smp[i0 + ii];
+    const C x = sread_lane<C>(own, ii);
     uint32_t c = 0;
 #pragma unroll
     for (int j = 0; j < J; ++j) c += (uint32_t)__popcll(__ballot(v[j] > x));
@@ -201,36 +249,48 @@ __global__ __launch_bounds__(kSRankThreads) void k_srank(const C* __restrict__ s
     uint32_t r = 0;
 #pragma unroll
     for (int w = 0; w < kSRankThreads / 64; ++w) r += cnt[threadIdx.x][w];
-    sorted[r] = smp[i0 + threadIdx.x];
+    sorted[r] = own;
   }
 }
 
 // ---------------------------------------------------------------------------
 // Streaming filter for one bucket or a first level.  Tiles of U loads per wave
 // are dealt to the workgroups in turn, so a dense stretch of candidates
-// (sorted input) is shared by many.  A wave keeps its candidates in its own
-// LDS slots and its fill level in a register; no barrier before the end.
+// (sorted input) is shared by many; a wave's next tile is in flight while it
+// works on the current one.  A wave keeps its candidates in its own LDS slots
+// and its fill level in a register; no barrier before the end, and one device
+// atomic a workgroup for what is left then (they are served one at a time,
+// 11.5 ns each, hence few large workgroups: two of 1024 threads a CU).
 // head: keys before the first 16-byte boundary.
-constexpr uint32_t kSWaveSlots = 512;
-
 template <typename K, int U>
-__global__ __launch_bounds__(kSFilterThreads) void k_sfilter(const K* __restrict__ keys, uint64_t n, uint32_t head,
-                                                             SCodec<K> cd, int L, uint32_t r, uint32_t m,
-                                                             const typename STraits<K>::Comp* __restrict__ sorted,
-                                                             uint64_t* alloc,
-                                                             typename STraits<K>::Comp* __restrict__ out,
-                                                             uint32_t cap) {
+__global__ __launch_bounds__(kSFilterThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_sfilter(
+    const K* __restrict__ keys, uint64_t n, uint32_t head, SCodec<K> cd, int L, uint32_t r, uint32_t m,
+    const typename STraits<K>::Comp* __restrict__ sorted, uint64_t* alloc,
+    typename STraits<K>::Comp* __restrict__ out, uint32_t cap) {
   typedef typename STraits<K>::Comp C;
   constexpr int V = 16 / (int)sizeof(K);  // keys of a 128-bit load
   constexpr uint32_t step = 64 * V;       // keys of a wave's load
-  __shared__ C stage[kSFilterThreads / 64][kSWaveSlots];
-  __shared__ uint32_t s_n[kSFilterThreads / 64];
+  constexpr uint32_t NW = kSFilterThreads / 64, SLOTS = 4096 / sizeof(C);
+  __shared__ C stage[NW][SLOTS];
+  __shared__ uint32_t s_n[NW];
   __shared__ uint32_t s_base;
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  constexpr uint64_t tile = (uint64_t)step * U * NW;
+  const uint64_t full = (n - head) / tile;
+  su32x4 nx[U];
+  auto load = [&](uint64_t tl) {
+    if (tl >= full) return;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      nx[u] = __builtin_nontemporal_load(
+          reinterpret_cast<const su32x4*>(keys + head + tl * tile + (u * NW + wave) * step + lane * V));
+  };
+  load(blockIdx.x);
   const uint32_t posmask = (uint32_t)((1ull << L) - 1);
-  const C t = r <= m ? sorted[r - 1] : (C)0;
+  const C t = suniform(r <= m ? sorted[r - 1] : (C)0);
   const K tkey = (K)(t >> L);
   const uint32_t tpos = scomp_pos<C>(t, posmask);
+  const K tnext = tkey + 1 ? tkey + 1 : tkey;
   C* st = stage[wave];
   uint32_t fill = 0;
   auto flush = [&]() {
@@ -248,17 +308,11 @@ __global__ __launch_bounds__(kSFilterThreads) void k_sfilter(const K* __restrict
       fill += (uint32_t)__popcll(b);
     }
   };
-  constexpr uint64_t tile = (uint64_t)step * U * (kSFilterThreads / 64);
-  const uint64_t full = (n - head) / tile;
   for (uint64_t tl = blockIdx.x; tl < full; tl += gridDim.x) {
-    const uint64_t lo = head + tl * tile + wave * step;
     K v[U][V];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const su32x4 x = __builtin_nontemporal_load(
-          reinterpret_cast<const su32x4*>(keys + lo + (uint64_t)u * step * (kSFilterThreads / 64) + lane * V));
-      __builtin_memcpy(v[u], &x, 16);
-    }
+    for (int u = 0; u < U; ++u) __builtin_memcpy(v[u], &nx[u], 16);
+    load(tl + gridDim.x);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       K mx = 0;
@@ -267,9 +321,10 @@ __global__ __launch_bounds__(kSFilterThreads) void k_sfilter(const K* __restrict
         v[u][c] = senc<K>(v[u][c], cd);
         mx = v[u][c] > mx ? v[u][c] : mx;
       }
-      if (__ballot(mx >= tkey)) {
-        const uint32_t p = (uint32_t)(lo + (uint64_t)u * step * (kSFilterThreads / 64)) + lane * V;
-        if (fill + step > kSWaveSlots) flush();
+      // keys equal to the cut's matter up to its position only
+      const uint32_t p1 = head + (uint32_t)(tl * tile) + (u * NW + wave) * step, p = p1 + lane * V;
+      if (__ballot(mx >= (p1 > tpos ? tnext : tkey))) {
+        if (fill + step > SLOTS) flush();
 #pragma unroll
         for (int c = 0; c < V; ++c)
           push(v[u][c] > tkey || (v[u][c] == tkey && p + c <= tpos), v[u][c], p + c);
@@ -278,20 +333,19 @@ __global__ __launch_bounds__(kSFilterThreads) void k_sfilter(const K* __restrict
   }
   // the keys the full tiles leave: the ones behind them, 64 a wave, then the head
   const uint64_t rest = full * tile;  // offset from the head
-  for (uint64_t q0 = rest + ((uint64_t)blockIdx.x * (kSFilterThreads / 64) + wave) * 64; q0 < n;
-       q0 += (uint64_t)gridDim.x * (kSFilterThreads / 64) * 64) {
-    if (fill + 64 > kSWaveSlots) flush();
+  for (uint64_t q0 = rest + ((uint64_t)blockIdx.x * NW + wave) * 64; q0 < n; q0 += (uint64_t)gridDim.x * NW * 64) {
+    if (fill + 64 > SLOTS) flush();
     const uint64_t q = q0 + lane;
     const uint64_t p = q < n - head ? q + head : q - (n - head);
     const K e = q < n ? senc<K>(keys[p], cd) : 0;
     push(q < n && (e > tkey || (e == tkey && (uint32_t)p <= tpos)), e, (uint32_t)p);
   }
-  // the waves' remainders leave together: one device atomic per workgroup
+  // the waves' remainders leave together
   if (lane == 0) s_n[wave] = fill;
   __syncthreads();
   uint32_t off = 0, tot = 0;
 #pragma unroll
-  for (uint32_t w = 0; w < kSFilterThreads / 64; ++w) {
+  for (uint32_t w = 0; w < NW; ++w) {
     if (w < wave) off += s_n[w];
     tot += s_n[w];
   }
@@ -304,17 +358,24 @@ __global__ __launch_bounds__(kSFilterThreads) void k_sfilter(const K* __restrict
 }
 
 // ---------------------------------------------------------------------------
+// Inclusive prefix sum over the wave by DPP: shifts inside the rows of 16
+// lanes, then each row's last lane added to the rows after it.
+__device__ __forceinline__ uint32_t swave_scan(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast 15: rows 1 and 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast 31: rows 2 and 3
+  return x;
+}
+
 // Block-wide exclusive prefix sums of one value per thread (T threads, whole
 // waves); *total is the sum.  s_w: T / 64 words.
 template <int T>
 __device__ __forceinline__ uint32_t sblock_scan(uint32_t x, uint32_t* s_w, uint32_t* total) {
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t y = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t z = (uint32_t)__shfl_up((int)y, o);
-    if ((int)lane >= o) y += z;
-  }
+  const uint32_t y = swave_scan(x);
   __syncthreads();
   if (lane == 63) s_w[wave] = y;
   __syncthreads();
@@ -327,6 +388,34 @@ __device__ __forceinline__ uint32_t sblock_scan(uint32_t x, uint32_t* s_w, uint3
   }
   *total = tot;
   return off + y - x;
+}
+
+// The same with two more values, of which only the sums are wanted.
+template <int T>
+__device__ __forceinline__ void sblock_scan3(uint32_t x, uint32_t a, uint32_t b, uint32_t (*s_w)[3], uint32_t* ex,
+                                             uint32_t* tx, uint32_t* ta, uint32_t* tb) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t y = swave_scan(x);
+  a = swave_scan(a);
+  b = swave_scan(b);
+  if (lane == 63) {
+    s_w[wave][0] = y;
+    s_w[wave][1] = a;
+    s_w[wave][2] = b;
+  }
+  __syncthreads();
+  uint32_t off = 0, sx = 0, sa = 0, sb = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < T / 64; ++w) {
+    if (w < wave) off += s_w[w][0];
+    sx += s_w[w][0];
+    sa += s_w[w][1];
+    sb += s_w[w][2];
+  }
+  *ex = off + y - x;
+  *tx = sx;
+  *ta = sa;
+  *tb = sb;
 }
 
 // Lower bounds of the window's buckets, highest first, from the sorted samples
@@ -343,33 +432,54 @@ __device__ __forceinline__ void sfill_splitters(C* split, const SWin& w, uint32_
     return;
   }
   const uint32_t q0 = w.a ? w.a : 1u, top = w.a ? 0u : kSTop;
-  const uint32_t lgP = 31u - (uint32_t)__clz((int)w.P), groups = (w.B - top) >> lgP;
-  for (uint32_t g = t; g < groups; g += T) {
+  const uint32_t lgP = 31u - (uint32_t)__clz((int)w.P), thin = w.a ? 0u : kSThin;
+  auto sample = [&](uint32_t q) { return q <= m ? sorted[q - 1] : (C)0; };
+  const uint32_t nthin = thin < w.s ? thin : w.s, per = thin_splits(w.P);
+  // thin groups, a thread a splitter: its slot is the number of samples and
+  // cuts above it
+  for (uint32_t i = t; i < nthin * per; i += T) {
+    const uint32_t g = i / per, j = i % per, cuts = w.P - 1;
+    const uint32_t qa = q0 + g * kSGroup, qb = qa + kSGroup < w.r ? qa + kSGroup : w.r;
+    const C x0 = sample(qa), step = (x0 - sample(qb)) >> lgP;
+    C v;
+    uint32_t slot;
+    if (j < cuts) {
+      v = x0 - step * (j + 1);
+      slot = j;
+      for (uint32_t q = qa + 1; q <= qa + kSGroup; ++q) slot += sample(q < qb ? q : qb) >= v ? 1u : 0u;
+    } else {
+      const uint32_t q = qa + 1 + (j - cuts);
+      v = sample(q < qb ? q : qb);
+      slot = j - cuts;
+      for (uint32_t f = 1; f <= cuts; ++f) slot += x0 - step * f > v ? 1u : 0u;
+    }
+    split[top + g * per + slot] = v;
+  }
+  for (uint32_t g = nthin + t; g < w.s; g += T) {
     const uint32_t qa = q0 + g * kSGroup, qb = qa + kSGroup < w.r ? qa + kSGroup : w.r;
     C x[kSGroup + 1];
 #pragma unroll
-    for (uint32_t i = 0; i <= kSGroup; ++i) {
-      const uint32_t q = qa + i < qb ? qa + i : qb;
-      x[i] = q <= m ? sorted[q - 1] : (C)0;
-    }
+    for (uint32_t i = 0; i <= kSGroup; ++i) x[i] = sample(qa + i < qb ? qa + i : qb);
     const C step = (x[0] - x[kSGroup]) >> lgP;
-    // six (of four pieces: seven) of the nine samples inside one piece's
-    // width: the keys are clustered here, the samples divide them better
+    C* const out = split + top + nthin * per + (g - nthin) * w.P;
+    // seven samples in one part's width: the keys are clustered here, and the
+    // samples divide them better
     bool crowded = false;
-    const bool four = w.P == 4;
 #pragma unroll
-    for (uint32_t i = 0; i + 5 <= kSGroup; ++i) crowded = crowded || (!four && x[i] - x[i + 5] < step);
+    for (uint32_t i = 0; i + 6 <= kSGroup; ++i) crowded = crowded || (qa + i + 6 <= qb && x[i] - x[i + 6] < step);
+    for (uint32_t f = 1; f < w.P; ++f) out[f - 1] = x[0] - step * f;
+    if (crowded) {
+      if (w.P >= kSGroup) {
+        for (uint32_t f = kSGroup; f < w.P; ++f) out[f] = x[kSGroup];
 #pragma unroll
-    for (uint32_t i = 0; i + 6 <= kSGroup; ++i) crowded = crowded || (four && x[i] - x[i + 6] < step);
-    for (uint32_t f = 1; f <= w.P; ++f) {
-      C v = x[0] - step * f;
-      if (crowded || f == w.P) {
-        const uint32_t i = (f * kSGroup) >> lgP;
-        const uint32_t q = qa + i < qb ? qa + i : qb;
-        v = q <= m ? sorted[q - 1] : (C)0;
+        for (uint32_t i = 1; i <= kSGroup; ++i) out[i - 1] = x[i];
+      } else {
+#pragma unroll
+        for (uint32_t i = 1; i <= kSGroup; ++i)
+          if (((i << lgP) & (kSGroup - 1)) == 0) out[(i << lgP) / kSGroup - 1] = x[i];
       }
-      split[top + g * w.P + f - 1] = v;
     }
+    out[w.P - 1] = x[kSGroup];
   }
   if (top && t < kSTop) {
     // above the first sample, by the spacing of the samples after it
@@ -382,24 +492,33 @@ __device__ __forceinline__ void sfill_splitters(C* split, const SWin& w, uint32_
 }
 
 // Staged candidates: key and position (composites are made when the stage is
-// written), or composites when the source holds them.
+// written), or composites when the source holds them; then the row, composites
+// in bucket order.  64 slots more take what the lanes do not keep, so a put
+// needs no branch.
 template <typename K, bool ARR, int ST>
 struct SStage {
-  K key[ST];
-  uint32_t pos[ST];
+  typedef typename STraits<K>::Comp C;
+  union {
+    struct {
+      K key[ST + 64];
+      uint32_t pos[ST + 64];
+    };
+    C row[ST];
+  };
   __device__ __forceinline__ void put(uint32_t i, K v, uint32_t p) {
     key[i] = v;
     pos[i] = p;
   }
-  __device__ __forceinline__ typename STraits<K>::Comp get(uint32_t i, int L, uint32_t posmask) const {
+  __device__ __forceinline__ C get(uint32_t i, int L, uint32_t posmask) const {
     return scomp<K>(key[i], pos[i], L, posmask);
   }
 };
 template <typename K, int ST>
 struct SStage<K, true, ST> {
-  typename STraits<K>::Comp c[ST];
-  __device__ __forceinline__ void put(uint32_t i, typename STraits<K>::Comp v, uint32_t) { c[i] = v; }
-  __device__ __forceinline__ typename STraits<K>::Comp get(uint32_t i, int, uint32_t) const { return c[i]; }
+  typedef typename STraits<K>::Comp C;
+  C row[ST + 64];
+  __device__ __forceinline__ void put(uint32_t i, C v, uint32_t) { row[i] = v; }
+  __device__ __forceinline__ C get(uint32_t i, int, uint32_t) const { return row[i]; }
 };
 
 // One pass over the source: counts the elements above the window, stages
@@ -411,24 +530,28 @@ template <typename K, bool ARR>
 __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ keys,
                                                          const typename STraits<K>::Comp* __restrict__ arr,
                                                          uint64_t n, uint32_t head, uint32_t cap1, uint32_t k,
-                                                         uint32_t m, SCodec<K> cd, int L,
+                                                         uint32_t m, SWin win, SCodec<K> cd, int L,
                                                          const typename STraits<K>::Comp* __restrict__ sorted,
                                                          SCtl* ctl, typename STraits<K>::Comp* __restrict__ out,
                                                          uint32_t cap, uint32_t maxrows, SRow* __restrict__ rows,
-                                                         uint16_t* __restrict__ offs, uint32_t pitch) {
+                                                         uint16_t* __restrict__ offs, uint32_t pitch,
+                                                         typename STraits<K>::Comp* __restrict__ bounds) {
   typedef typename STraits<K>::Comp C;
   typedef typename std::conditional<ARR, C, K>::type R;
-  constexpr int ST = STraits<K>::kStage, MB = STraits<K>::kMaxB, T = kSPartThreads;
-  constexpr int NE = ST / T;                                       // elements a thread stages at most
+  constexpr int ST = STraits<K>::kStage, TILE = STraits<K>::kTile, MB = STraits<K>::kMaxB, T = kSPartThreads;
+  constexpr int NE = TILE / T;  // elements a thread reads at a time
+  constexpr int NF = ST / T;    // elements it writes at most
   constexpr int V = ARR ? 16 / (int)sizeof(C) : 16 / (int)sizeof(K);  // elements of a 128-bit load
   constexpr int U = NE / V;
-  static_assert(U >= 1 && NE % V == 0, "a tile is whole 128-bit loads");
+  static_assert(U >= 1 && NE % V == 0 && ST % T == 0, "a tile is whole 128-bit loads");
   constexpr int BP = (MB + T - 1) / T;  // bucket counters a thread scans
   __shared__ SStage<K, ARR, ST> stage;
   __shared__ C split[MB];
   __shared__ uint32_t hist[MB + 1];
-  __shared__ uint32_t s_w[T / 64], s_above;
+  __shared__ uint32_t s_w[T / 64], s_above, s_maxlen;
+  __shared__ uint16_t tab[kSCells + 1];  // tab[i + 1]: splitters above cell i; tab[0]: all
   __shared__ uint32_t s_n, s_row, s_base;
+  uint32_t* const stage_cells = reinterpret_cast<uint32_t*>(&stage);  // before anything is staged
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t posmask = (uint32_t)((1ull << L) - 1);
   uint64_t count = n;
@@ -436,90 +559,15 @@ __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ k
     count = (uint32_t)ctl->alloc1;
     if (count > cap1 || count < k) return;
   }
-  const SWin w = ctl->win;
-  const uint32_t B = w.B;
-  sfill_splitters<C>(split, w, m, sorted, threadIdx.x, T);
-  for (uint32_t b = threadIdx.x; b <= B; b += T) hist[b] = 0;
-  if (threadIdx.x == 0) { s_n = 0; s_above = 0; }
-  const C hi = w.a ? sorted[w.a - 1] : ~(C)0;
-  const C lo = w.r <= m ? sorted[w.r - 1] : (C)0;
-  const R hikey = ARR ? (R)hi : (R)(hi >> L), lokey = ARR ? (R)lo : (R)(lo >> L);
-  const uint32_t hipos = scomp_pos<C>(hi, posmask), lopos = scomp_pos<C>(lo, posmask);
-  uint32_t above = 0;  // wave-uniform
-  __syncthreads();
-
-  // Writes the `cnt` staged candidates as one row (every thread calls).
-  auto flush = [&](uint32_t cnt) {
-    if (above && lane == 0) atomicAdd(&s_above, above);
-    above = 0;
-    C c[NE];
-    uint32_t at[NE];  // bucket << 16 | rank in it
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const uint32_t i = e * T + threadIdx.x;
-      if (i < cnt) {
-        c[e] = stage.get(i, L, posmask);
-        uint32_t b0 = 0, len = B;  // splitters above c: the first len candidates of [b0, b0 + len)
-        while (len) {
-          const uint32_t h = len >> 1;
-          const bool g = split[b0 + h] > c[e];
-          b0 = g ? b0 + h + 1 : b0;
-          len = g ? len - h - 1 : h;
-        }
-        at[e] = (b0 << 16) | atomicAdd(&hist[b0], 1u);
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const uint64_t al = atomicAdd((unsigned long long*)&ctl->alloc, (1ull << 32) | cnt);
-      s_row = (uint32_t)(al >> 32);
-      s_base = (uint32_t)al;
-    }
-    uint32_t h[BP], sum = 0;
-#pragma unroll
-    for (int j = 0; j < BP; ++j) {
-      const uint32_t b = threadIdx.x * BP + j;
-      h[j] = b < B ? hist[b] : 0;
-      sum += h[j];
-    }
-    uint32_t tot;
-    uint32_t ex = sblock_scan<T>(sum, s_w, &tot);
-#pragma unroll
-    for (int j = 0; j < BP; ++j) {
-      const uint32_t b = threadIdx.x * BP + j;
-      if (b < B) hist[b] = ex;
-      ex += h[j];
-    }
-    if (threadIdx.x == 0) hist[B] = cnt;
-    __syncthreads();
-    const uint32_t row = s_row, base = s_base;
-    if (row < maxrows) {
-      if (threadIdx.x == 0) rows[row] = SRow{base, s_above};
-      for (uint32_t b = threadIdx.x; b <= B; b += T) offs[(size_t)row * pitch + b] = (uint16_t)hist[b];
-    }
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const uint32_t i = e * T + threadIdx.x;
-      if (i < cnt) {
-        const uint64_t o = (uint64_t)base + hist[at[e] >> 16] + (at[e] & 0xFFFFu);
-        if (o < cap) out[o] = c[e];
-      }
-    }
-    __syncthreads();
-    for (uint32_t b = threadIdx.x; b <= B; b += T) hist[b] = 0;
-    if (threadIdx.x == 0) s_above = 0;
-  };
-
-  // Tiles of ST elements from the first 16-byte boundary on (head: the
+  // Tiles of TILE elements from the first 16-byte boundary on (head: the
   // elements before it, a last tile of their own).  A thread's loads of the
   // next tile are in flight while it works on the current one.
   const R* src;
   if constexpr (ARR) src = arr;
   else src = keys;
-  constexpr uint32_t tile = ST;
+  constexpr uint32_t tile = TILE;
   const uint64_t body = (count - head + tile - 1) / tile;
   const uint64_t ntile = body + (head ? 1 : 0);
-  uint32_t staged = 0;  // block-uniform fill level
   R cur[NE], nxt[NE];
   uint32_t nvalid = 0;
   // element e of thread t in a tile: load e / V, 16-byte piece t, part e % V
@@ -553,9 +601,133 @@ __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ k
       }
     }
   };
-  load(blockIdx.x);
+  load(blockIdx.x);  // in flight while the window is prepared
+  SWin w = win;  // level 2's was made on the device
+  if constexpr (ARR) w = suniform(ctl->win);
+  const uint32_t B = w.B;
+  sfill_splitters<C>(split, w, m, sorted, threadIdx.x, T);
+  for (uint32_t b = threadIdx.x; b <= B; b += T) hist[b] = 0;
+  if (threadIdx.x == 0) { s_n = 0; s_above = 0; }
+  const C hi = suniform(w.a ? sorted[w.a - 1] : ~(C)0);
+  const C lo = suniform(w.r <= m ? sorted[w.r - 1] : (C)0);
+  const R hikey = ARR ? (R)hi : (R)(hi >> L), lokey = ARR ? (R)lo : (R)(lo >> L);
+  const uint32_t hipos = scomp_pos<C>(hi, posmask), lopos = scomp_pos<C>(lo, posmask);
+  uint32_t above = 0;
+  uint32_t staged = 0;  // block-uniform fill level
+  // Where to look for a composite's bucket: kSCells equal cells of [lo, top),
+  // each with the number of splitters above it, so the search is over the few
+  // splitters of one cell (a search over all of them was half of a row's time).
+  if (threadIdx.x == 0) s_maxlen = kSTop - 1;
+  stage_cells[threadIdx.x] = 0;
+  __syncthreads();
+  if (blockIdx.x == 0)  // for the bucket kernel
+    for (uint32_t b = threadIdx.x; b < B; b += T) bounds[b] = split[b];
+  // at or above `top`: one of the first ntop + 1 buckets
+  const uint32_t ntop = w.P && !w.a ? kSTop - 1 : 0u;
+  const C top = suniform(split[ntop]);
+  const uint32_t cbits = sbits((C)(top - lo));
+  const int csh = cbits > 10 ? (int)cbits - 10 : 0;
+  static_assert(kSCells == T, "a cell a thread");
+  for (uint32_t b = threadIdx.x; b < B; b += T)
+    if (split[b] < top) atomicAdd(&stage_cells[(uint32_t)((split[b] - lo) >> csh)], 1u);
+  __syncthreads();
+  {
+    uint32_t m = stage_cells[kSCells - 1 - threadIdx.x], tot;  // cells from the top down
+    const uint32_t ex = sblock_scan<T>(m, s_w, &tot);
+    tab[kSCells - threadIdx.x] = (uint16_t)(B - tot + ex);  // B - tot splitters are not below top
+    if (threadIdx.x == 0) tab[0] = (uint16_t)B;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const uint32_t q = (uint32_t)__shfl_xor((int)m, o);
+      m = q > m ? q : m;
+    }
+    if (lane == 0) atomicMax(&s_maxlen, m);
+  }
+  __syncthreads();
+  const uint32_t maxlen = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_maxlen);
+
+  // Writes the `cnt` staged candidates as one row (every thread calls).
+  auto flush = [&](uint32_t cnt) {
+    // opaque, so that the many indices made from it are made here and not
+    // carried through the tile loop in registers
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    uint64_t al = 0;  // in flight while the buckets are found
+    if (tid == 0) al = atomicAdd((unsigned long long*)&ctl->alloc, (1ull << 32) | cnt);
+    if (w.a) {
+      const uint32_t x = swave_scan(above);
+      if (lane == 63 && x) atomicAdd(&s_above, x);
+      above = 0;
+    }
+    C c[NF];
+    uint32_t at[NF];  // first splitter to look at << 16 | how many; then bucket << 16 | rank in it
+#pragma unroll
+    for (int e = 0; e < NF; ++e) {
+      const uint32_t i = e * T + tid;
+      at[e] = 0;
+      c[e] = 0;
+      if (i < cnt) {
+        c[e] = stage.get(i, L, posmask);
+        at[e] = ntop;
+        if (c[e] < top) {
+          const uint32_t cell = (uint32_t)((c[e] - lo) >> csh), f = tab[cell + 1];
+          at[e] = (f << 16) | (tab[cell] - f);
+        }
+      }
+    }
+    for (uint32_t w = maxlen; w; w >>= 1) {
+#pragma unroll
+      for (int e = 0; e < NF; ++e) {
+        const uint32_t len = at[e] & 0xFFFFu, h = len >> 1;
+        if (len) at[e] = split[(at[e] >> 16) + h] > c[e] ? at[e] + ((h + 1) << 16) - h - 1 : at[e] - len + h;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < NF; ++e)
+      if (e * T + tid < cnt) at[e] = (at[e] & 0xFFFF0000u) | atomicAdd(&hist[at[e] >> 16], 1u);
+    __syncthreads();
+    uint32_t h[BP], sum = 0;
+#pragma unroll
+    for (int j = 0; j < BP; ++j) {
+      const uint32_t b = tid * BP + j;
+      h[j] = b < B ? hist[b] : 0;
+      sum += h[j];
+    }
+    uint32_t tot;
+    uint32_t ex = sblock_scan<T>(sum, s_w, &tot);
+#pragma unroll
+    for (int j = 0; j < BP; ++j) {
+      const uint32_t b = tid * BP + j;
+      if (b < B) hist[b] = ex;
+      ex += h[j];
+    }
+    if (tid == 0) {
+      hist[B] = cnt;
+      s_row = (uint32_t)(al >> 32);
+      s_base = (uint32_t)al;
+    }
+    __syncthreads();
+    const uint32_t row = s_row, base = s_base;
+    if (row < maxrows) {
+      if (tid == 0) rows[row] = SRow{base, s_above};
+      for (uint32_t b = tid; b <= B; b += T) offs[(size_t)row * pitch + b] = (uint16_t)hist[b];
+    }
+    // through LDS into bucket order, so that the row leaves in whole lines
+    // (scattered stores took 10 us a row of 10^4)
+#pragma unroll
+    for (int e = 0; e < NF; ++e)
+      if (e * T + tid < cnt) stage.row[hist[at[e] >> 16] + (at[e] & 0xFFFFu)] = c[e];
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += T)
+      if ((uint64_t)base + i < cap) out[base + i] = stage.row[i];
+    __syncthreads();
+    for (uint32_t b = tid; b <= B; b += T) hist[b] = 0;
+    if (threadIdx.x == 0) s_above = 0;
+  };
+
   for (uint64_t tl = blockIdx.x; tl < ntile; tl += gridDim.x) {
     const uint32_t valid = nvalid;
+    const bool whole = tl < body && (tl + 1) * tile <= count - head;  // every element valid
     const uint32_t p0 = tl == body ? threadIdx.x : head + (uint32_t)first(tl, 0);
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
@@ -563,43 +735,72 @@ __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ k
       else cur[e] = senc<K>(nxt[e], cd);
     }
     load(tl + gridDim.x);
-    uint32_t wcnt = 0;
-    uint64_t bal[NE];
+    // Each lane marks what it keeps, a prefix sum over the lanes' counts places
+    // it, and every element is written, the ones not kept to a spare slot: the
+    // loop is bound by its instructions, and this takes the fewest (a branch
+    // per element: 2.0 us a tile of 32 KB).  Whether keys equal to a
+    // bound's are inside is settled by position for a wave's load as a whole,
+    // but for the one load that the bound's own position lies in.
+    bool in[NE];
+    uint32_t mine = 0;
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const uint32_t pos = p0 + (uint32_t)(e / V) * T * V + e % V;
-      bal[e] = __ballot(cur[e] >= lokey);
+    for (int u = 0; u < U; ++u) {
+      R low = lokey, span = hikey - lokey;  // inside: key - low <= span
+      bool exact = !whole;
       if constexpr (!ARR) {
-        if (__ballot(cur[e] == lokey)) bal[e] &= ~__ballot(cur[e] == lokey && pos > lopos);
+        const uint32_t p1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(p0 + (uint32_t)u * T * V));
+        const uint32_t p2 = p1 + 64 * V - 1;
+        const bool past = p1 > lopos, before = w.a && p2 < hipos;
+        low = past ? lokey + 1 : lokey;
+        const R high = before ? hikey - 1 : hikey;
+        span = high - low;
+        exact = exact || (!past && p2 > lopos) || (w.a && !before && p1 < hipos) || low < lokey || high > hikey ||
+                high < low;
       }
-      if (!__all(valid == (1u << NE) - 1)) bal[e] &= __ballot((valid >> e) & 1u);
-      if (w.a) {
-        uint64_t up = __ballot(cur[e] > hikey);
-        if constexpr (!ARR) {
-          if (__ballot(cur[e] == hikey)) up |= __ballot(cur[e] == hikey && pos < hipos);
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const int e = u * V + j;
+        if (exact) {
+          const uint32_t pos = p0 + (uint32_t)u * T * V + j;
+          bool ok = (valid >> e) & 1u, up;
+          if constexpr (ARR) {
+            ok = ok && cur[e] >= lo;
+            up = ok && cur[e] > hi;
+          } else {
+            ok = ok && (cur[e] > lokey || (cur[e] == lokey && pos <= lopos));
+            up = w.a && ok && (cur[e] > hikey || (cur[e] == hikey && pos < hipos));
+          }
+          above += up ? 1u : 0u;
+          in[e] = ok && !up;
+        } else if (w.a) {
+          in[e] = (R)(cur[e] - low) <= span;
+          above += !in[e] && cur[e] > low ? 1u : 0u;
+        } else {
+          in[e] = cur[e] >= low;
         }
-        up &= bal[e];
-        above += (uint32_t)__popcll(up);
-        bal[e] &= ~up;
+        mine += in[e] ? 1u : 0u;
       }
-      wcnt += (uint32_t)__popcll(bal[e]);
     }
+    const uint32_t upto = swave_scan(mine);
+    const uint32_t wcnt = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
     uint32_t wbase = 0;
     if (lane == 0 && wcnt) wbase = atomicAdd(&s_n, wcnt);
     wbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)wbase);
     __syncthreads();
-    uint32_t now = s_n;
+    uint32_t now = suniform(s_n);
     if (now > (uint32_t)ST) {  // block-uniform: the tile does not fit beside what is staged
       flush(staged);
       if (threadIdx.x == 0) s_n = now - staged;
       wbase -= staged;
       now -= staged;
     }
+    if (wcnt) {
+      uint32_t at = wbase + upto - mine;
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const uint32_t pos = p0 + (uint32_t)(e / V) * T * V + e % V;
-      if (__builtin_amdgcn_inverse_ballot_w64(bal[e])) stage.put(wbase + mbcnt(bal[e]), cur[e], pos);
-      wbase += (uint32_t)__popcll(bal[e]);
+      for (int e = 0; e < NE; ++e) {
+        stage.put(in[e] ? at : (uint32_t)ST + lane, cur[e], p0 + (uint32_t)(e / V) * T * V + e % V);
+        at += in[e] ? 1u : 0u;
+      }
     }
     staged = now;
     __syncthreads();
@@ -650,26 +851,27 @@ __device__ __forceinline__ void ssplit_sort(C* split, uint32_t* rank) {
   __syncthreads();
 }
 
-template <typename C>
-__device__ __forceinline__ C sshfl_xor(C v, int o) {
+// The larger (UP) or smaller of v and the value of a lane in the other M-half
+// of this lane's 2M-block.
+template <int M, bool UP, typename C>
+__device__ __forceinline__ C sbest_cross(C v) {
   uint32_t w[sizeof(C) / 4];
   __builtin_memcpy(w, &v, sizeof(C));
 #pragma unroll
-  for (uint32_t i = 0; i < sizeof(C) / 4; ++i) w[i] = (uint32_t)__shfl_xor((int)w[i], o);
-  __builtin_memcpy(&v, w, sizeof(C));
-  return v;
+  for (uint32_t i = 0; i < sizeof(C) / 4; ++i) w[i] = lane_cross32<M>(w[i]);
+  C o;
+  __builtin_memcpy(&o, w, sizeof(C));
+  return (o > v) == UP ? o : v;
 }
 
 // Largest and smallest over the workgroup, held by every thread.  red: T / 64
 // pairs, free before and after.
 template <typename C, int T>
 __device__ __forceinline__ void sblock_minmax(C& mx, C& mn, C (*red)[2]) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const C a = sshfl_xor(mx, o), b = sshfl_xor(mn, o);
-    mx = a > mx ? a : mx;
-    mn = b < mn ? b : mn;
-  }
+  mx = sbest_cross<32, true>(sbest_cross<16, true>(sbest_cross<8, true>(
+      sbest_cross<4, true>(sbest_cross<2, true>(sbest_cross<1, true>(mx))))));
+  mn = sbest_cross<32, false>(sbest_cross<16, false>(sbest_cross<8, false>(
+      sbest_cross<4, false>(sbest_cross<2, false>(sbest_cross<1, false>(mn))))));
   __syncthreads();
   if ((threadIdx.x & 63) == 0) {
     red[threadIdx.x >> 6][0] = mx;
@@ -694,6 +896,36 @@ __device__ __forceinline__ uint32_t slog_bin(C d) {
   return ((w - MB) << MB) + ((uint32_t)(d >> (w - MB - 1)) & ((1u << MB) - 1));
 }
 
+// lo plus the number of buf[lo .. hi) above c; four LDS reads in flight (one at
+// a time, a bin of 300 cost 12 us).
+template <typename C>
+__device__ __forceinline__ uint32_t srank_in(const C* buf, uint32_t lo, uint32_t hi, C c) {
+  uint32_t rk = lo;
+  for (uint32_t j = lo; j < hi; j += 4) {
+    C x[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) x[q] = buf[j + q < hi ? j + q : j];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) rk += j + q < hi && x[q] > c ? 1u : 0u;
+  }
+  return rk;
+}
+
+// Adds the lane to bin b of an LDS histogram and returns its rank there.  Lanes
+// that all hold one bin (tied keys) add themselves once for the wave: the LDS
+// serves adds to one address one lane at a time.
+__device__ __forceinline__ uint32_t scount(uint32_t* hist, uint32_t b) {
+  const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+  const uint64_t on = __ballot(1);
+  if (__ballot(b == b0) == on) {
+    uint32_t r = 0;
+    const uint32_t rk = mbcnt(on);
+    if (rk == 0) r = atomicAdd(&hist[b0], (uint32_t)__popcll(on));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)r) + rk;
+  }
+  return atomicAdd(&hist[b], 1u);
+}
+
 // Sorts the N (<= CAP) composites held N = e * T + thread in c[] descending
 // and calls emit(slot, composite) for each of the first `need` slots (and
 // perhaps a few after them).  Linear bins over [min, max] (logarithmic from the
@@ -703,17 +935,23 @@ __device__ __forceinline__ uint32_t slog_bin(C d) {
 // are left alone.  When a bin that counts is crowded (keys in far-apart
 // clusters, floats of both signs) bins between samples instead.
 template <typename C, uint32_t CAP, int T, int E, typename F>
-__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint64_t need, F&& emit) {
-  C mx = 0, mn = ~(C)0;
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (e * T + threadIdx.x < N) {
-      mx = c[e] > mx ? c[e] : mx;
-      mn = c[e] < mn ? c[e] : mn;
-    }
+__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint64_t need, F&& emit,
+                                      C mn = 0, C mx = ~(C)0) {
   for (int b = threadIdx.x; b <= kSBins; b += T) sm.hist[b] = 0;
   if (threadIdx.x == 0) sm.misc[0] = 0;
-  sblock_minmax<C, T>(mx, mn, sm.red);
+  if (mx == ~(C)0) {  // uniform
+    mx = 0;
+    mn = ~(C)0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e * T + threadIdx.x < N) {
+        mx = c[e] > mx ? c[e] : mx;
+        mn = c[e] < mn ? c[e] : mn;
+      }
+    sblock_minmax<C, T>(mx, mn, sm.red);
+  } else {
+    __syncthreads();
+  }
   const uint32_t bl = sbits((C)(mx - mn));
   const int sh = bl > 11 ? (int)bl - 11 : 0;
   const bool logb = need <= N / 4;
@@ -722,7 +960,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
   for (int e = 0; e < E; ++e)
     if (e * T + threadIdx.x < N) {
       const uint32_t b = logb ? slog_bin<C>(mx - c[e]) : (uint32_t)((mx - c[e]) >> sh);
-      at[e] = (b << 16) | atomicAdd(&sm.hist[b], 1u);
+      at[e] = (b << 16) | scount(sm.hist, b);
     }
   __syncthreads();
   constexpr int BP = kSBins / T;
@@ -737,7 +975,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
 #pragma unroll
   for (int j = 0; j < BP; ++j) {
     sm.hist[threadIdx.x * BP + j] = ex;
-    if (h[j] > 96u && ex < need) sm.misc[0] = 1;
+    if (h[j] > kSCrowd && ex < need) sm.misc[0] = 1;
     ex += h[j];
   }
   if (threadIdx.x == 0) sm.hist[kSBins] = N;
@@ -756,9 +994,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
         const uint32_t b = at[e] >> 16;
         const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
         if (lo < need) {
-          uint32_t rk = lo;
-          for (uint32_t j = lo; j < hi; ++j) rk += sm.buf[j] > c[e] ? 1u : 0u;
-          emit(rk, c[e]);
+          emit(srank_in(sm.buf, lo, hi, c[e]), c[e]);
         }
       }
     __syncthreads();
@@ -828,9 +1064,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
       const uint32_t b = at[e] >> 16;
       const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
       if (lo < need) {
-        uint32_t rk = lo;
-        for (uint32_t j = lo; j < hi; ++j) rk += sm.buf[j] > c[e] ? 1u : 0u;
-        emit(rk, c[e]);
+        emit(srank_in(sm.buf, lo, hi, c[e]), c[e]);
       }
     }
   __syncthreads();
@@ -838,15 +1072,10 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
 
 template <typename K>
 struct SBucketShared : SSortShared<typename STraits<K>::Comp, STraits<K>::kCap, kSBucketThreads> {
-  uint32_t pre[kSMaxRows + 1];  // bucket elements in the rows before this one
-  uint32_t src[kSMaxRows];      // candidate index of the row's segment
+  uint32_t pre[kSMaxRows + 1];  // bucket elements in the segments before this one
+  uint32_t src[kSMaxRows];      // candidate index of the segment
+  uint32_t w3[kSBucketThreads / 64][3];
 };
-
-template <typename K, int E, typename F>
-__device__ __forceinline__ void sbucket_sort(SBucketShared<K>& sm, typename STraits<K>::Comp (&c)[E], uint32_t N,
-                                             uint64_t need, F&& emit) {
-  ssort<typename STraits<K>::Comp, STraits<K>::kCap, kSBucketThreads, E>(sm, c, N, need, emit);
-}
 
 // f(get(i)) for the workgroup's i < count, four elements a thread at a time so
 // that their loads overlap.
@@ -919,11 +1148,11 @@ __device__ __forceinline__ int sbucket_hist(SSortShared<C, CAP, T>& sm, uint64_t
   return sh;
 }
 
-// The element of 1-based rank `rank` among get(i), i < count (all distinct).
+// The element of 1-based rank `rank` among get(i), i < count (all distinct, at most `top`).
 template <typename C, uint32_t CAP, int T, typename G>
-__device__ __forceinline__ C sbucket_select(SSortShared<C, CAP, T>& sm, uint64_t count,
-                                                                    uint64_t rank, G&& get) {
-  C mn = 0, mx = ~(C)0;
+__device__ __forceinline__ C sbucket_select(SSortShared<C, CAP, T>& sm, uint64_t count, uint64_t rank, C top,
+                                            G&& get) {
+  C mn = 0, mx = top;
   for (;;) {
     const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
     if (threadIdx.x == 0) sm.misc[2] = 0;
@@ -941,164 +1170,282 @@ __device__ __forceinline__ C sbucket_select(SSortShared<C, CAP, T>& sm, uint64_t
   }
 }
 
-// One workgroup per bucket.  B buckets from the rows (PLAIN false), or the
-// candidate buffer as the only bucket (PLAIN true).
-template <typename K, bool PLAIN>
-__global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_sbucket(
-    const K* __restrict__ keys, uint64_t n, uint32_t k, int kth_only, int levels, SCodec<K> cd, int L,
-    const SCtl* __restrict__ ctl, const typename STraits<K>::Comp* __restrict__ cand, uint32_t cap1, uint32_t cap,
-    uint32_t maxrows, const SRow* __restrict__ rows, const uint16_t* __restrict__ offs, uint32_t pitch, K* __restrict__ out_vals,
-    uint32_t* __restrict__ out_idx, K* __restrict__ out_kth) {
+// Where a slot of the output goes.
+template <typename K>
+struct SOut {
+  K* vals;
+  uint32_t* idx;
+  K* kth;
+  uint32_t k;
+  int kth_only;
+  SCodec<K> cd;
+  int L;
+  uint32_t posmask;
+  SPayload pay;
+  __device__ __forceinline__ void operator()(uint64_t slot, typename STraits<K>::Comp c) const {
+    if (slot >= k) return;
+    const K v = sdec<K>((K)(c >> L), cd);
+    if (!kth_only) {
+      const uint32_t p = scomp_pos<typename STraits<K>::Comp>(c, posmask);
+      if (vals) vals[slot] = v;
+      if (idx) idx[slot] = p;
+      if (pay.bytes == 8)
+        static_cast<uint64_t*>(pay.out)[slot] = static_cast<const uint64_t*>(pay.in)[p];
+      else if (pay.bytes == 4)
+        static_cast<uint32_t*>(pay.out)[slot] = static_cast<const uint32_t*>(pay.in)[p];
+    }
+    if (kth && slot == k - 1) *kth = v;
+  }
+};
+
+// Where the candidates are: one list that is one bucket; one list of a few
+// buckets, which each workgroup reads whole; or rows grouped by bucket.
+enum SMode { kSPlain, kSList, kSRows };
+
+// Element i of a bucket's source: candidate i, or by the segments' prefix sums.
+template <typename K, SMode MODE>
+__device__ __forceinline__ typename STraits<K>::Comp sbucket_get(const SBucketShared<K>& sm,
+                                                                 const typename STraits<K>::Comp* cand, uint64_t i) {
+  if constexpr (MODE != kSRows) {
+    return cand[i];
+  } else {
+    uint32_t r0 = 0;  // last segment with pre <= i
+#pragma unroll
+    for (uint32_t h = kSMaxRows / 2; h >= 1; h >>= 1)
+      if (sm.pre[r0 + h] <= (uint32_t)i) r0 += h;
+    return cand[sm.src[r0] + ((uint32_t)i - sm.pre[r0])];
+  }
+}
+
+// The rare ways to the output: runs of at most CAP elements, sorted one after
+// the other.  Either the leading bins of what is left of a bucket larger than
+// the LDS (its elements of the source's `count` lie in [low, upto], its first
+// slot is `start`), or (count 0) a rescue: each workgroup answers ranks of its
+// own from the input, independently of the others.
+template <typename K, SMode MODE>
+__device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys, uint64_t n,
+                                             const typename STraits<K>::Comp* cand, uint64_t start, uint32_t count,
+                                             typename STraits<K>::Comp low, typename STraits<K>::Comp upto,
+                                             const SOut<K>& out) {
+  typedef typename STraits<K>::Comp C;
+  constexpr int T = kSBucketThreads;
+  constexpr uint32_t CAP = STraits<K>::kCap;
+  constexpr int E = (int)(CAP + T - 1) / T;
+  const bool rescue = count == 0;
+  const uint32_t k = out.k;
+  auto input = [&](uint64_t i) { return scomp<K>(senc<K>(keys[i], out.cd), (uint32_t)i, out.L, out.posmask); };
+  auto get = [&](uint64_t i) { return sbucket_get<K, MODE>(sm, cand, i); };
+  if (rescue && out.kth_only && blockIdx.x > 0) return;
+  uint64_t base = rescue ? (out.kth_only ? (uint64_t)k - 1 : (uint64_t)blockIdx.x * CAP) : start;
+  C c[E];
+  while (base < k) {
+    uint32_t N;
+    uint64_t next;
+    if (rescue) {
+      const uint64_t r1 = base + CAP < k ? base + CAP : k;
+      C bound[2];
+#pragma unroll 1
+      for (int s = 0; s < 2; ++s)
+        bound[s] = sbucket_select<C, CAP, T>(sm, n, s ? r1 : base + 1, ((C)(K)~(K)0 << out.L) | out.posmask, input);
+      N = sbucket_collect<C, CAP, T, E>(sm, c, n, bound[1], bound[0], input);
+      next = base + (uint64_t)gridDim.x * CAP;
+    } else {
+      C mn = ~(C)0, mx = 0;
+      sbucket_each<C, T>(count, get, [&](C x) {
+        if (x >= low && x <= upto) {
+          mx = x > mx ? x : mx;
+          mn = x < mn ? x : mn;
+        }
+      });
+      sblock_minmax<C, T>(mx, mn, sm.red);
+      if (mx < mn) break;  // nothing is left
+      C cut = mn;
+      for (;;) {
+        const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
+        // the most leading bins whose elements fit
+        if (threadIdx.x == 0) sm.misc[3] = 0;
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < (uint32_t)kSBins; i += T)
+          if (sm.hist[i + 1] <= CAP && (i + 1 == (uint32_t)kSBins || sm.hist[i + 2] > CAP)) sm.misc[3] = i + 1;
+        __syncthreads();
+        const uint32_t fit = sm.misc[3];
+        __syncthreads();
+        const C width = (C)(fit ? fit : 1u) << sh;  // composites of the kept bins
+        const bool all = mx - mn < width;
+        cut = all ? mn : mx - (width - 1);
+        if (fit || sh == 0) break;
+        mn = cut;  // the first bin alone is too large: look inside it
+      }
+      N = sbucket_collect<C, CAP, T, E>(sm, c, count, cut, mx, get);
+      if (N == 0) break;
+      next = cut > low ? base + N : k;
+      upto = cut - 1;
+    }
+    ssort<C, CAP, T, E>(sm, c, N, k - base, [&](uint32_t rk, C x) { out(base + rk, x); });
+    base = next;
+  }
+}
+
+// One workgroup per bucket.  RARE: the rare ways are part of the kernel, which
+// then takes so many registers that one workgroup fills a CU: for few buckets.
+// With many, a kernel without them runs first (two workgroups a CU) and only
+// notes in ctl->rare that they are needed; `second` then runs this kernel for
+// those buckets, or for nothing.
+template <typename K, SMode MODE, bool RARE>
+__global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu(RARE ? 2 : 4))) void k_sbucket(
+    const K* __restrict__ keys, uint64_t n, uint32_t k, int kth_only, int levels, int second, SCodec<K> cd, int L,
+    SCtl* __restrict__ ctl, const typename STraits<K>::Comp* __restrict__ cand, uint32_t cap1, uint32_t cap,
+    uint32_t maxrows, const SRow* __restrict__ rows, const uint16_t* __restrict__ offs, uint32_t pitch, uint32_t m,
+    SWin win, const typename STraits<K>::Comp* __restrict__ sorted,
+    const typename STraits<K>::Comp* __restrict__ bounds, K* __restrict__ out_vals, uint32_t* __restrict__ out_idx,
+    K* __restrict__ out_kth, SPayload pay) {
   typedef typename STraits<K>::Comp C;
   constexpr int T = kSBucketThreads;
   constexpr uint32_t CAP = STraits<K>::kCap;
   constexpr int E = (int)(CAP + T - 1) / T;
   __shared__ SBucketShared<K> sm;
-  const uint32_t posmask = (uint32_t)((1ull << L) - 1);
+  if (second && !ctl->rare) return;
+  const SOut<K> out{out_vals, out_idx, out_kth, k, kth_only, cd, L, (uint32_t)((1ull << L) - 1), pay};
   const uint64_t al = ctl->alloc;
   const uint32_t nc = (uint32_t)al, nrows = (uint32_t)(al >> 32);
-  uint64_t start = 0;  // elements ranked above the bucket
-  uint32_t count = 0;
-  auto emit = [&](uint64_t slot, C c) {  // slot: 0-based rank in the whole input
-    if (slot >= k) return;
-    const K v = sdec<K>((K)(c >> L), cd);
-    if (!kth_only) {
-      if (out_vals) out_vals[slot] = v;
-      if (out_idx) out_idx[slot] = scomp_pos<C>(c, posmask);
-    }
-    if (out_kth && slot == k - 1) *out_kth = v;
-  };
+  const uint32_t b = blockIdx.x;
   bool bad = nc > cap;
   if (levels == 2) {
     const uint32_t c1 = (uint32_t)ctl->alloc1;
     bad = bad || c1 > cap1 || c1 < k;
   }
+  uint64_t start = 0;  // elements ranked above the bucket
+  uint32_t count = nc, source = nc;
+  C low = 0, upto = ~(C)0;  // the bucket's bounds in its source
   C c[E];
-  uint64_t total = 0, over = 0;  // elements at or above the cut; above the window
-  if constexpr (PLAIN) {
-    count = nc;
-    total = nc;
+  if constexpr (MODE == kSPlain) {
+    bad = bad || nc < k;
+    if (!bad && count <= CAP) {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * T + threadIdx.x < count) c[e] = cand[e * T + threadIdx.x];
+    }
+  } else if constexpr (MODE == kSList) {
+    bad = bad || nc < k;
+    if (!bad) {
+      const SWin w = win;
+      C* const split = sm.buf;  // before anything is collected
+      sfill_splitters<C>(split, w, m, sorted, threadIdx.x, T);
+      if (threadIdx.x == 0) sm.misc[4] = 0;
+      __syncthreads();
+      if (b >= w.B) return;
+      low = suniform(split[b]);
+      if (b) upto = suniform(split[b - 1]) - 1;
+      __syncthreads();
+      uint32_t above = 0, seen = 0;
+      if (low <= upto) {
+        // eight 16-byte loads a thread in flight; what a wave keeps of them is
+        // placed by a prefix sum over its lanes and one LDS atomic
+        constexpr uint32_t V = 16 / sizeof(C), U = 8;
+        const uint32_t pieces = (nc + V - 1) / V;  // the buffer is whole pieces
+        for (uint32_t g0 = 0; g0 < pieces; g0 += U * T) {
+          C x[U * V];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t g = g0 + u * T + threadIdx.x;
+            su32x4 q = {};
+            if (g < pieces) q = *reinterpret_cast<const su32x4*>(cand + (size_t)g * V);
+            __builtin_memcpy(&x[u * V], &q, 16);
+          }
+          uint32_t mine = 0;
+#pragma unroll
+          for (uint32_t j = 0; j < U * V; ++j) {
+            if ((g0 + j / V * T + threadIdx.x) * V + j % V >= nc) x[j] = 0;  // below every bucket that is looked at
+            above += x[j] > upto ? 1u : 0u;
+            mine += x[j] >= low ? 1u : 0u;
+          }
+          mine -= above - seen;
+          seen = above;
+          const uint32_t inc = swave_scan(mine);
+          uint32_t at = 0;
+          if ((threadIdx.x & 63) == 63 && inc) at = atomicAdd(&sm.misc[4], inc);
+          at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + inc - mine;
+#pragma unroll
+          for (uint32_t j = 0; j < U * V; ++j)
+            if (x[j] >= low && x[j] <= upto) {
+              if (at < CAP) sm.buf[at] = x[j];
+              ++at;
+            }
+        }
+        __syncthreads();
+      }
+      uint32_t tot, zero;
+      sblock_scan3<T>(0, above, 0, sm.w3, &zero, &zero, &tot, &zero);
+      start = tot;
+      count = sm.misc[4];
+      if (start >= k || count == 0 || (kth_only && start + count < k)) return;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * T + threadIdx.x < count && count <= CAP) c[e] = sm.buf[e * T + threadIdx.x];
+      __syncthreads();
+    }
   } else {
     bad = bad || nrows > maxrows;
-    const uint32_t b = blockIdx.x;
     const uint32_t B = ctl->win.B;
-    if (!bad) {
-      // this bucket's segments: thread t takes rows 2t and 2t + 1
-      static_assert(kSMaxRows == 2 * T, "two rows a thread");
-      uint32_t len[2], sum = 0, before = 0, ab = 0;
+    low = bounds[b];
+    if (b) upto = bounds[b - 1];
+    low = suniform(low);
+    upto = suniform(upto);
+    // this bucket's segments: thread t takes rows t and t + T, whose loads do
+    // not wait for the number of rows
+    static_assert(kSMaxRows == 2 * T, "two rows a thread");
+    uint32_t len[2], from[2], sum = 0, before = 0, ab = 0;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint32_t r = 2 * threadIdx.x + j;
-        len[j] = 0;
-        if (r < nrows) {
-          const SRow rw = rows[r];
-          ab += rw.above;
-          if (b < B) {
-            const uint32_t o0 = offs[(size_t)r * pitch + b], o1 = offs[(size_t)r * pitch + b + 1];
-            len[j] = o1 - o0;
-            before += o0;
-            sm.src[r] = rw.base + o0;
-          }
-        }
-        sum += len[j];
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t r = threadIdx.x + j * T;
+      SRow rw = {};
+      uint32_t o0 = 0, o1 = 0;
+      if (r < maxrows) {
+        rw = rows[r];
+        o0 = offs[(size_t)r * pitch + b];
+        o1 = offs[(size_t)r * pitch + b + 1];
       }
-      uint32_t tb, ta;
-      (void)sblock_scan<T>(before, sm.s_w, &tb);
-      (void)sblock_scan<T>(ab, sm.s_w, &ta);
-      uint32_t ex = sblock_scan<T>(sum, sm.s_w, &count);
+      const bool on = r < nrows && !bad;
+      ab += on ? rw.above : 0u;
+      len[j] = on && b < B ? o1 - o0 : 0u;
+      before += on && b < B ? o0 : 0u;
+      from[j] = rw.base + o0;
+      sum += len[j];
+    }
+    uint32_t ex, tb, ta;
+    sblock_scan3<T>(sum, before, ab, sm.w3, &ex, &count, &tb, &ta);
+    start = (uint64_t)ta + tb;
+    source = count;
+    bad = bad || (uint64_t)ta + nc < k || ta >= k;  // too few at or above the cut, or too many above the window
+    if (!bad && (b >= B || start >= k || count == 0 || (kth_only && start + count < k))) return;
+    if (!bad) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         sm.pre[2 * threadIdx.x + j] = ex;
+        sm.src[2 * threadIdx.x + j] = from[j];
         ex += len[j];
       }
       if (threadIdx.x == T - 1) sm.pre[kSMaxRows] = ex;
-      start = (uint64_t)ta + tb;
-      over = ta;
-      total = (uint64_t)ta + nc;
       __syncthreads();
-    }
-    if (!bad && total >= k && over < k) {
-      if (b >= B || start >= k || count == 0) return;
-      if (kth_only && start + count < k) return;
-    }
-  }
-  if (bad || total < k || over >= k) {
-    // rescue: the sample misjudged this input.  Each workgroup answers its
-    // own ranks from the input, independently of the others.
-    auto get = [&](uint64_t i) { return scomp<K>(senc<K>(keys[i], cd), (uint32_t)i, L, posmask); };
-    if (kth_only) {
-      if (blockIdx.x == 0) {
-        const C x = sbucket_select<C, CAP, T>(sm, n, k, get);
-        if (threadIdx.x == 0) emit((uint64_t)k - 1, x);
+      if (count <= CAP && !second) {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (e * T + threadIdx.x < count) c[e] = sbucket_get<K, MODE>(sm, cand, e * T + threadIdx.x);
       }
-      return;
     }
-    for (uint64_t j = blockIdx.x; j * CAP < k; j += gridDim.x) {
-      const uint64_t r0 = j * CAP, r1 = r0 + CAP < k ? r0 + CAP : k;
-      const C hi = sbucket_select<C, CAP, T>(sm, n, r0 + 1, get);
-      const C lo = sbucket_select<C, CAP, T>(sm, n, r1, get);
-      const uint32_t N = sbucket_collect<C, CAP, T, E>(sm, c, n, lo, hi, get);
-      sbucket_sort<K, E>(sm, c, N, N, [&](uint32_t rk, C x) { emit(r0 + rk, x); });
-    }
-    return;
   }
-  auto get = [&](uint64_t i) {
-    if constexpr (PLAIN) {
-      return cand[i];
+  if (bad || count > CAP) {
+    if constexpr (RARE) {
+      sbucket_rare<K, MODE>(sm, keys, n, cand, start, bad ? 0u : source, low, upto, out);
     } else {
-      uint32_t r0 = 0;  // last row with pre <= i
-#pragma unroll
-      for (uint32_t h = kSMaxRows / 2; h >= 1; h >>= 1)
-        if (sm.pre[r0 + h] <= (uint32_t)i) r0 += h;
-      return cand[sm.src[r0] + ((uint32_t)i - sm.pre[r0])];
+      if (threadIdx.x == 0) ctl->rare = 1;
     }
-  };
-  if (count <= CAP) {
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (e * T + threadIdx.x < count) c[e] = get(e * T + threadIdx.x);
-    sbucket_sort<K, E>(sm, c, count, k - start, [&](uint32_t rk, C x) { emit(start + rk, x); });
     return;
   }
-  // a bucket larger than the LDS: descending runs of at most CAP elements,
-  // each the leading bins of a histogram of what is left
-  uint64_t done = 0;
-  C top = ~(C)0;  // elements above it are written
-  while (done < count && start + done < k) {
-    C mn = ~(C)0, mx = 0;
-    sbucket_each<C, T>(count, get, [&](C x) {
-      if (x <= top) {
-        mx = x > mx ? x : mx;
-        mn = x < mn ? x : mn;
-      }
-    });
-    sblock_minmax<C, T>(mx, mn, sm.red);
-    C cut = mn;
-    for (;;) {
-      const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
-      // the most leading bins whose elements fit
-      if (threadIdx.x == 0) sm.misc[3] = 0;
-      __syncthreads();
-      for (uint32_t b = threadIdx.x; b < (uint32_t)kSBins; b += T)
-        if (sm.hist[b + 1] <= CAP && (b + 1 == (uint32_t)kSBins || sm.hist[b + 2] > CAP)) sm.misc[3] = b + 1;
-      __syncthreads();
-      const uint32_t nb = sm.misc[3];
-      __syncthreads();
-      const C width = (C)(nb ? nb : 1u) << sh;  // composites of the kept bins
-      const bool all = mx - mn < width;
-      cut = all ? mn : mx - (width - 1);
-      if (nb || sh == 0) break;
-      mn = cut;  // the first bin alone is too large: look inside it
-    }
-    const uint32_t N = sbucket_collect<C, CAP, T, E>(sm, c, count, cut, mx, get);
-    sbucket_sort<K, E>(sm, c, N, k - start - done, [&](uint32_t rk, C x) { emit(start + done + rk, x); });
-    done += N;
-    if (N == 0 || cut == 0) break;
-    top = cut - 1;
-  }
+  if (second) return;
+  ssort<C, CAP, T, E>(sm, c, count, k - start, [&](uint32_t rk, C x) { out(start + rk, x); }, low, upto);
 }
 
-// ---------------------------------------------------------------------------
 // The whole problem in one workgroup.  n <= CAP: every element goes into the
 // sort.  Otherwise the r-th of 256 samples cuts the input to between k and
 // CAP elements in one streaming pass, the survivors collected in LDS and
@@ -1113,7 +1460,7 @@ struct SOne {
 template <typename K, int T>
 __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t n, uint32_t k, uint32_t r,
                                             int kth_only, SCodec<K> cd, int L, K* __restrict__ out_vals,
-                                            uint32_t* __restrict__ out_idx, K* __restrict__ out_kth) {
+                                            uint32_t* __restrict__ out_idx, K* __restrict__ out_kth, SPayload pay) {
   typedef typename STraits<K>::Comp C;
   constexpr uint32_t CAP = T == 1024 ? SOne<K>::kCap : 1024;
   constexpr int E = (int)(CAP / T);
@@ -1196,7 +1543,7 @@ __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t
     __syncthreads();
     N = sm.misc[4];
     if (N < k || N > CAP) {
-      const C kth = sbucket_select<C, CAP, T>(sm, n, k, get);
+      const C kth = sbucket_select<C, CAP, T>(sm, n, k, ((C)(K)~(K)0 << L) | posmask, get);
       N = sbucket_collect<C, CAP, T, E>(sm, c, n, kth, ~(C)0, get);
     } else {
 #pragma unroll
@@ -1205,15 +1552,8 @@ __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t
     }
     __syncthreads();
   }
-  ssort<C, CAP, T, E>(sm, c, N, k, [&](uint32_t slot, C x) {
-    if (slot >= k) return;
-    const K v = sdec<K>((K)(x >> L), cd);
-    if (!kth_only) {
-      if (out_vals) out_vals[slot] = v;
-      if (out_idx) out_idx[slot] = scomp_pos<C>(x, posmask);
-    }
-    if (out_kth && slot == k - 1) *out_kth = v;
-  });
+  const SOut<K> out{out_vals, out_idx, out_kth, k, kth_only, cd, L, posmask, pay};
+  ssort<C, CAP, T, E>(sm, c, N, k, [&](uint32_t slot, C x) { out(slot, x); });
 }
 
 }  // namespace drtopk

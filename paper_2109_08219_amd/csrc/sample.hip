@@ -64,11 +64,16 @@ void plan_for(SPlan& p) {
     w.a = 0;
     w.B = p.bmax = 1;
     cap = T::kCap;
-  } else if (gap <= 2.0 * T::kTarget) {
+  } else if (p.top && gap <= 2.0 * T::kTarget && cap_top <= T::kList) {
+    // few enough that each bucket's workgroup can read all of them
+    p.plain = 1;
     sample_buckets(gap, T::kTarget, T::kMaxB, &w);
-    cap = (uint64_t)span_cap(w.r - w.a, gap);
+    cap = (uint64_t)cap_top;
     p.bmax = w.B;
   } else if (p.top) {
+    // few of many: the streaming filter, and its candidates partitioned; the
+    // partition's own pass over the input (2.2 us per 32 KB and CU) is for
+    // windows that keep a share of it
     p.levels = 2;
     cap1 = (uint64_t)cap_top;
     if (cap1 > p.n) cap1 = p.n;
@@ -77,15 +82,19 @@ void plan_for(SPlan& p) {
     sample_window((double)cap1, k, kSLevel2, false, &w2);
     cap = (uint64_t)span_cap(w2.r, (double)cap1 / kSLevel2);
     if (cap > cap1) cap = cap1;
-    const uint64_t b = 4 * cap / T::kTarget + 32;
+    const uint64_t b = 4 * cap / T::kTarget + 64;
     p.bmax = b < (uint64_t)T::kMaxB ? (uint32_t)b : (uint32_t)T::kMaxB;
+  } else if (gap <= 2.0 * T::kTarget) {
+    sample_buckets(gap, T::kTarget, T::kMaxB, &w);
+    cap = (uint64_t)span_cap(w.r - w.a, gap);
+    p.bmax = w.B;
   } else {
     return;
   }
   p.win = w;
   if (cap > p.n) cap = p.n;
-  // rows: one per workgroup, and any two rows of a workgroup but its last hold a stage
-  const uint64_t rows = grid_for(p.levels == 2 ? cap1 : p.n, T::kStage, 256) + 2 * cap / T::kStage + 1;
+  // rows: a workgroup's last, and those written because a tile did not fit
+  const uint64_t rows = grid_for(p.levels == 2 ? cap1 : p.n, T::kTile, 256) + cap / (T::kStage - T::kTile) + 1;
   if (!p.plain && rows > (uint64_t)kSMaxRows) return;
   p.rows = (uint32_t)rows;
   p.cap1 = (uint32_t)cap1;
@@ -102,28 +111,28 @@ void plan_for(SPlan& p) {
   p.off_smp = seg(ms * sizeof(C));
   p.off_sorted = seg(ms * sizeof(C));
   if (p.levels == 2) p.off_c1 = seg((size_t)p.cap1 * sizeof(C));
-  p.off_cand = seg((size_t)p.cap * sizeof(C));
+  p.off_cand = seg(((size_t)p.cap + 1) * sizeof(C));  // whole 16-byte pieces
   if (!p.plain) {
     p.off_rows = seg(p.rows * sizeof(SRow));
+    p.off_bounds = seg((size_t)p.bmax * sizeof(C));
     p.off_offs = seg((size_t)p.rows * p.pitch * sizeof(uint16_t));
   }
-  p.off_pos = off;
   p.total = off;
   p.on = true;
 }
 
 // Whether one workgroup takes the call whole, and its cut: r = 0 sends every
 // element to the sort, else the r-th of 256 samples.  A miss only costs a few passes over
-// at most 65536 keys, so three and a half standard deviations will do.
+// at most 65536 keys, so four and a half standard deviations will do.
 template <typename K>
 bool one_fits(uint64_t n, uint32_t k, uint32_t* r) {
   const uint32_t cap = n <= 1024 ? 1024u : SOne<K>::kCap;
   *r = 0;
   if (n <= cap) return true;
   if (n > 65536) return false;
-  const double lam = (double)k * kSSplit / n, q = lam + 3.5 * std::sqrt(lam) + 5.0;
+  const double lam = (double)k * kSSplit / n, q = lam + 4.5 * std::sqrt(lam) + 6.0;
   *r = (uint32_t)q;
-  return (q + 3.5 * std::sqrt(q) + 4.0) * n / kSSplit <= cap;
+  return (q + 4.0 * std::sqrt(q) + 4.0) * n / kSSplit <= cap;
 }
 
 template <typename K>
@@ -134,10 +143,10 @@ void enqueue_one(const SPlan& p, const void* keys_v, K* out_vals, uint32_t* out_
   const int kth = p.kth_only ? 1 : 0;
   if (n <= 1024)
     hipLaunchKernelGGL((k_sone<K, 256>), dim3(1), dim3(256), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, out_idx,
-                       out_kth);
+                       out_kth, p.pay);
   else
     hipLaunchKernelGGL((k_sone<K, 1024>), dim3(1), dim3(1024), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, out_idx,
-                       out_kth);
+                       out_kth, p.pay);
 }
 
 template <typename K>
@@ -154,6 +163,7 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
   C* cand = at<C>(ws, p.off_cand);
   SRow* rows = at<SRow>(ws, p.off_rows);
   uint16_t* offs = at<uint16_t>(ws, p.off_offs);
+  C* bounds = at<C>(ws, p.off_bounds);
   const int kth = p.kth_only ? 1 : 0;
   auto rank = [&](uint32_t m) {
     const dim3 g(m / kSRankPer), t(kSRankThreads);
@@ -163,7 +173,7 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
   };
   pm.start(s);  // the timed pass: the sample and the one pass over the input
   if (p.top)
-    hipLaunchKernelGGL((k_sgather<K, false, true>), dim3(p.m / kSKeep), dim3(256), 0, s, keys, (const C*)nullptr, p.n,
+    hipLaunchKernelGGL((k_sgather<K, false, true>), dim3(p.m / kSKeep), dim3(1024), 0, s, keys, (const C*)nullptr, p.n,
                        0u, p.k, p.m * 16, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
   else
     hipLaunchKernelGGL((k_sgather<K, false, false>), dim3(p.m / 256), dim3(256), 0, s, keys, (const C*)nullptr, p.n,
@@ -174,37 +184,48 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
     uint64_t* al = p.plain ? &ctl->alloc : &ctl->alloc1;
     C* o = p.plain ? cand : c1;
     const uint32_t c = p.plain ? p.cap : p.cap1;
-    if (p.n < 8 * load * 512)
-      hipLaunchKernelGGL((k_sfilter<K, 2>), dim3(grid_for(p.n, 2 * load, 1024)), dim3(kSFilterThreads), 0, s, keys,
-                         p.n, p.head, cd, p.L, p.win.r, p.m, sorted, al, o, c);
-    else
-      hipLaunchKernelGGL((k_sfilter<K, 8>), dim3(grid_for(p.n, 8 * load, 1024)), dim3(kSFilterThreads), 0, s, keys,
-                         p.n, p.head, cd, p.L, p.win.r, p.m, sorted, al, o, c);
+#define DRTOPK_FILTER(U)                                                                                            \
+  hipLaunchKernelGGL((k_sfilter<K, U>), dim3(grid_for(p.n, U * load, 512)), dim3(kSFilterThreads), 0, s, keys, p.n, \
+                     p.head, cd, p.L, p.win.r, p.m, sorted, al, o, c)
+    // as many loads a tile as leave every workgroup two tiles
+    if (p.n < 2 * 2 * load * 512) DRTOPK_FILTER(1);
+    else if (p.n < 4 * 2 * load * 512) DRTOPK_FILTER(2);
+    else DRTOPK_FILTER(4);
+#undef DRTOPK_FILTER
   } else {
-    const unsigned g = grid_for(p.n, T::kStage, 256);
+    const unsigned g = grid_for(p.n, T::kTile, 256);
     hipLaunchKernelGGL((k_spart<K, false>), dim3(g), dim3(kSPartThreads), 0, s, keys, (const C*)nullptr, p.n, p.head,
-                       0u, p.k, p.m, cd, p.L, sorted, ctl, cand, p.cap, p.rows, rows, offs, p.pitch);
+                       0u, p.k, p.m, p.win, cd, p.L, sorted, ctl, cand, p.cap, p.rows, rows, offs, p.pitch, bounds);
   }
   pm.mid(s);
   if (p.levels == 2) {
     hipLaunchKernelGGL((k_sgather<K, true, false>), dim3(kSLevel2 / 256), dim3(256), 0, s, keys, c1, p.n, p.cap1, p.k,
                        kSLevel2, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
     rank(kSLevel2);
-    const unsigned g = grid_for(p.cap1, T::kStage, 256);
+    const unsigned g = grid_for(p.cap1, T::kTile, 256);
     hipLaunchKernelGGL((k_spart<K, true>), dim3(g), dim3(kSPartThreads), 0, s, keys, c1, p.n, 0u, p.cap1, p.k,
-                       kSLevel2, cd, p.L, sorted, ctl, cand, p.cap, p.rows, rows, offs, p.pitch);
+                       kSLevel2, p.win, cd, p.L, sorted, ctl, cand, p.cap, p.rows, rows, offs, p.pitch, bounds);
   }
-  if (p.plain)
-    hipLaunchKernelGGL((k_sbucket<K, true>), dim3(1), dim3(kSBucketThreads), 0, s, keys, p.n, p.k, kth, p.levels, cd,
-                       p.L, ctl, cand, p.cap1, p.cap, p.rows, rows, offs, p.pitch, out_vals, out_idx, out_kth);
-  else
-    hipLaunchKernelGGL((k_sbucket<K, false>), dim3(p.bmax), dim3(kSBucketThreads), 0, s, keys, p.n, p.k, kth, p.levels,
-                       cd, p.L, ctl, cand, p.cap1, p.cap, p.rows, rows, offs, p.pitch, out_vals, out_idx, out_kth);
+#define DRTOPK_BUCKET(MODE, RARE, GRID, SECOND)                                                                    \
+  hipLaunchKernelGGL((k_sbucket<K, MODE, RARE>), dim3(GRID), dim3(kSBucketThreads), 0, s, keys, p.n, p.k, kth,     \
+                     p.levels, SECOND, cd, p.L, ctl, cand, p.cap1, p.cap, p.rows, rows, offs, p.pitch, p.m, p.win,   \
+                     sorted, bounds, out_vals, out_idx, out_kth, p.pay)
+  if (p.plain && p.bmax == 1) {
+    DRTOPK_BUCKET(kSPlain, true, 1, 0);
+  } else if (p.plain) {
+    DRTOPK_BUCKET(kSList, true, p.bmax, 0);
+  } else if (p.bmax <= 512 || kth) {  // one workgroup a CU, two rounds at most; of one bucket
+    DRTOPK_BUCKET(kSRows, true, p.bmax, 0);
+  } else {
+    DRTOPK_BUCKET(kSRows, false, p.bmax, 0);
+    DRTOPK_BUCKET(kSRows, true, p.bmax, 1);
+  }
+#undef DRTOPK_BUCKET
 }
 
 }  // namespace
 
-void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, bool pos_in_ws, SPlan* out) {
+void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, SPlan* out) {
   SPlan p;
   p.n = n;
   p.k = k;
@@ -222,17 +243,19 @@ void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_o
   const uint32_t word = p.wide ? 8 : 4;
   p.head = (uint32_t)(((16 - (reinterpret_cast<uintptr_t>(keys) & 15u)) & 15u) / word);
   if ((reinterpret_cast<uintptr_t>(keys) & (word - 1)) == 0) {
-    // float keys of both signs crowd linear bins when most of them are sorted:
-    // up to 4096 the batched form's selection is faster (k = 2048 of 4096 normal
-    // float32: 12.7 against 19.9 us; uint32: 12.9 against 9.1)
-    const bool crowd = base == DRTOPK_F32 && n <= 4096 && k <= 2048 && (uint64_t)k * 4 > n;
-    p.one = (k > 1 || p.wide) && !crowd && (p.wide ? one_fits<uint64_t>(n, k, &p.win.r) : one_fits<uint32_t>(n, k, &p.win.r));
+    // left to the batched form's kernel: most of a few keys, which crowd the
+    // bins of a sort where they lie in clusters or, floats, on both sides of
+    // zero (2048 of 4096 normal float32: 12.7 against 19.9 us), and a handful
+    // of many (4 of 50000 uint32: 14.8 against 19.3; 64 of them: 21.5 / 19.1)
+    const bool old = !p.wide && ((n <= 8192 && k <= 2048 && (uint64_t)k * 8 > n) ||
+                                 (n > 8192 && n <= 65536 && k <= 16));
+    p.one = (k > 1 || p.wide) && !old &&
+            (p.wide ? one_fits<uint64_t>(n, k, &p.win.r) : one_fits<uint32_t>(n, k, &p.win.r));
     if (p.one) p.on = true;
-    else if (crowd) ;
+    else if (old) ;
     else if (p.wide) plan_for<uint64_t>(p);
     else plan_for<uint32_t>(p);
   }
-  if (p.on && pos_in_ws) p.total = salign(p.off_pos + (size_t)k * 4);
   *out = p;
 }
 

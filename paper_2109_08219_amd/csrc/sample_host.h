@@ -18,9 +18,10 @@ struct SPlan {
   bool wide = false;      // 8-byte keys
   uint32_t head = 0;      // keys before the first 16-byte boundary
   bool kth_only = false;
+  SPayload pay = {};      // set by the caller
   bool one = false;       // one workgroup takes the whole problem
   int levels = 1;         // 2: the first filter's candidates are sampled and partitioned again
-  int plain = 0;          // one bucket: the candidates are sorted by one workgroup
+  int plain = 0;          // the candidates are one list, not grouped by bucket
   uint64_t n = 0;
   uint32_t k = 0;
   int L = 1;              // position bits of a composite
@@ -32,13 +33,12 @@ struct SPlan {
   uint32_t rows = 0;      // rows of the offset table
   uint32_t pitch = 0;            // entries of a row of the offset table
   uint64_t codec_a = 0, codec_c = 0;
-  size_t off_ctl = 0, off_smp = 0, off_sorted = 0, off_c1 = 0, off_cand = 0, off_rows = 0, off_offs = 0;
-  size_t off_pos = 0;     // k output positions (payload gathers without out_idx)
+  size_t off_ctl = 0, off_smp = 0, off_sorted = 0, off_c1 = 0, off_cand = 0, off_rows = 0, off_offs = 0, off_bounds = 0;
   size_t total = 0;
 };
 
 // Fills *out (out->on false: the path does not take this call).
-void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, bool pos_in_ws, SPlan* out);
+void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, SPlan* out);
 
 // Enqueues the whole path on `s` over the workspace `ws` (p.total bytes).
 int sample_enqueue(const SPlan& p, const void* keys, void* ws, void* out_vals, uint32_t* out_idx,

@@ -8,16 +8,27 @@
 
 namespace drtopk {
 
+// Payload of each selected key, gathered where its slot is written (bytes 0:
+// none; 4 or 8).
+struct SPayload {
+  const void* in;
+  void* out;
+  uint32_t bytes, pad;
+};
+
 // The window of sample ranks of one level: elements above the a-th sample are
 // counted only, those from it down to the r-th sample are the candidates.
-// Buckets: with P = 0, every s samples from rank a on; otherwise P equal
-// intervals of composite space (a power of two) between every eighth sample,
-// and kSTop intervals above the first sample when the window is open (a = 0).
+// Buckets: with P = 0, every s samples from rank a on.  Otherwise, with P a
+// power of two, from rank max(a, 1) on: P equal intervals of composite space
+// between every kSGroup-th sample; and when the window is open (a = 0), where
+// the keys thin out, before that kSTop intervals above the first sample and
+// over the first kSThin groups the samples themselves besides the intervals.  s: groups in all.
 struct SWin {
   uint32_t r, a, s, P, B, pad[3];
 };
 constexpr uint32_t kSTop = 8;
-constexpr uint32_t kSGroup = 8;
+constexpr uint32_t kSGroup = 16;
+constexpr uint32_t kSThin = 4;
 
 // Window for rank k of `count` elements under m samples: the number of
 // samples among the k largest is bounded both ways but for a probability below
@@ -33,28 +44,33 @@ __host__ __device__ inline void sample_window(double count, double k, double m, 
   w->r = hi < m ? (uint32_t)hi : (uint32_t)m + 1;  // m + 1: no cut, every element is a candidate
   w->a = kth && lo >= 1.0 ? (uint32_t)lo : 0u;
 }
+// Splitters of the first `thin` groups (see SWin) and of one after them.
+__host__ __device__ inline uint32_t thin_splits(uint32_t P) { return P + kSGroup - 1; }
+
 // Buckets are planned for `target` elements.  Gaps between neighbouring samples
-// are as uneven as exponential variables (one in 55 holds four times the
-// mean), so where a bucket would be less than four gaps it is an interval
-// between samples eight gaps apart instead (four times the mean: 1 in 10^7
-// where the density is smooth).
+// are as uneven as exponential variables (one in 43 holds 3.75 times the mean,
+// a workgroup's capacity), so where a bucket would be less than six gaps it is
+// an equal part of the space between every sixteenth sample instead: as even as
+// that space, a quarter of the mean in one standard deviation, where the density
+// changes little over it.
 __host__ __device__ inline void sample_buckets(double gap, uint32_t target, uint32_t bmax, SWin* w) {
   const uint32_t q0 = w->a ? w->a : 1u, top = w->a ? 0u : kSTop;
   const uint32_t groups = (w->r - q0 + kSGroup - 1) / kSGroup;
   uint32_t P = 0;
-  if (4.0 * gap > (double)target) {
+  if (6.0 * gap > (double)target) {
     P = 4;
-    while (P < 64 && 8.0 * gap > (double)target * P) P <<= 1;
-    while (P > 1 && top + (uint64_t)groups * P > bmax) P >>= 1;
-    if (top + (uint64_t)groups * P > bmax || P < 4) P = 0;
+    while (P < 64 && (double)kSGroup * gap > (double)target * P) P <<= 1;
+    const uint32_t thin = w->a ? 0u : groups < kSThin ? groups : kSThin;
+    const uint64_t B = top + (uint64_t)thin * thin_splits(P) + (uint64_t)(groups - thin) * P;
+    w->B = (uint32_t)B;
+    if (B > bmax) P = 0;
   }
   w->P = P;
   if (P) {
-    w->s = 0;
-    w->B = top + groups * P;
+    w->s = groups;
     return;
   }
-  const double per = (double)target / gap;
+  const double per = 0.75 * (double)target / gap;
   uint32_t s = per > 1.0 ? (per < 1e6 ? (uint32_t)per : 1000000u) : 1u;
   const uint32_t span = w->r - w->a;
   if ((uint64_t)s * bmax < span) s = (span + bmax - 1) / bmax;
