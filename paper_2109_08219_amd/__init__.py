@@ -181,9 +181,14 @@ def _prep(keys, dtype, largest: bool = True):
 
 
 def _stream(stream):
+    """Handle of the stream, or of the current one (read without building a torch.cuda.Stream,
+    which took a fifth of a small call's host time)."""
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _opts(alpha, beta, mode, variant=0):
@@ -226,8 +231,7 @@ def topk_select(keys, k: int, out_vals=None, out_idx=None, *, dtype=None, larges
         out_idx = torch.empty(k, dtype=torch.int32, device=keys.device)
     opts = _opts(alpha, beta, mode, variant)
     st = Stats() if stats else None
-    rc = lib().topk_select_ex(ctypes.c_void_p(keys.data_ptr()), keys.numel(), k, code,
-                              ctypes.c_void_p(out_vals.data_ptr()), ctypes.c_void_p(out_idx.data_ptr()),
+    rc = lib().topk_select_ex(keys.data_ptr(), keys.numel(), k, code, out_vals.data_ptr(), out_idx.data_ptr(),
                               ctypes.byref(opts) if opts is not None else None,
                               ctypes.byref(st) if st is not None else None, _stream(stream))
     if rc != 0 and st is not None and st.err_flags:
@@ -259,8 +263,7 @@ def kth_select(keys, k: int, out=None, *, dtype=None, largest: bool = True, chec
     code = _prep(keys, dtype, largest)
     if out is None:
         out = torch.empty(1, dtype=keys.dtype, device=keys.device)
-    rc = lib().kth_select(ctypes.c_void_p(keys.data_ptr()), keys.numel(), k, code,
-                          ctypes.c_void_p(out.data_ptr()), _stream(stream))
+    rc = lib().kth_select(keys.data_ptr(), keys.numel(), k, code, out.data_ptr(), _stream(stream))
     _check(rc, "kth_select")
     if check:
         check_stream(stream)
