@@ -80,10 +80,9 @@ typedef enum {
  *   out_idx  device, k uint32 positions into keys (out_vals[r] == keys[out_idx[r]]),
  *            or NULL
  *   stream   hipStream_t or NULL
- * Beyond one workgroup's sizes (n > 2^16 or k > 2048, n >= 2^14, k > 1) calls
- * without explicit options or counters split the work by a sample of the keys
- * (filter pass, buckets sorted independently); the result is the same, and
- * exact, whatever the sample. */
+ * Calls with k > 1 (8-byte keys: any k) split the work by a sample of the keys
+ * (one workgroup with a cut for few keys; else a filter pass and buckets sorted
+ * independently); the result is exact whatever the sample. */
 int topk_select(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals,
                 uint32_t* out_idx, void* stream);
 

@@ -1,6 +1,9 @@
 // Host side of drtopk: planner, per-stream workspace, kernel sequence, C-ABI.
 //
-// One call enqueues, on the caller's stream and with no host synchronisation:
+// A call enqueues its kernels on the caller's stream with no host
+// synchronisation.  Calls with the planner's choices take the sampled path
+// (sample.h) wherever it is planned (take_sampled); the others, and calls with
+// explicit options or counters:
 //   k_init -> delegate pass (+ first digit of the delegate select) -> five more
 //   digit passes over the delegates (threshold t, Rule 2) -> qualify (Rule 3)
 //   -> scan of the qualifying subranges -> survivor select -> sorted output.
@@ -397,13 +400,15 @@ constexpr size_t kSampledFree = size_t(4) << 20;
 
 // Whether a call with the planner's choices (no explicit options, no counters
 // asked for) takes the sampled path: wherever it can be planned, since it was
-// the faster one at every size measured (n = 2^20, k = 1024 uint32: 28.6
-// against 39.1 us; n = 3 * 10^6, k = 100: 29.9 / 46.3; n = 2^24, k = 2^21:
-// 129 / 641, its median: 60 / 262; n = 2^30, k = 1024: 666 / 676, k = 131072:
-// 673 / 799; float64, n = 2^28, k = 131072: 375 / 799).  k = 1 of 32-bit keys
-// stays with the delegate pass, which alone answers it.  `total` is the workspace of the
-// other path: the no-allocation limit is stated in it, so the sampled path
-// needs no more than that or a small part of that limit.
+// the faster one at every size measured (us a call, against the other path;
+// 50000 float32, k = 64: 19.9 / 21.9; n = 2^20, k = 1024 uint32: 23.9 / 39.6;
+// n = 3 * 10^6, k = 100: 24.4 / 47.6; n = 2^24, k = 2^21: 90 / 641, its median:
+// 59 / 261; n = 2^29 of 16 values, k = 16384: 350 / 446; n = 2^30, k = 1024:
+// 660 / 679, k = 131072: 667 / 796; float64, n = 2^28, k = 131072: 364 / 799).
+// k = 1 of 32-bit keys stays with the delegate pass, which alone answers it.
+// `total` is the workspace of the other path: the no-allocation limit is stated
+// in it, so the sampled path needs no more than that or a small part of that
+// limit.
 bool take_sampled(const SPlan& sp, size_t total) {
   return sp.on && (sp.k > 1 || sp.wide) && sp.total <= (total > kSampledFree ? total : kSampledFree) &&
          g_cap_override.load(std::memory_order_relaxed) == 0;

@@ -139,7 +139,9 @@ __device__ __forceinline__ uint32_t shash(uint32_t x) {
 // for odds far below the window's own, and if one is lost the r-th kept sample
 // only lies lower: more candidates, never fewer.  So 65536 samples cost one
 // gather and the ranks of 4096, and the r-th of 65536 leaves a tenth to a half
-// of the candidates that the corresponding sample of 4096 does.
+// of the candidates that the corresponding sample of 4096 does (n = 2^20, k =
+// 1024: 28.6 us a call with 8192 plain samples, 23.9 with these).  Bound by the
+// latency of one load from memory and of the count: 4.6 us.
 // The launch also clears the state of the kernels after it.
 constexpr uint32_t kSKeep = 16;
 
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(TOP ? 1024 : 256) void k_sgather(const K* __restric
 // vector compare and a scalar bit count.  J * 512 = m samples.  The workgroup's
 // own 16 samples reach the scalar side by lane reads: scalar loads in the loop
 // had it wait for memory once per four (m = 4096: 6.7 us with 32 samples a
-// workgroup, the launch 2 of them).
+// workgroup, the launch 2 of them; now 4.4, m = 8192 8.5).
 template <typename C>
 __device__ __forceinline__ C sread_lane(C v, int lane) {
   uint32_t w[sizeof(C) / 4];
@@ -260,7 +262,10 @@ __global__ __launch_bounds__(kSRankThreads) void k_srank(const C* __restrict__ s
 // works on the current one.  A wave keeps its candidates in its own LDS slots
 // and its fill level in a register; no barrier before the end, and one device
 // atomic a workgroup for what is left then (they are served one at a time,
-// 11.5 ns each, hence few large workgroups: two of 1024 threads a CU).
+// 11.5 ns each, hence few large workgroups: two of 1024 threads a CU).  Bound
+// by memory from 2^25 keys on (24.5 us, 5.5 TB/s; 2^30: 630 us, 6.8 TB/s, where
+// the delegate pass takes 665) and by launch, first load and atomics below
+// (2^20: 6.7 us).
 // head: keys before the first 16-byte boundary.
 template <typename K, int U>
 __global__ __launch_bounds__(kSFilterThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_sfilter(
@@ -525,7 +530,11 @@ struct SStage<K, true, ST> {
 // those inside it, and writes every full stage as one row of the candidate
 // buffer, grouped by bucket.  A row's place costs one device atomic; the
 // bucket's size and first output slot are sums over the rows' offsets, so no
-// counting pass and no global scatter are needed.  One workgroup a CU.
+// counting pass and no global scatter are needed.  One workgroup a CU.  Bound by
+// instructions (2.2 us a tile of 32 KB and CU, 1.3 of them memory) and by a
+// row's chain of LDS steps: n = 2^24 float32, k = 2^21: 42 us, its median 37,
+// where six passes of a digit select took 260 and the sort of the select's
+// output 380.
 template <typename K, bool ARR>
 __global__ __launch_bounds__(kSPartThreads) void k_spart(const K* __restrict__ keys,
                                                          const typename STraits<K>::Comp* __restrict__ arr,
@@ -1290,7 +1299,9 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
 // then takes so many registers that one workgroup fills a CU: for few buckets.
 // With many, a kernel without them runs first (two workgroups a CU) and only
 // notes in ctl->rare that they are needed; `second` then runs this kernel for
-// those buckets, or for nothing.
+// those buckets, or for nothing.  Bound by the chain of LDS passes of one
+// bucket: one bucket of up to 7680, 8 us; 2^21 elements in 1300 buckets, 37 us,
+// where LDS tiles and merges took 320; a list of 10^4 with payloads 18 us.
 template <typename K, SMode MODE, bool RARE>
 __global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu(RARE ? 2 : 4))) void k_sbucket(
     const K* __restrict__ keys, uint64_t n, uint32_t k, int kth_only, int levels, int second, SCodec<K> cd, int L,
@@ -1450,7 +1461,10 @@ __global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu
 // sort.  Otherwise the r-th of 256 samples cuts the input to between k and
 // CAP elements in one streaming pass, the survivors collected in LDS and
 // sorted; when the sample misjudges that, the k-th element is found by
-// histograms of the input instead.  k <= CAP.
+// histograms of the input instead.  k <= CAP.  Bound by the issue of one CU's
+// vector units, about 15 instructions a key: 50000 float32, k = 64, 19.9 us a
+// call against 21.9 for the delegate method in one workgroup; a few thousand 8-byte keys
+// 7 against 43 for the passes over the device.
 template <typename K>
 struct SOne {
   typedef typename STraits<K>::Comp C;

@@ -21,8 +21,9 @@ struct SPayload {
 // Buckets: with P = 0, every s samples from rank a on.  Otherwise, with P a
 // power of two, from rank max(a, 1) on: P equal intervals of composite space
 // between every kSGroup-th sample; and when the window is open (a = 0), where
-// the keys thin out, before that kSTop intervals above the first sample and
-// over the first kSThin groups the samples themselves besides the intervals.  s: groups in all.
+// the keys thin out, before that kSTop intervals above the first sample and over
+// the first kSThin groups the samples themselves besides the intervals.  s:
+// groups in all.
 struct SWin {
   uint32_t r, a, s, P, B, pad[3];
 };
