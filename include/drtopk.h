@@ -129,14 +129,14 @@ typedef struct {
  * call (the caller may reuse it on return).  Each problem obeys topk_select's
  * rules, except that out_vals may be NULL when out_kth is not (k-selection
  * only).  Results equal topk_select / kth_select on each problem alone, bit
- * for bit.  Problems with n <= 2^22 and k <= 2048 run in one persistent
- * launch, one workgroup per problem at a time, largest first (the delegate
- * method of Sections 4-5 inside the workgroup's LDS); larger ones run one
+ * for bit.  Problems with n <= 2^22 and k <= 2048 run in one launch,
+ * a workgroup per problem, largest first, each in one pass over its keys;
+ * larger ones run one
  * after another through the single-problem path, on the same stream.  Any
  * invalid descriptor, or count >= 2^24, fails the whole call with
- * DRTOPK_EINVAL before any work is enqueued.  Problems of more than 2^16 keys
- * on the delegate route may have their delegate vector built by several
- * workgroups.  Output buffers of different problems must not overlap. */
+ * DRTOPK_EINVAL before any work is enqueued.  Problems of more than 2^16 keys and
+ * of more than a workgroup's share of the batch run the delegate method of
+ * Sections 4-5 over several workgroups.  Output buffers of different problems must not overlap. */
 int topk_select_batched(const drtopk_problem_t* problems, uint32_t count, void* stream);
 
 /* Autotuner table (Rule 4's subrange size and Rule 3's beta, measured rather
@@ -164,7 +164,9 @@ int drtopk_tune_set(const drtopk_tune_t* entries, uint32_t count);
 /* Copies up to `cap` entries to `out` (host) and the table size to *count. */
 int drtopk_tune_get(drtopk_tune_t* out, uint32_t cap, uint32_t* count);
 
-/* How a batched problem of this shape is run (no device work):
+/* How the delegate method would run a batched problem of this shape (no device
+ * work; alpha and beta are those of split problems, and of whole ones where a
+ * batch splits many):
  *   *route 0 = single-problem path, 1 = sorted outright in the workgroup,
  *          2 = delegate method in the workgroup with subrange exponent
  *          *alpha and *beta delegates per subrange (1 or 2; beta may be

@@ -1,25 +1,29 @@
-// Many independent top-k problems in one persistent launch.
+// Many independent top-k problems in one launch.
 //
-// Each workgroup (kBT threads) takes whole problems from an atomic counter,
-// largest first (the host orders them), and runs the delegate method for one
-// problem entirely in its LDS:
+// A workgroup (kBT threads, two share a CU, so one streams keys while the other
+// sorts) takes one problem:
+//   of at most kBSmallN keys: selected in LDS directly (the k-th by radix
+//     select, then the k at or above it sorted);
+//   of more: one pass over its keys (b_stream).
+// Problems of more than a slot's share of the batch's keys are split, and run
+// the delegate method over several workgroups:
 //   delegate vector (Rules 1 and 3): the top beta (1 or 2) of each subrange
-//     of 2^alpha keys, built in LDS by waves streaming the keys;
+//     of 2^alpha keys, built in LDS by waves streaming the keys, a tile a
+//     workgroup, and published; the workgroup that arrives last goes on:
 //   t = the k-th largest delegate: an LDS radix select over the delegates;
 //   survivors (Rules 2 and 3): t itself, every element ranked >= t in the
 //     subranges whose last delegate ranks above t (read as one virtual
 //     concatenated vector), and with beta = 2 the first delegates above t of
 //     the other subranges;
 //   output: survivors sorted in registers, the first k written.
-// Problems of at most kBSmallN keys are selected in LDS directly (the k-th
-// by radix select, then the k at or above it sorted).  A problem whose
-// survivors overflow the LDS (adversarial inputs), or whose delegate vector
-// would not exceed k, takes a block-level MSD radix select over its keys.
-// Two workgroups share a CU, so one streams keys while the other sorts.
-// No workgroup ever waits for another: the only shared state is the claim
-// counter.
+// When there are many tiles of split problems (k_batched_split), and for one
+// problem alone (k_one), whole problems run the delegate method in one
+// workgroup's LDS too.  One whose survivors overflow the LDS (adversarial
+// inputs), or whose delegate vector would not exceed k, takes a block-level MSD
+// radix select over its keys.  No workgroup ever waits for another.
 #pragma once
 
+#include "sample.h"
 #include "tail.h"
 
 namespace drtopk {
@@ -163,9 +167,11 @@ struct Keys {
   __amdgpu_buffer_rsrc_t r;
   __device__ __forceinline__ Keys(const uint32_t* p, uint32_t nrec)
       : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p), (short)0, (int)(nrec * 4u), kBufWord3)) {}
+  // NT: read once, not to be kept in the caches
+  template <int NT = 0>
   __device__ __forceinline__ void load4(uint32_t p, uint32_t (&v)[4]) const {
     if constexpr (VEC) {
-      const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(p * 4u), 0, 0);
+      const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(p * 4u), 0, NT ? 2 : 0);
       v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     } else {
 #pragma unroll
@@ -815,6 +821,283 @@ template <bool VEC, int BETA>
 __device__ inline void b_tile(const BatchDesc& d, uint32_t tile, uint32_t* arrive, uint64_t* Dg, BatchSmem& sm,
                               uint32_t* rec);
 
+// ---------------------------------------------------------------------------
+// Top-k of one problem by one workgroup in one pass over its keys.
+//
+// A sample of the keys gives a first cut.  Elements that reach the cut are
+// appended to LDS, each wave to a region of its own.  When a region is full,
+// everything below the k-th of what is held (roughly: below the bin of a
+// 2048-bin histogram that the k-th lies in) is dropped and the cut raised to
+// it.  What is left at the end is sorted.  Exact for every input: an element is
+// dropped only if k others rank above it or by the first cut, and if fewer
+// than k reach that, the keys are read once more without it.
+//
+// Bound by memory (4096 problems of 2^10 to 2^20 keys, k <= 2048: 499 us, 5.0
+// TB/s; by delegates and a re-read of 25 to 50% of the large problems' keys, or
+// several passes where k is large: 649) as long as what an element costs stays
+// small: about five instructions a key, and a load with hits four compares more.
+// Placing hits by a scan and an LDS atomic a chunk took 600 instructions a chunk
+// and 560 -> 690 us; raising the cut from the first keys instead of a sample,
+// four more sorts of the buffer a problem.  Loads marked for one use: 616 -> 582.
+constexpr uint32_t kBStreamCap = 7680;               // elements held (two workgroups fit a CU)
+constexpr uint32_t kBRegion = kBStreamCap / kBWaves; // of them by one wave
+constexpr uint32_t kBStreamSlack = kBStreamCap / 4;  // elements kept beyond k when the cut is raised
+// Keys a wave takes at a time, the next as many in flight: 1536 spill registers
+// (582 us where 1280 and 1024 take 534).
+constexpr uint32_t kBChunk = 1024;
+static_assert((kBMaxK + kBStreamSlack) / kBWaves + 1 + 256 <= kBRegion, "room for a load after every raise");
+static_assert(kBRegion % 64 == 0, "a region is whole rows of a wave");
+
+struct BStreamSmem : SSortShared<uint64_t, kBStreamCap, kBT> {
+  uint32_t fill[kBWaves];  // elements in each region
+  uint32_t full;           // a region is full
+};
+
+// A composite that at least k and at most k + slack of the N in sm.buf reach
+// (those above `hi` or below `lo` are not looked at; every thread calls).
+__device__ __forceinline__ uint64_t b_stream_cut(BStreamSmem& sm, uint32_t N, uint32_t k, uint32_t slack, uint64_t lo,
+                                                 uint64_t hi) {
+  uint32_t above = 0;  // elements above hi
+  for (;;) {
+    const int sh = sbucket_hist<uint64_t, kBStreamCap, kBT>(sm, N, lo, hi, [&](uint64_t i) { return sm.buf[i]; });
+    const uint32_t need = k - above;
+    for (uint32_t b = threadIdx.x; b < (uint32_t)kSBins; b += kBT)
+      if (sm.hist[b] < need && need <= sm.hist[b + 1]) sm.misc[2] = b;
+    __syncthreads();
+    const uint32_t b = sm.misc[2], before = sm.hist[b], upto = sm.hist[b + 1];
+    __syncthreads();
+    const uint64_t first = hi - ((uint64_t)b << sh), width = ((uint64_t)1 << sh) - 1;
+    lo = first - lo > width ? first - width : lo;
+    if (sh == 0 || above + upto <= k + slack) return suniform(lo);
+    hi = first;
+    above += before;
+  }
+}
+
+// Moves the regions' elements to the front of sm.buf and returns their number.
+__device__ __forceinline__ uint32_t b_stream_gather(BStreamSmem& sm) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t at = 0, N = 0;
+  for (uint32_t w = 0; w < (uint32_t)kBWaves; ++w) {
+    if (w == wave) at = N;
+    N += sm.fill[w];
+  }
+  const uint32_t mine = sm.fill[wave];
+  uint64_t c[kBRegion / 64];
+#pragma unroll
+  for (int e = 0; e < (int)(kBRegion / 64); ++e)
+    if (e * 64 + lane < mine) c[e] = sm.buf[wave * kBRegion + e * 64 + lane];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < (int)(kBRegion / 64); ++e)
+    if (e * 64 + lane < mine) sm.buf[at + e * 64 + lane] = c[e];
+  __syncthreads();
+  return N;
+}
+
+// Raises the cut to one that the elements held leave k of, and at most
+// kBStreamSlack more, drops those under it and deals the rest to the regions.
+// Returns the new cut.
+__device__ __forceinline__ uint64_t b_stream_raise(BStreamSmem& sm, uint32_t k, uint64_t cut, uint64_t top) {
+  constexpr int E = kBStreamCap / kBT;
+  const uint32_t N = b_stream_gather(sm);
+  // few held in all, but unevenly: dealing them out makes the room
+  const uint64_t lo = N > k + kBStreamSlack ? b_stream_cut(sm, N, k, kBStreamSlack, cut, top) : cut;
+  uint64_t c[E];
+  uint32_t mine = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t i = e * kBT + threadIdx.x;
+    c[e] = i < N ? sm.buf[i] : 0;
+    mine += i < N && c[e] >= lo ? 1u : 0u;
+  }
+  uint32_t tot;
+  uint32_t at = sblock_scan<kBT>(mine, sm.s_w, &tot);
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (e * kBT + threadIdx.x < N && c[e] >= lo) {
+      sm.buf[at % kBWaves * kBRegion + at / kBWaves] = c[e];
+      ++at;
+    }
+  if (threadIdx.x < kBWaves) sm.fill[threadIdx.x] = (tot + kBWaves - 1 - threadIdx.x) / kBWaves;
+  if (threadIdx.x == 0) sm.full = 0;
+  __syncthreads();
+  return lo;
+}
+
+// The pass over the keys.  Waves stream independently, the next chunk in
+// flight; one whose region is full sets sm.full, and every wave comes to the
+// barrier below when it sees that or has no chunk left, so they meet there the
+// same number of times.
+template <bool VEC>
+__device__ __forceinline__ void b_stream_keys(const uint32_t* keys, uint32_t n, uint32_t k, Codec cx, int L,
+                                              uint32_t posmask, uint64_t cut, BStreamSmem& sm) {
+  constexpr int U = kBChunk / 256;
+  const uint32_t n4 = vec_end<VEC>(n);
+  const Keys<VEC> ks(keys, n4);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t nch = (n4 + kBChunk - 1) / kBChunk;
+  uint64_t* st = sm.buf + wave * kBRegion;
+  uint32_t nx[U][4], v[U][4];
+  uint32_t i = wave, done = 0, fill = 0;  // the chunk in nx; its loads worked off; elements in the region
+  uint32_t tkey = 0, tpos = 0;
+  auto fetch = [&]() {  // past the last chunk: beyond the buffer resource, nothing is read
+#pragma unroll
+    for (int u = 0; u < U; ++u) ks.template load4<1>(i * kBChunk + u * 256 + lane * 4, nx[u]);
+  };
+  auto push = [&](bool in, uint32_t key, uint32_t p) {
+    const uint64_t b = __ballot(in);
+    if (b) {
+      if (in) st[fill + mbcnt(b)] = scomp<uint32_t>(key, p, L, posmask);
+      fill += (uint32_t)__popcll(b);
+    }
+  };
+  auto begin = [&]() {
+    tkey = (uint32_t)(cut >> L);
+    tpos = posmask - ((uint32_t)cut & posmask);
+    fill = done = 0;
+    i = wave;
+    fetch();
+    if (threadIdx.x == 0) sm.full = 0;
+    if (wave == 0 && n4 < n) {  // the keys after the last whole 16 bytes
+      const uint32_t p = n4 + lane;
+      const uint32_t x = p < n ? cx.enc(keys[p]) : 0u;
+      push(p < n && (x > tkey || (x == tkey && p <= tpos)), x, p);
+    }
+    if (tpos >= n4) tpos = n4 - 1;  // zeros read past n4 are keys of no position
+    __syncthreads();
+  };
+  // one chunk; false: a load (the one after `done` loads) may not fit
+  auto work = [&](uint32_t base) -> bool {
+    const uint32_t tnext = tkey + 1 ? tkey + 1 : tkey;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if ((uint32_t)u < done) continue;
+      const uint32_t a = v[u][0] > v[u][1] ? v[u][0] : v[u][1], b = v[u][2] > v[u][3] ? v[u][2] : v[u][3];
+      const uint32_t p1 = base + u * 256, p = p1 + lane * 4;
+      // keys equal to the cut's matter up to its position only
+      if (__ballot((a > b ? a : b) >= (p1 > tpos ? tnext : tkey))) {
+        if (fill + 256 > kBRegion) {
+          done = u;
+          return false;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) push(v[u][c] > tkey || (v[u][c] == tkey && p + c <= tpos), v[u][c], p + c);
+      }
+    }
+    done = 0;
+    return true;
+  };
+  begin();
+  for (;;) {
+    while (i < nch) {
+      const uint32_t base = i * kBChunk;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[u][c] = cx.enc(nx[u][c]);
+      i += kBWaves;
+      fetch();
+      if (base + kBChunk > n4) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (base + u * 256 + lane * 4 + c >= n4) v[u][c] = 0;
+      }
+      if (!work(base)) {
+        i -= kBWaves;  // read again once there is room: rare, and no registers held meanwhile
+        if (lane == 0) __hip_atomic_store(&sm.full, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        break;
+      }
+      if (__builtin_amdgcn_readfirstlane(
+              (int)__hip_atomic_load(&sm.full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)))
+        break;
+    }
+    if (lane == 0) sm.fill[wave] = fill;
+    __syncthreads();
+    if (!sm.full) {  // every wave came here without a chunk left
+      uint32_t N = 0;
+      for (uint32_t w = 0; w < (uint32_t)kBWaves; ++w) N += sm.fill[w];
+      if (N >= k) return;
+      cut = 0;  // the sample misjudged the keys: once more without it
+      __syncthreads();
+      begin();
+      continue;
+    }
+    cut = b_stream_raise(sm, k, cut, ((uint64_t)0xFFFFFFFFu << L) | posmask);
+    fill = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.fill[wave]);
+    tkey = (uint32_t)(cut >> L);
+    tpos = posmask - ((uint32_t)cut & posmask);
+    if (tpos >= n4) tpos = n4 - 1;
+    fetch();
+  }
+}
+
+// The first cut: of 2048 or 6144 keys, in runs of 16 (a line of memory) at
+// hashed places of equal strata, about the one that as many are expected above
+// as of the k largest, and four and a half standard deviations more.  Fewer
+// than k above it means a second pass, so no more margin is needed.
+__device__ __forceinline__ uint64_t b_stream_sample(const uint32_t* keys, uint32_t n, uint32_t k, Codec cx, int L,
+                                                    uint32_t posmask, BStreamSmem& sm) {
+  const int loads = n < (1u << 17) ? 1 : 3;
+  const Keys<false> ks(keys, n);
+  uint32_t x[3][4], p[3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (u < loads) {
+      const uint32_t g = (threadIdx.x >> 2) + u * (kBT / 4), G = loads * (kBT / 4);
+      const uint32_t lo = (uint32_t)((uint64_t)g * n / G), len = (uint32_t)((uint64_t)(g + 1) * n / G) - lo;
+      p[u] = ((lo + (uint32_t)(((uint64_t)shash(g) * len) >> 32)) & ~15u) + (threadIdx.x & 3u) * 4;
+      ks.load4(p[u], x[u]);
+    }
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (u < loads)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        sm.buf[(u * 4 + c) * kBT + threadIdx.x] = p[u] + c < n ? scomp<uint32_t>(cx.enc(x[u][c]), p[u] + c, L, posmask) : 0;
+  __syncthreads();
+  const uint32_t S = loads * 4 * kBT;
+  const float lam = (float)k * (float)S / (float)n;
+  const uint32_t r = (uint32_t)(lam + 4.5f * sqrtf(lam) + 6.0f);
+  return b_stream_cut(sm, S, r < S ? r : S, r / 8, 0, ((uint64_t)0xFFFFFFFFu << L) | posmask);
+}
+
+__device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm) {
+  constexpr int E = kBStreamCap / kBT;
+  const uint32_t n = (uint32_t)d.n, k = d.k;
+  const Codec cx = codec_of(d.dtype);
+  const int L = 32 - __clz((int)(n - 1));
+  const uint32_t posmask = (1u << L) - 1;
+  const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
+  const uint64_t cut = n <= kBStreamCap ? 0 : b_stream_sample(d.keys, n, k, cx, L, posmask, sm);
+  if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm);
+  else b_stream_keys<false>(d.keys, n, k, cx, L, posmask, cut, sm);
+  const uint32_t N = b_stream_gather(sm);
+  uint64_t c[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (e * kBT + threadIdx.x < N) c[e] = sm.buf[e * kBT + threadIdx.x];
+  __syncthreads();
+  ssort<uint64_t, kBStreamCap, kBT, E>(sm, c, N, k, [&](uint32_t r, uint64_t x) {
+    if (r >= k) return;
+    const uint32_t val = cx.dec((uint32_t)(x >> L));
+    if (d.out_vals) d.out_vals[r] = val;
+    if (d.out_idx) d.out_idx[r] = posmask - ((uint32_t)x & posmask);
+    if (d.out_kth && r == k - 1) *d.out_kth = val;
+  });
+}
+
+
+// LDS of a workgroup.
+union BatchLds {
+  BatchSmem b;
+  BStreamSmem s;
+};
+
+// By the descriptor's alpha and beta.
 template <bool VEC>
 __device__ inline void b_problem_v(const BatchDesc& d, BatchSmem& sm, uint32_t* rec) {
   if (d.n <= kBSmallN) {
@@ -877,6 +1160,13 @@ __device__ inline void b_problem(const BatchDesc& d, BatchSmem& sm, uint32_t* re
   else b_problem_v<false>(d, sm, rec);
 }
 
+// One problem of a batch in one pass.
+__device__ __forceinline__ void b_whole(const BatchDesc& d, BatchLds& lds) {
+  if (d.n > kBSmallN) b_stream(d, lds.s);
+  else if ((reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0) b_small<true>(d, lds.b);
+  else b_small<false>(d, lds.b);
+}
+
 __device__ inline void b_tile_any(const BatchDesc& d, uint32_t tile, uint32_t* arrive, uint64_t* Dg, BatchSmem& sm,
                                   uint32_t* rec) {
   const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
@@ -889,12 +1179,31 @@ __device__ inline void b_tile_any(const BatchDesc& d, uint32_t tile, uint32_t* a
   }
 }
 
-// Work items (problem << 8 | tile), claimed from *counter (starts at 0):
-// a problem with tiles <= 1 is one item and runs whole in the workgroup; a
-// split problem is `tiles` items whose workgroups share its delegate vector
-// through Dg, with arrive[problem] (starts at 0) counting finished tiles.
-// Any grid size works: no workgroup waits for another.
+// Work items are problem << 8 | tile, longest problems first: a problem with
+// tiles <= 1 is one item and runs whole in its workgroup; a split problem is
+// `tiles` items whose workgroups share its delegate vector through Dg, with
+// arrive[problem] (starts at 0) counting finished tiles.  No workgroup waits for
+// another.
+//
+// A workgroup per item.  (In a loop over items the whole problems' many
+// indices made from the thread's number are carried through it in registers:
+// 4000 of them spilled; and the code of a call costs 20 us a launch.)
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched(
+    const BatchDesc* __restrict__ descs, const uint32_t* __restrict__ items, uint32_t* arrive, uint64_t* Dg,
+    uint32_t* rec) {
+  __shared__ BatchLds lds;
+  const uint32_t it = items[blockIdx.x];
+  const uint32_t i = it >> 8;
+  const BatchDesc d = descs[i];
+  if (d.tiles > 1) b_tile_any(d, it & 0xFFu, &arrive[i], Dg, lds.b, rec);
+  else b_whole(d, lds);
+}
+
+// Items claimed from *counter (starts at 0), any grid size: for more tiles of
+// split problems than run at once, whose uneven ends a claim evens out better
+// than the order of launch does (512 problems of 2^20, k <= 2048: 558 us; 677 with
+// a workgroup per tile).
+__global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched_split(
     const BatchDesc* __restrict__ descs, const uint32_t* __restrict__ items, uint32_t nitems, uint32_t* counter,
     uint32_t* arrive, uint64_t* Dg, uint32_t* rec) {
   __shared__ BatchSmem sm;
@@ -919,9 +1228,10 @@ constexpr uint32_t kBInline = 32;
 struct BatchInline {
   BatchDesc d[kBInline];
 };
-__global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched_inline(BatchInline b, uint32_t* rec) {
-  __shared__ BatchSmem sm;
-  b_problem(b.d[blockIdx.x], sm, rec);
+__global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched_inline(BatchInline b) {
+  __shared__ BatchLds lds;
+  const BatchDesc d = b.d[blockIdx.x];
+  b_whole(d, lds);
 }
 
 // One problem, descriptor by value: the single-problem path for small inputs.

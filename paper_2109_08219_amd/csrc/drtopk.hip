@@ -621,13 +621,29 @@ size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
 // only).  Everything before the delegate vectors is copied from the pinned
 // buffer, counters zeroed.
 int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_t s, Workspace* ws) {
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const size_t slots = 2 * (size_t)cus;  // two workgroups fit a CU's LDS and registers
   std::vector<BatchDesc> descs(items.size());
   bool split = false;
   uint64_t dg_entries = 0;
   size_t nwork = 0;
+  uint64_t keys = 0;
+  size_t ntiles = 0;
+  for (const drtopk_problem_t* q : items) keys += q->n;
+  // Whole in one workgroup, in one pass, where that is no more than a slot's
+  // share of all keys (4096 problems of 2^10 to 2^20 keys, k <= 2048: 533 us, the
+  // larger ones split 690; 600 of 2^19: 297 / 359).  Larger ones are split, and
+  // when their tiles alone are more than two rounds of the slots, so are all that can be (1500
+  // problems of 2^10 to 2^22: 677 us, the smaller ones whole 757).
   for (size_t i = 0; i < items.size(); ++i) {
     descs[i] = make_desc(*items[i]);
-    descs[i].tiles = batched_tiles(descs[i]);
+    descs[i].tiles = descs[i].n * slots <= keys ? 1 : batched_tiles(descs[i]);
+    if (descs[i].tiles > 1) ntiles += descs[i].tiles;
+  }
+  const bool claim = ntiles > 2 * slots;
+  for (size_t i = 0; i < items.size(); ++i) {
+    if (claim) descs[i].tiles = batched_tiles(descs[i]);
     if (descs[i].tiles > 1) {
       split = true;
       descs[i].doff = dg_entries;
@@ -638,7 +654,7 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
   if (items.size() <= kBInline && !split) {  // descriptors as kernel arguments
     BatchInline b{};
     for (size_t i = 0; i < items.size(); ++i) b.d[i] = descs[i];
-    hipLaunchKernelGGL(k_batched_inline, dim3((unsigned)items.size()), dim3(kBT), 0, s, b, ws->rec);
+    hipLaunchKernelGGL(k_batched_inline, dim3((unsigned)items.size()), dim3(kBT), 0, s, b);
     return hipGetLastError() == hipSuccess ? (int)DRTOPK_OK : (int)DRTOPK_EDEVICE;
   }
   const size_t off_desc = 64;
@@ -660,15 +676,16 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
   if (hipMemcpyAsync(ws->bdev, ws->bhost, need, hipMemcpyHostToDevice, s) != hipSuccess) return DRTOPK_EDEVICE;
   if (hipEventRecord(ws->bev, s) != hipSuccess) return DRTOPK_EDEVICE;
   ws->bev_pending = true;
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const size_t slots = 2 * (size_t)cus;  // two workgroups fit a CU's LDS and registers
-  const unsigned grid = (unsigned)(nwork < slots ? nwork : slots);
   char* dv = static_cast<char*>(ws->bdev);
-  hipLaunchKernelGGL(k_batched, dim3(grid), dim3(kBT), 0, s, reinterpret_cast<const BatchDesc*>(dv + off_desc),
-                     reinterpret_cast<const uint32_t*>(dv + off_items), (uint32_t)nwork,
-                     reinterpret_cast<uint32_t*>(dv), reinterpret_cast<uint32_t*>(dv + off_arrive),
-                     reinterpret_cast<uint64_t*>(dv + off_dg), ws->rec);
+  const BatchDesc* dd = reinterpret_cast<const BatchDesc*>(dv + off_desc);
+  const uint32_t* di = reinterpret_cast<const uint32_t*>(dv + off_items);
+  uint32_t* da = reinterpret_cast<uint32_t*>(dv + off_arrive);
+  uint64_t* dg = reinterpret_cast<uint64_t*>(dv + off_dg);
+  if (claim)
+    hipLaunchKernelGGL(k_batched_split, dim3((unsigned)(nwork < slots ? nwork : slots)), dim3(kBT), 0, s, dd, di,
+                       (uint32_t)nwork, reinterpret_cast<uint32_t*>(dv), da, dg, ws->rec);
+  else
+    hipLaunchKernelGGL(k_batched, dim3((unsigned)nwork), dim3(kBT), 0, s, dd, di, da, dg, ws->rec);
   if (hipGetLastError() != hipSuccess) return DRTOPK_EDEVICE;
   return DRTOPK_OK;
 }
