@@ -2,8 +2,8 @@
 //
 // A workgroup (kBT threads, two share a CU, so one streams keys while the other
 // sorts) takes one problem:
-//   of at most kBSmallN keys: selected in LDS directly (the k-th by radix
-//     select, then the k at or above it sorted);
+//   of at most kBSmallN keys: sorted in LDS, or selected first (the k-th by
+//     radix select, then the k at or above it sorted; see b_whole);
 //   of more: one pass over its keys (b_stream).
 // Problems of more than a slot's share of the batch's keys are split, and run
 // the delegate method over several workgroups:
@@ -31,6 +31,7 @@ namespace drtopk {
 constexpr int kBT = 512;                  // threads per workgroup (two workgroups per CU)
 constexpr int kBWaves = kBT / 64;
 constexpr uint32_t kBSmallN = 4096;       // problems this small are selected in LDS directly
+constexpr uint32_t kBShortN = 1024;       // problems this small are sorted whole, whatever k
 constexpr uint32_t kBMaxS = 4096;         // delegate vector capacity (LDS)
 constexpr uint32_t kBMaxSG = 32768;       // delegate vector of a split problem (global memory)
 constexpr uint32_t kBSurv = 4096;         // survivor capacity (LDS)
@@ -1065,22 +1066,11 @@ __device__ __forceinline__ uint64_t b_stream_sample(const uint32_t* keys, uint32
   return b_stream_cut(sm, S, r < S ? r : S, r / 8, 0, ((uint64_t)0xFFFFFFFFu << L) | posmask);
 }
 
-__device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm) {
-  constexpr int E = kBStreamCap / kBT;
-  const uint32_t n = (uint32_t)d.n, k = d.k;
-  const Codec cx = codec_of(d.dtype);
-  const int L = 32 - __clz((int)(n - 1));
-  const uint32_t posmask = (1u << L) - 1;
-  const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
-  const uint64_t cut = n <= kBStreamCap ? 0 : b_stream_sample(d.keys, n, k, cx, L, posmask, sm);
-  if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm);
-  else b_stream_keys<false>(d.keys, n, k, cx, L, posmask, cut, sm);
-  const uint32_t N = b_stream_gather(sm);
-  uint64_t c[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (e * kBT + threadIdx.x < N) c[e] = sm.buf[e * kBT + threadIdx.x];
-  __syncthreads();
+// Sorts the N composites in c and writes the first k.
+template <int E>
+__device__ __forceinline__ void b_stream_write(const BatchDesc& d, uint64_t (&c)[E], uint32_t N, Codec cx, int L,
+                                               uint32_t posmask, BStreamSmem& sm) {
+  const uint32_t k = d.k;
   ssort<uint64_t, kBStreamCap, kBT, E>(sm, c, N, k, [&](uint32_t r, uint64_t x) {
     if (r >= k) return;
     const uint32_t val = cx.dec((uint32_t)(x >> L));
@@ -1090,6 +1080,35 @@ __device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm) {
   });
 }
 
+__device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm) {
+  const uint32_t n = (uint32_t)d.n, k = d.k;
+  const Codec cx = codec_of(d.dtype);
+  const int L = n > 1 ? 32 - __clz((int)(n - 1)) : 1;
+  const uint32_t posmask = (1u << L) - 1;
+  if (n <= kBSmallN) {  // all of them
+    constexpr int E = kBSmallN / kBT;
+    uint64_t c[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint32_t p = e * kBT + threadIdx.x;
+      if (p < n) c[e] = scomp<uint32_t>(cx.enc(d.keys[p]), p, L, posmask);
+    }
+    b_stream_write<E>(d, c, n, cx, L, posmask, sm);
+    return;
+  }
+  const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
+  const uint64_t cut = n <= kBStreamCap ? 0 : b_stream_sample(d.keys, n, k, cx, L, posmask, sm);
+  if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm);
+  else b_stream_keys<false>(d.keys, n, k, cx, L, posmask, cut, sm);
+  const uint32_t N = b_stream_gather(sm);
+  constexpr int E = kBStreamCap / kBT;
+  uint64_t c[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (e * kBT + threadIdx.x < N) c[e] = sm.buf[e * kBT + threadIdx.x];
+  __syncthreads();
+  b_stream_write<E>(d, c, N, cx, L, posmask, sm);
+}
 
 // LDS of a workgroup.
 union BatchLds {
@@ -1160,9 +1179,13 @@ __device__ inline void b_problem(const BatchDesc& d, BatchSmem& sm, uint32_t* re
   else b_problem_v<false>(d, sm, rec);
 }
 
-// One problem of a batch in one pass.
+// One problem of a batch.  Up to kBSmallN keys are sorted whole where few are
+// wanted or there are few (us a call: 30 problems of 64..4000 keys, k <= 64, 8.2
+// against 10.2 by a select first; of 64..500, k <= 100, 6.5 / 8.6); most of
+// more (float keys of both signs crowd the sort's bins) are selected first and
+// sorted by a network (4096 of 2000..4096, k <= 2048: 207 / 211).
 __device__ __forceinline__ void b_whole(const BatchDesc& d, BatchLds& lds) {
-  if (d.n > kBSmallN) b_stream(d, lds.s);
+  if (d.n > kBSmallN || d.n <= kBShortN || (uint64_t)d.k * 8 <= d.n) b_stream(d, lds.s);
   else if ((reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0) b_small<true>(d, lds.b);
   else b_small<false>(d, lds.b);
 }

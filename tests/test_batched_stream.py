@@ -31,8 +31,9 @@ def run(hosts, largest, repeat=1):
             check_exact(x, k, dt, to_np(b.values(j)), to_np(b.indices(j)), tag, largest=largest)
 
 
-# below and at the LDS's capacity, chunk remainders, the samples' limits
-SIZES = [(4097, 1), (4097, 2048), (7680, 2048), (7681, 2048), (7681, 1), (8192 + 5, 700), (65537, 2047), (131071, 2048),
+# sorted whole or selected first; below and at the LDS's capacity, chunk remainders, the samples' limits
+SIZES = [(1, 1), (2, 2), (511, 511), (1024, 1024), (1025, 128), (1025, 129), (4096, 512), (4096, 513),
+         (4097, 1), (4097, 2048), (7680, 2048), (7681, 2048), (7681, 1), (8192 + 5, 700), (65537, 2047), (131071, 2048),
          (131072, 2048), (200003, 33)]
 
 
@@ -51,7 +52,7 @@ def test_against_oracle(kind, largest):
         else:
             x, dt = synth.keys(kind, n, n + k)
         hosts.append((x, dt, k, j % 4))
-    run(hosts[:5], largest)           # descriptors as arguments
+    run(hosts[:13], largest)          # descriptors as arguments
     run(hosts, largest, repeat=8)     # staged descriptors
 
 
