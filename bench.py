@@ -7,8 +7,9 @@ normal through the order-preserving uint32 encoding) and for each
 k in {1, 1024, 131072}: six topk_select calls, sorted values + positions.
 
 Reported: keys/s over the whole step (value), HBM GB/s of the mandatory read
-(4 bytes per key), per-case timings, the roofline of the dominant kernel (the
-delegate pass, timed live with HIP events on its own stream), and the CPU
+(4 bytes per key), per-case timings, the roofline of the dominant pass (the one
+that streams all keys: the delegate pass at k = 1, else the sample and the filter,
+timed live with HIP events on its own stream), and the CPU
 oracle on a bounded sample of the same workload, and a probe kernel's read
 bandwidth with the delegate pass's access pattern.  Beside the step, outside
 its timed region:
@@ -118,8 +119,8 @@ def bench_batched(drt, synth, torch, args):
         drt.topk_select(t, k, v, ix)
     torch.cuda.synchronize()
     ms_loop = (time.perf_counter() - t0) * 1e3
-    # the method's re-read per problem on the delegate route (route 2), not counted as useful
-    # bytes: beta 1 re-reads exactly the k - 1 subranges whose delegate ranks above t; beta 2
+    # the delegate method's re-read per problem by its plan (route 2; a problem that one
+    # workgroup takes whole runs in one pass and re-reads nothing): beta 1 re-reads exactly the k - 1 subranges whose delegate ranks above t; beta 2
     # at most (k - 1) / 2 subranges (those whose second delegate does), counted at that bound
     reread = 0
     routes = {1: 0, 2: 0, 3: 0}
@@ -442,7 +443,8 @@ def main() -> int:
     def call(c):
         drt.topk_select(c["keys"], c["k"], c["vals"], c["idx"], stream=stream)
 
-    # plan / counters of each case (outside the timed region)
+    # plan / counters of each case (outside the timed region; calls with counters run the
+    # delegate method, the timed ones the sampled path at k > 1)
     for c in cases:
         _, _, st = drt.topk_select(c["keys"], c["k"], c["vals"], c["idx"], stats=True, stream=stream)
         c.update(alpha=st.alpha, beta=st.beta, scanned=int(st.scanned), candidates=int(st.candidates),
@@ -560,7 +562,8 @@ def main() -> int:
         "hbm_GBps_mandatory_read": 4.0 * keys_per_step / step_s / 1e9,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_delegate (delegate pass, 4 B/key read once)",
+                     "kernel": "the pass over all keys, 4 B/key read once (k_delegate at k = 1; "
+                               "k_sgather, k_srank, k_sfilter at larger k)",
                      "avg_launch_us": del_avg_s * 1e6, "launches": calls,
                      "rest_of_path_avg_us": tail_ms / calls * 1e3,
                      "probe_read_GBps": probe_GBps, "frac_of_probe": achieved / probe_GBps},
