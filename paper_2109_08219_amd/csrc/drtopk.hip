@@ -641,7 +641,8 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
     descs[i].tiles = descs[i].n * slots <= keys ? 1 : batched_tiles(descs[i]);
     if (descs[i].tiles > 1) ntiles += descs[i].tiles;
   }
-  const bool claim = ntiles > 2 * slots;
+  // (a grid holds fewer than 2^32 threads)
+  const bool claim = ntiles > 2 * slots || items.size() > (size_t(1) << 22);
   for (size_t i = 0; i < items.size(); ++i) {
     if (claim) descs[i].tiles = batched_tiles(descs[i]);
     if (descs[i].tiles > 1) {
