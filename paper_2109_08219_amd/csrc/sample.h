@@ -1279,9 +1279,7 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
         __syncthreads();
         const uint32_t fit = sm.misc[3];
         __syncthreads();
-        const C width = (C)(fit ? fit : 1u) << sh;  // composites of the kept bins
-        const bool all = mx - mn < width;
-        cut = all ? mn : mx - (width - 1);
+        cut = leading_bins_cut<C>(mx, mn, fit ? fit : 1u, sh);
         if (fit || sh == 0) break;
         mn = cut;  // the first bin alone is too large: look inside it
       }

@@ -79,4 +79,13 @@ __host__ __device__ inline void sample_buckets(double gap, uint32_t target, uint
   w->B = (span + s - 1) / s;
 }
 
+// The lowest composite of the first `bins` of at most 2048 bins of 2^sh
+// composites each, from mx down to mn.  All of them can span the whole of C
+// (64-bit composites of more than 2^31 keys), whose number of composites C does
+// not hold.
+template <typename C>
+__host__ __device__ inline C leading_bins_cut(C mx, C mn, uint32_t bins, int sh) {
+  return (mx - mn) >> sh < (C)bins ? mn : mx - (((C)bins << sh) - 1);
+}
+
 }  // namespace drtopk
