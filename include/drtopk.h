@@ -402,6 +402,14 @@ int drtopk_check(void* stream, uint32_t* flags);
  * Process-wide; not for production use. */
 int drtopk_set_survivor_cap(uint64_t cap);
 
+/* Testing hook for the error path of the sampled path (see topk_select): what
+ * an input that the sample misjudges, or a bucket larger than a workgroup, has
+ * collected at a time is capped at `cap` keys for calls made after it; 0 restores
+ * the workgroup's capacity.  With a cap below what a call needs, writes past it
+ * are dropped, flags 16 and 2 raised, and every kernel exits normally.
+ * Process-wide; not for production use. */
+int drtopk_set_run_cap(uint32_t cap);
+
 /* Human-readable name of a status code (static string). */
 const char* drtopk_status_string(int status);
 

@@ -120,6 +120,7 @@ def lib() -> ctypes.CDLL:
             "drtopk_server_destroy": [vp],
             "drtopk_check": [vp, ctypes.POINTER(u32)],
             "drtopk_set_survivor_cap": [u64],
+            "drtopk_set_run_cap": [u32],
         }
         for name, args in sig.items():
             f = getattr(L, name)
@@ -213,6 +214,12 @@ check = check_stream
 def set_survivor_cap(cap: int) -> None:
     """Testing hook: caps the delegate method's survivor buffers (0 = planner's bound)."""
     _check(lib().drtopk_set_survivor_cap(int(cap)), "drtopk_set_survivor_cap")
+
+
+def set_run_cap(cap: int) -> None:
+    """Testing hook: caps what the sampled path collects at a time where a sample misjudges the
+    keys or a bucket is larger than a workgroup (0 = the workgroup's capacity)."""
+    _check(lib().drtopk_set_run_cap(int(cap)), "drtopk_set_run_cap")
 
 
 def topk_select(keys, k: int, out_vals=None, out_idx=None, *, dtype=None, largest: bool = True, alpha=None,

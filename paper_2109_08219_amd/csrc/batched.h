@@ -857,11 +857,15 @@ struct BStreamSmem : SSortShared<uint64_t, kBStreamCap, kBT> {
 // A composite that at least k and at most k + slack of the N in sm.buf reach
 // (those above `hi` or below `lo` are not looked at; every thread calls).
 __device__ __forceinline__ uint64_t b_stream_cut(BStreamSmem& sm, uint32_t N, uint32_t k, uint32_t slack, uint64_t lo,
-                                                 uint64_t hi) {
+                                                 uint64_t hi, uint32_t* rec) {
   uint32_t above = 0;  // elements above hi
   for (;;) {
     const int sh = sbucket_hist<uint64_t, kBStreamCap, kBT>(sm, N, lo, hi, [&](uint64_t i) { return sm.buf[i]; });
     const uint32_t need = k - above;
+    if (sm.hist[kSBins] < need) {  // no bin holds the rank (uniform)
+      if (threadIdx.x == 0) record_err(rec, ERR_SELECT);
+      return suniform(lo);
+    }
     for (uint32_t b = threadIdx.x; b < (uint32_t)kSBins; b += kBT)
       if (sm.hist[b] < need && need <= sm.hist[b + 1]) sm.misc[2] = b;
     __syncthreads();
@@ -899,11 +903,12 @@ __device__ __forceinline__ uint32_t b_stream_gather(BStreamSmem& sm) {
 // Raises the cut to one that the elements held leave k of, and at most
 // kBStreamSlack more, drops those under it and deals the rest to the regions.
 // Returns the new cut.
-__device__ __forceinline__ uint64_t b_stream_raise(BStreamSmem& sm, uint32_t k, uint64_t cut, uint64_t top) {
+__device__ __forceinline__ uint64_t b_stream_raise(BStreamSmem& sm, uint32_t k, uint64_t cut, uint64_t top,
+                                                   uint32_t* rec) {
   constexpr int E = kBStreamCap / kBT;
   const uint32_t N = b_stream_gather(sm);
   // few held in all, but unevenly: dealing them out makes the room
-  const uint64_t lo = N > k + kBStreamSlack ? b_stream_cut(sm, N, k, kBStreamSlack, cut, top) : cut;
+  const uint64_t lo = N > k + kBStreamSlack ? b_stream_cut(sm, N, k, kBStreamSlack, cut, top, rec) : cut;
   uint64_t c[E];
   uint32_t mine = 0;
 #pragma unroll
@@ -932,7 +937,7 @@ __device__ __forceinline__ uint64_t b_stream_raise(BStreamSmem& sm, uint32_t k, 
 // same number of times.
 template <bool VEC>
 __device__ __forceinline__ void b_stream_keys(const uint32_t* keys, uint32_t n, uint32_t k, Codec cx, int L,
-                                              uint32_t posmask, uint64_t cut, BStreamSmem& sm) {
+                                              uint32_t posmask, uint64_t cut, BStreamSmem& sm, uint32_t* rec) {
   constexpr int U = kBChunk / 256;
   const uint32_t n4 = vec_end<VEC>(n);
   const Keys<VEC> ks(keys, n4);
@@ -1022,12 +1027,16 @@ __device__ __forceinline__ void b_stream_keys(const uint32_t* keys, uint32_t n, 
       uint32_t N = 0;
       for (uint32_t w = 0; w < (uint32_t)kBWaves; ++w) N += sm.fill[w];
       if (N >= k) return;
+      if (cut == 0) {  // uniform
+        if (threadIdx.x == 0) record_err(rec, ERR_FEW);
+        return;
+      }
       cut = 0;  // the sample misjudged the keys: once more without it
       __syncthreads();
       begin();
       continue;
     }
-    cut = b_stream_raise(sm, k, cut, ((uint64_t)0xFFFFFFFFu << L) | posmask);
+    cut = b_stream_raise(sm, k, cut, ((uint64_t)0xFFFFFFFFu << L) | posmask, rec);
     fill = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.fill[wave]);
     tkey = (uint32_t)(cut >> L);
     tpos = posmask - ((uint32_t)cut & posmask);
@@ -1041,7 +1050,7 @@ __device__ __forceinline__ void b_stream_keys(const uint32_t* keys, uint32_t n, 
 // as of the k largest, and four and a half standard deviations more.  Fewer
 // than k above it means a second pass, so no more margin is needed.
 __device__ __forceinline__ uint64_t b_stream_sample(const uint32_t* keys, uint32_t n, uint32_t k, Codec cx, int L,
-                                                    uint32_t posmask, BStreamSmem& sm) {
+                                                    uint32_t posmask, BStreamSmem& sm, uint32_t* rec) {
   const int loads = n < (1u << 17) ? 1 : 3;
   const Keys<false> ks(keys, n);
   uint32_t x[3][4], p[3];
@@ -1063,7 +1072,7 @@ __device__ __forceinline__ uint64_t b_stream_sample(const uint32_t* keys, uint32
   const uint32_t S = loads * 4 * kBT;
   const float lam = (float)k * (float)S / (float)n;
   const uint32_t r = (uint32_t)(lam + 4.5f * sqrtf(lam) + 6.0f);
-  return b_stream_cut(sm, S, r < S ? r : S, r / 8, 0, ((uint64_t)0xFFFFFFFFu << L) | posmask);
+  return b_stream_cut(sm, S, r < S ? r : S, r / 8, 0, ((uint64_t)0xFFFFFFFFu << L) | posmask, rec);
 }
 
 // Sorts the N composites in c and writes the first k.
@@ -1080,7 +1089,7 @@ __device__ __forceinline__ void b_stream_write(const BatchDesc& d, uint64_t (&c)
   });
 }
 
-__device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm) {
+__device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm, uint32_t* rec) {
   const uint32_t n = (uint32_t)d.n, k = d.k;
   const Codec cx = codec_of(d.dtype);
   const int L = n > 1 ? 32 - __clz((int)(n - 1)) : 1;
@@ -1097,9 +1106,9 @@ __device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm) {
     return;
   }
   const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
-  const uint64_t cut = n <= kBStreamCap ? 0 : b_stream_sample(d.keys, n, k, cx, L, posmask, sm);
-  if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm);
-  else b_stream_keys<false>(d.keys, n, k, cx, L, posmask, cut, sm);
+  const uint64_t cut = n <= kBStreamCap ? 0 : b_stream_sample(d.keys, n, k, cx, L, posmask, sm, rec);
+  if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm, rec);
+  else b_stream_keys<false>(d.keys, n, k, cx, L, posmask, cut, sm, rec);
   const uint32_t N = b_stream_gather(sm);
   constexpr int E = kBStreamCap / kBT;
   uint64_t c[E];
@@ -1184,8 +1193,8 @@ __device__ inline void b_problem(const BatchDesc& d, BatchSmem& sm, uint32_t* re
 // against 10.2 by a select first; of 64..500, k <= 100, 6.5 / 8.6); most of
 // more (float keys of both signs crowd the sort's bins) are selected first and
 // sorted by a network (4096 of 2000..4096, k <= 2048: 207 / 211).
-__device__ __forceinline__ void b_whole(const BatchDesc& d, BatchLds& lds) {
-  if (d.n > kBSmallN || d.n <= kBShortN || (uint64_t)d.k * 8 <= d.n) b_stream(d, lds.s);
+__device__ __forceinline__ void b_whole(const BatchDesc& d, BatchLds& lds, uint32_t* rec) {
+  if (d.n > kBSmallN || d.n <= kBShortN || (uint64_t)d.k * 8 <= d.n) b_stream(d, lds.s, rec);
   else if ((reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0) b_small<true>(d, lds.b);
   else b_small<false>(d, lds.b);
 }
@@ -1219,7 +1228,7 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k
   const uint32_t i = it >> 8;
   const BatchDesc d = descs[i];
   if (d.tiles > 1) b_tile_any(d, it & 0xFFu, &arrive[i], Dg, lds.b, rec);
-  else b_whole(d, lds);
+  else b_whole(d, lds, rec);
 }
 
 // Items claimed from *counter (starts at 0), any grid size: for more tiles of
@@ -1251,10 +1260,10 @@ constexpr uint32_t kBInline = 32;
 struct BatchInline {
   BatchDesc d[kBInline];
 };
-__global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched_inline(BatchInline b) {
+__global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched_inline(BatchInline b, uint32_t* rec) {
   __shared__ BatchLds lds;
   const BatchDesc d = b.d[blockIdx.x];
-  b_whole(d, lds);
+  b_whole(d, lds, rec);
 }
 
 // One problem, descriptor by value: the single-problem path for small inputs.

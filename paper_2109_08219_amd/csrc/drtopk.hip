@@ -77,6 +77,10 @@ bool valid_beta(int b) { return b == 1 || b == 2 || b == 4 || b == 8; }
 // planner's bound).  A smaller cap makes the kernels drop writes and flag it.
 std::atomic<uint64_t> g_cap_override{0};
 
+// Testing hook: elements that a run or a fallback of the sampled path collects
+// (0 = the workgroup's capacity).
+std::atomic<uint32_t> g_run_cap{0};
+
 int floor_log2(uint64_t x) { return 63 - __builtin_clzll(x); }
 
 // Autotuner table: measured (alpha, beta) per (form, floor log2 n, floor log2 k).
@@ -414,6 +418,11 @@ bool take_sampled(const SPlan& sp, size_t total) {
          g_cap_override.load(std::memory_order_relaxed) == 0;
 }
 
+// The testing hook's cap, where it is set.
+void hook_run_cap(SPlan& sp) {
+  if (const uint32_t cap = g_run_cap.load(std::memory_order_relaxed)) sp.hold = cap;
+}
+
 // The sampled path's plan of a call; not on if it does not take the call.
 // `other()` gives the other path's workspace, asked for only when it decides.
 template <typename F>
@@ -423,22 +432,39 @@ SPlan sampled_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth
   sample_plan(keys, n, k, dtype, kth_only, &sp);
   sp.on = take_sampled(sp, sp.on && sp.total > kSampledFree ? other() : 0);
   sp.pay = pay;
+  hook_run_cap(sp);
   return sp;
 }
 
-// Enqueues a call that the sampled path takes.  One workgroup needs no
-// workspace, so such a call touches no shared state.
+// The check record for a call that needs nothing else of its stream's entry.
+// Nothing is allocated under capture: without a record yet, such a call runs
+// without one.
+uint32_t* light_record(Workspace* ws, hipStream_t s) {
+  std::lock_guard<std::mutex> g(ws->mu);
+  if (!ws->rec) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess)
+      (void)hipGetLastError();
+    else if (cap == hipStreamCaptureStatusNone)
+      (void)ensure_record(ws);
+  }
+  return ws->rec;
+}
+
+// Enqueues a call that the sampled path takes.  One workgroup needs no workspace.
 int run_sampled(const SPlan& sp, const void* keys, void* out_vals, uint32_t* out_idx, void* out_kth, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (sp.one) return sample_enqueue(sp, keys, nullptr, out_vals, out_idx, out_kth, s, false);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return DRTOPK_EDEVICE;
   Workspace* ws = workspace_entry(dev, stream);
   if (!ws) return DRTOPK_ENOMEM;
+  if (sp.one) return sample_enqueue(sp, keys, nullptr, light_record(ws, s), out_vals, out_idx, out_kth, s, false);
   std::lock_guard<std::mutex> g(ws->mu);
-  const int st = ensure_bytes(ws, sp.total);
+  int st = ensure_record(ws);
   if (st) return st;
-  return sample_enqueue(sp, keys, ws->ptr, out_vals, out_idx, out_kth, s, !sp.wide);
+  st = ensure_bytes(ws, sp.total);
+  if (st) return st;
+  return sample_enqueue(sp, keys, ws->ptr, ws->rec, out_vals, out_idx, out_kth, s, !sp.wide);
 }
 
 // Workspace of a call: the larger of the sampled path's, where it is taken,
@@ -655,7 +681,7 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
   if (items.size() <= kBInline && !split) {  // descriptors as kernel arguments
     BatchInline b{};
     for (size_t i = 0; i < items.size(); ++i) b.d[i] = descs[i];
-    hipLaunchKernelGGL(k_batched_inline, dim3((unsigned)items.size()), dim3(kBT), 0, s, b);
+    hipLaunchKernelGGL(k_batched_inline, dim3((unsigned)items.size()), dim3(kBT), 0, s, b, ws->rec);
     return hipGetLastError() == hipSuccess ? (int)DRTOPK_OK : (int)DRTOPK_EDEVICE;
   }
   const size_t off_desc = 64;
@@ -870,8 +896,9 @@ int topk_select_noalloc(const void* keys, uint64_t n, uint32_t k, int dtype, voi
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     SPlan sp;
     sample_plan(keys, n, k, dtype, false, &sp);
+    hook_run_cap(sp);
     if (take_sampled(sp, wide ? wp.total : p.total))
-      return sample_enqueue(sp, keys, ws, out_vals, out_idx, nullptr, s, false);
+      return sample_enqueue(sp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, s, false);
     if (wide) return wide_enqueue(wp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, false, s);
     p.rec = static_cast<uint32_t*>(base);
     p.marks = false;  // no timing events
@@ -1330,6 +1357,11 @@ int drtopk_check(void* stream, uint32_t* flags) {
 
 int drtopk_set_survivor_cap(uint64_t cap) {
   g_cap_override.store(cap, std::memory_order_relaxed);
+  return DRTOPK_OK;
+}
+
+int drtopk_set_run_cap(uint32_t cap) {
+  g_run_cap.store(cap, std::memory_order_relaxed);
   return DRTOPK_OK;
 }
 

@@ -1102,22 +1102,34 @@ __device__ __forceinline__ void sbucket_each(uint64_t count, G&& get, F&& f) {
   for (; i < count; i += T) f(get(i));
 }
 
-// Collects the elements get(i), i < count, lying in [lo, hi] (N of them, at
+// Internal checks of the sampled path: `rec` is the stream's check record
+// (nullptr: none), `hold` the most elements that a run or a fallback collects
+// (the LDS's capacity; less only through the testing hook drtopk_set_run_cap).
+struct SCheck {
+  uint32_t* rec;
+  uint32_t hold;
+};
+
+// Collects the elements get(i), i < count, lying in [lo, hi] (`want` of them, at
 // most CAP, known to the caller) into registers in sort order's layout.
 template <typename C, uint32_t CAP, int T, int E, typename G>
-__device__ __forceinline__ uint32_t sbucket_collect(SSortShared<C, CAP, T>& sm, C (&c)[E],
-                                                    uint64_t count, C lo,
-                                                    C hi, G&& get) {
+__device__ __forceinline__ uint32_t sbucket_collect(SSortShared<C, CAP, T>& sm, C (&c)[E], uint64_t count, C lo,
+                                                    C hi, uint32_t want, const SCheck& ck, G&& get) {
+  const uint32_t hold = ck.hold < CAP ? ck.hold : CAP;
   if (threadIdx.x == 0) sm.misc[1] = 0;
   __syncthreads();
   sbucket_each<C, T>(count, get, [&](C x) {
     if (x >= lo && x <= hi) {
       const uint32_t s = atomicAdd(&sm.misc[1], 1u);
-      if (s < CAP) sm.buf[s] = x;
+      if (s < hold) sm.buf[s] = x;
     }
   });
   __syncthreads();
-  const uint32_t N = sm.misc[1] < CAP ? sm.misc[1] : CAP;
+  const uint32_t got = sm.misc[1], N = got < hold ? got : hold;
+  if (threadIdx.x == 0) {
+    if (got > hold) record_err(ck.rec, ERR_CAP);
+    if (N < want) record_err(ck.rec, ERR_FEW);
+  }
 #pragma unroll
   for (int e = 0; e < E; ++e)
     if (e * T + threadIdx.x < N) c[e] = sm.buf[e * T + threadIdx.x];
@@ -1160,11 +1172,14 @@ __device__ __forceinline__ int sbucket_hist(SSortShared<C, CAP, T>& sm, uint64_t
 // The element of 1-based rank `rank` among get(i), i < count (all distinct, at most `top`).
 template <typename C, uint32_t CAP, int T, typename G>
 __device__ __forceinline__ C sbucket_select(SSortShared<C, CAP, T>& sm, uint64_t count, uint64_t rank, C top,
-                                            G&& get) {
+                                            const SCheck& ck, G&& get) {
   C mn = 0, mx = top;
   for (;;) {
     const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
-    if (threadIdx.x == 0) sm.misc[2] = 0;
+    if (threadIdx.x == 0) {
+      sm.misc[2] = 0;
+      if (rank - 1 >= sm.hist[kSBins]) record_err(ck.rec, ERR_SELECT);  // no bin holds the rank
+    }
     __syncthreads();
     for (uint32_t b = threadIdx.x; b < (uint32_t)kSBins; b += T)
       if (sm.hist[b] < rank && rank <= sm.hist[b + 1]) sm.misc[2] = b;
@@ -1228,14 +1243,14 @@ __device__ __forceinline__ typename STraits<K>::Comp sbucket_get(const SBucketSh
 
 // The rare ways to the output: runs of at most CAP elements, sorted one after
 // the other.  Either the leading bins of what is left of a bucket larger than
-// the LDS (its elements of the source's `count` lie in [low, upto], its first
-// slot is `start`), or (count 0) a rescue: each workgroup answers ranks of its
-// own from the input, independently of the others.
+// the LDS (its `size` elements of the source's `count` lie in [low, upto], its
+// first slot is `start`), or (count 0) a rescue: each workgroup answers ranks of
+// its own from the input, independently of the others.
 template <typename K, SMode MODE>
 __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys, uint64_t n,
-                                             const typename STraits<K>::Comp* cand, uint64_t start, uint32_t count,
-                                             typename STraits<K>::Comp low, typename STraits<K>::Comp upto,
-                                             const SOut<K>& out) {
+                                             const typename STraits<K>::Comp* cand, uint64_t start, uint32_t size,
+                                             uint32_t count, typename STraits<K>::Comp low,
+                                             typename STraits<K>::Comp upto, const SOut<K>& out, const SCheck& ck) {
   typedef typename STraits<K>::Comp C;
   constexpr int T = kSBucketThreads;
   constexpr uint32_t CAP = STraits<K>::kCap;
@@ -1247,7 +1262,8 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
   if (rescue && out.kth_only && blockIdx.x > 0) return;
   uint64_t base = rescue ? (out.kth_only ? (uint64_t)k - 1 : (uint64_t)blockIdx.x * CAP) : start;
   C c[E];
-  while (base < k) {
+  bool more = true;
+  while (more && base < k) {
     uint32_t N;
     uint64_t next;
     if (rescue) {
@@ -1255,8 +1271,9 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
       C bound[2];
 #pragma unroll 1
       for (int s = 0; s < 2; ++s)
-        bound[s] = sbucket_select<C, CAP, T>(sm, n, s ? r1 : base + 1, ((C)(K)~(K)0 << out.L) | out.posmask, input);
-      N = sbucket_collect<C, CAP, T, E>(sm, c, n, bound[1], bound[0], input);
+        bound[s] =
+            sbucket_select<C, CAP, T>(sm, n, s ? r1 : base + 1, ((C)(K)~(K)0 << out.L) | out.posmask, ck, input);
+      N = sbucket_collect<C, CAP, T, E>(sm, c, n, bound[1], bound[0], (uint32_t)(r1 - base), ck, input);
       next = base + (uint64_t)gridDim.x * CAP;
     } else {
       C mn = ~(C)0, mx = 0;
@@ -1269,6 +1286,7 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
       sblock_minmax<C, T>(mx, mn, sm.red);
       if (mx < mn) break;  // nothing is left
       C cut = mn;
+      uint32_t fit;
       for (;;) {
         const int sh = sbucket_hist<C, CAP, T>(sm, count, mn, mx, get);
         // the most leading bins whose elements fit
@@ -1277,20 +1295,23 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
         for (uint32_t i = threadIdx.x; i < (uint32_t)kSBins; i += T)
           if (sm.hist[i + 1] <= CAP && (i + 1 == (uint32_t)kSBins || sm.hist[i + 2] > CAP)) sm.misc[3] = i + 1;
         __syncthreads();
-        const uint32_t fit = sm.misc[3];
+        fit = sm.misc[3];
         __syncthreads();
         cut = leading_bins_cut<C>(mx, mn, fit ? fit : 1u, sh);
         if (fit || sh == 0) break;
         mn = cut;  // the first bin alone is too large: look inside it
       }
-      N = sbucket_collect<C, CAP, T, E>(sm, c, count, cut, mx, get);
+      N = sbucket_collect<C, CAP, T, E>(sm, c, count, cut, mx, sm.hist[fit ? fit : 1u], ck, get);
       if (N == 0) break;
-      next = cut > low ? base + N : k;
+      next = base + N;
+      more = cut > low;
       upto = cut - 1;
     }
     ssort<C, CAP, T, E>(sm, c, N, k - base, [&](uint32_t rk, C x) { out(base + rk, x); });
     base = next;
   }
+  // the runs are the whole bucket, or reach the last slot
+  if (!rescue && base < k && base != start + size && threadIdx.x == 0) record_err(ck.rec, ERR_FEW);
 }
 
 // One workgroup per bucket.  RARE: the rare ways are part of the kernel, which
@@ -1307,7 +1328,7 @@ __global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu
     uint32_t maxrows, const SRow* __restrict__ rows, const uint16_t* __restrict__ offs, uint32_t pitch, uint32_t m,
     SWin win, const typename STraits<K>::Comp* __restrict__ sorted,
     const typename STraits<K>::Comp* __restrict__ bounds, K* __restrict__ out_vals, uint32_t* __restrict__ out_idx,
-    K* __restrict__ out_kth, SPayload pay) {
+    K* __restrict__ out_kth, SPayload pay, SCheck ck) {
   typedef typename STraits<K>::Comp C;
   constexpr int T = kSBucketThreads;
   constexpr uint32_t CAP = STraits<K>::kCap;
@@ -1445,7 +1466,7 @@ __global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu
   }
   if (bad || count > CAP) {
     if constexpr (RARE) {
-      sbucket_rare<K, MODE>(sm, keys, n, cand, start, bad ? 0u : source, low, upto, out);
+      sbucket_rare<K, MODE>(sm, keys, n, cand, start, count, bad ? 0u : source, low, upto, out, ck);
     } else {
       if (threadIdx.x == 0) ctl->rare = 1;
     }
@@ -1472,7 +1493,8 @@ struct SOne {
 template <typename K, int T>
 __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t n, uint32_t k, uint32_t r,
                                             int kth_only, SCodec<K> cd, int L, K* __restrict__ out_vals,
-                                            uint32_t* __restrict__ out_idx, K* __restrict__ out_kth, SPayload pay) {
+                                            uint32_t* __restrict__ out_idx, K* __restrict__ out_kth, SPayload pay,
+                                            SCheck ck) {
   typedef typename STraits<K>::Comp C;
   constexpr uint32_t CAP = T == 1024 ? SOne<K>::kCap : 1024;
   constexpr int E = (int)(CAP / T);
@@ -1555,8 +1577,8 @@ __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t
     __syncthreads();
     N = sm.misc[4];
     if (N < k || N > CAP) {
-      const C kth = sbucket_select<C, CAP, T>(sm, n, k, ((C)(K)~(K)0 << L) | posmask, get);
-      N = sbucket_collect<C, CAP, T, E>(sm, c, n, kth, ~(C)0, get);
+      const C kth = sbucket_select<C, CAP, T>(sm, n, k, ((C)(K)~(K)0 << L) | posmask, ck, get);
+      N = sbucket_collect<C, CAP, T, E>(sm, c, n, kth, ~(C)0, k, ck, get);
     } else {
 #pragma unroll
       for (int e = 0; e < E; ++e)

@@ -136,22 +136,23 @@ bool one_fits(uint64_t n, uint32_t k, uint32_t* r) {
 }
 
 template <typename K>
-void enqueue_one(const SPlan& p, const void* keys_v, K* out_vals, uint32_t* out_idx, K* out_kth, hipStream_t s) {
+void enqueue_one(const SPlan& p, const void* keys_v, K* out_vals, uint32_t* out_idx, K* out_kth, SCheck ck,
+                 hipStream_t s) {
   const K* keys = static_cast<const K*>(keys_v);
   const SCodec<K> cd{(K)p.codec_a, (K)p.codec_c};
   const uint32_t n = (uint32_t)p.n;
   const int kth = p.kth_only ? 1 : 0;
   if (n <= 1024)
     hipLaunchKernelGGL((k_sone<K, 256>), dim3(1), dim3(256), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, out_idx,
-                       out_kth, p.pay);
+                       out_kth, p.pay, ck);
   else
     hipLaunchKernelGGL((k_sone<K, 1024>), dim3(1), dim3(1024), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, out_idx,
-                       out_kth, p.pay);
+                       out_kth, p.pay, ck);
 }
 
 template <typename K>
 void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint32_t* out_idx, K* out_kth,
-                 hipStream_t s, PhaseMarks& pm) {
+                 SCheck ck, hipStream_t s, PhaseMarks& pm) {
   typedef STraits<K> T;
   typedef typename T::Comp C;
   const K* keys = static_cast<const K*>(keys_v);
@@ -209,7 +210,7 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
 #define DRTOPK_BUCKET(MODE, RARE, GRID, SECOND)                                                                    \
   hipLaunchKernelGGL((k_sbucket<K, MODE, RARE>), dim3(GRID), dim3(kSBucketThreads), 0, s, keys, p.n, p.k, kth,     \
                      p.levels, SECOND, cd, p.L, ctl, cand, p.cap1, p.cap, p.rows, rows, offs, p.pitch, p.m, p.win,   \
-                     sorted, bounds, out_vals, out_idx, out_kth, p.pay)
+                     sorted, bounds, out_vals, out_idx, out_kth, p.pay, ck)
   if (p.plain && p.bmax == 1) {
     DRTOPK_BUCKET(kSPlain, true, 1, 0);
   } else if (p.plain) {
@@ -259,23 +260,24 @@ void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_o
   *out = p;
 }
 
-int sample_enqueue(const SPlan& p, const void* keys, void* ws, void* out_vals, uint32_t* out_idx, void* out_kth,
-                   hipStream_t s, bool marks) {
+int sample_enqueue(const SPlan& p, const void* keys, void* ws, uint32_t* rec, void* out_vals, uint32_t* out_idx,
+                   void* out_kth, hipStream_t s, bool marks) {
+  const SCheck ck{rec, p.hold};
   if (p.one) {
     if (p.wide)
-      enqueue_one<uint64_t>(p, keys, static_cast<uint64_t*>(out_vals), out_idx, static_cast<uint64_t*>(out_kth), s);
+      enqueue_one<uint64_t>(p, keys, static_cast<uint64_t*>(out_vals), out_idx, static_cast<uint64_t*>(out_kth), ck, s);
     else
-      enqueue_one<uint32_t>(p, keys, static_cast<uint32_t*>(out_vals), out_idx, static_cast<uint32_t*>(out_kth), s);
+      enqueue_one<uint32_t>(p, keys, static_cast<uint32_t*>(out_vals), out_idx, static_cast<uint32_t*>(out_kth), ck, s);
     return hipGetLastError() == hipSuccess ? (int)DRTOPK_OK : (int)DRTOPK_EDEVICE;
   }
   PhaseMarks pm;
   if (marks) pm.begin(s);
   if (p.wide)
-    enqueue_for<uint64_t>(p, keys, ws, static_cast<uint64_t*>(out_vals), out_idx, static_cast<uint64_t*>(out_kth), s,
-                          pm);
+    enqueue_for<uint64_t>(p, keys, ws, static_cast<uint64_t*>(out_vals), out_idx, static_cast<uint64_t*>(out_kth), ck,
+                          s, pm);
   else
-    enqueue_for<uint32_t>(p, keys, ws, static_cast<uint32_t*>(out_vals), out_idx, static_cast<uint32_t*>(out_kth), s,
-                          pm);
+    enqueue_for<uint32_t>(p, keys, ws, static_cast<uint32_t*>(out_vals), out_idx, static_cast<uint32_t*>(out_kth), ck,
+                          s, pm);
   pm.end(s);
   return hipGetLastError() == hipSuccess ? (int)DRTOPK_OK : (int)DRTOPK_EDEVICE;
 }

@@ -19,6 +19,7 @@ struct SPlan {
   uint32_t head = 0;      // keys before the first 16-byte boundary
   bool kth_only = false;
   SPayload pay = {};      // set by the caller
+  uint32_t hold = ~0u;    // most elements that a run or a fallback collects (below the LDS's capacity: testing hook)
   bool one = false;       // one workgroup takes the whole problem
   int levels = 1;         // 2: the first filter's candidates are sampled and partitioned again
   int plain = 0;          // the candidates are one list, not grouped by bucket
@@ -40,8 +41,9 @@ struct SPlan {
 // Fills *out (out->on false: the path does not take this call).
 void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, SPlan* out);
 
-// Enqueues the whole path on `s` over the workspace `ws` (p.total bytes).
-int sample_enqueue(const SPlan& p, const void* keys, void* ws, void* out_vals, uint32_t* out_idx,
+// Enqueues the whole path on `s` over the workspace `ws` (p.total bytes); failed
+// internal checks are recorded in `rec` (nullptr: nowhere).
+int sample_enqueue(const SPlan& p, const void* keys, void* ws, uint32_t* rec, void* out_vals, uint32_t* out_idx,
                    void* out_kth, hipStream_t s, bool marks);
 
 }  // namespace drtopk
