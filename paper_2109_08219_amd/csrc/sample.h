@@ -437,15 +437,16 @@ __device__ __forceinline__ void sfill_splitters(C* split, const SWin& w, uint32_
     return;
   }
   const uint32_t q0 = w.a ? w.a : 1u, top = w.a ? 0u : kSTop;
-  const uint32_t lgP = 31u - (uint32_t)__clz((int)w.P), thin = w.a ? 0u : kSThin;
+  const uint32_t lgP = 31u - (uint32_t)__clz((int)w.P), thin = w.a ? 0u : kSThin, cuts = w.P2 - 1;
+  const uint32_t lgP2 = 31u - (uint32_t)__clz((int)w.P2);
   auto sample = [&](uint32_t q) { return q <= m ? sorted[q - 1] : (C)0; };
-  const uint32_t nthin = thin < w.s ? thin : w.s, per = thin_splits(w.P);
+  const uint32_t nthin = thin < w.s ? thin : w.s, per = thin_splits(w.P2);
   // thin groups, a thread a splitter: its slot is the number of samples and
   // cuts above it
   for (uint32_t i = t; i < nthin * per; i += T) {
-    const uint32_t g = i / per, j = i % per, cuts = w.P - 1;
+    const uint32_t g = i / per, j = i % per;
     const uint32_t qa = q0 + g * kSGroup, qb = qa + kSGroup < w.r ? qa + kSGroup : w.r;
-    const C x0 = sample(qa), step = (x0 - sample(qb)) >> lgP;
+    const C x0 = sample(qa), step = (x0 - sample(qb)) >> lgP2;
     C v;
     uint32_t slot;
     if (j < cuts) {
@@ -467,13 +468,38 @@ __device__ __forceinline__ void sfill_splitters(C* split, const SWin& w, uint32_
     for (uint32_t i = 0; i <= kSGroup; ++i) x[i] = sample(qa + i < qb ? qa + i : qb);
     const C step = (x[0] - x[kSGroup]) >> lgP;
     C* const out = split + top + nthin * per + (g - nthin) * w.P;
-    // seven samples in one part's width: the keys are clustered here, and the
-    // samples divide them better
-    bool crowded = false;
+    // Seven samples in a quarter of a part's width: the keys are clustered here,
+    // and the samples divide them better.  In one part's width: they may be, or
+    // the keys are even and the samples met by chance (7 to 37% of calls on normal
+    // keys had a group that did; between its samples a bucket then often held
+    // more than a workgroup sorts).  Where that would leave buckets of single
+    // gaps, twice as wide parts and every second sample divide the keys together,
+    // at most two parts and two gaps whichever it is; else the parts do.
+    bool tight = false, crowded = false;
 #pragma unroll
-    for (uint32_t i = 0; i + 6 <= kSGroup; ++i) crowded = crowded || (qa + i + 6 <= qb && x[i] - x[i + 6] < step);
+    for (uint32_t i = 0; i + 6 <= kSGroup; ++i)
+      if (qa + i + 6 <= qb) {
+        crowded = crowded || x[i] - x[i + 6] < step;
+        tight = tight || x[i] - x[i + 6] < (step >> 2);
+      }
     for (uint32_t f = 1; f < w.P; ++f) out[f - 1] = x[0] - step * f;
-    if (crowded) {
+    if (crowded && !tight && w.P >= kSGroup) {
+      const uint32_t half = w.P >> 1;
+      for (uint32_t f = 1; f < half; ++f) {
+        const C v = x[0] - step * (2 * f);
+        uint32_t slot = f - 1;
+#pragma unroll
+        for (uint32_t i = 2; i <= kSGroup; i += 2) slot += x[i] >= v ? 1u : 0u;
+        out[slot] = v;
+      }
+#pragma unroll
+      for (uint32_t i = 2; i <= kSGroup; i += 2) {
+        uint32_t slot = i / 2 - 1;
+        for (uint32_t f = 1; f < half; ++f) slot += x[0] - step * (2 * f) > x[i] ? 1u : 0u;
+        out[slot] = x[i];
+      }
+      for (uint32_t f = half - 1 + kSGroup / 2; f < w.P; ++f) out[f] = x[kSGroup];
+    } else if (tight) {
       if (w.P >= kSGroup) {
         for (uint32_t f = kSGroup; f < w.P; ++f) out[f] = x[kSGroup];
 #pragma unroll

@@ -22,10 +22,12 @@ struct SPayload {
 // power of two, from rank max(a, 1) on: P equal intervals of composite space
 // between every kSGroup-th sample; and when the window is open (a = 0), where
 // the keys thin out, before that kSTop intervals above the first sample and over
-// the first kSThin groups the samples themselves besides the intervals.  s:
-// groups in all.
+// the first kSThin groups the samples themselves besides P2 intervals (twice as
+// many, unless they would make too many buckets: the keys of the first group
+// thin out so fast that its lowest interval of P held more than a workgroup sorts
+// in 1 of 80 calls, normal float32, n = 2^24, k = 2^21).  s: groups in all.
 struct SWin {
-  uint32_t r, a, s, P, B, pad[3];
+  uint32_t r, a, s, P, B, P2, pad[2];
 };
 constexpr uint32_t kSTop = 8;
 constexpr uint32_t kSGroup = 16;
@@ -45,8 +47,8 @@ __host__ __device__ inline void sample_window(double count, double k, double m, 
   w->r = hi < m ? (uint32_t)hi : (uint32_t)m + 1;  // m + 1: no cut, every element is a candidate
   w->a = kth && lo >= 1.0 ? (uint32_t)lo : 0u;
 }
-// Splitters of the first `thin` groups (see SWin) and of one after them.
-__host__ __device__ inline uint32_t thin_splits(uint32_t P) { return P + kSGroup - 1; }
+// Splitters of one of the first kSThin groups (see SWin).
+__host__ __device__ inline uint32_t thin_splits(uint32_t P2) { return P2 + kSGroup - 1; }
 
 // Buckets are planned for `target` elements.  Gaps between neighbouring samples
 // are as uneven as exponential variables (one in 43 holds 3.75 times the mean,
@@ -57,16 +59,21 @@ __host__ __device__ inline uint32_t thin_splits(uint32_t P) { return P + kSGroup
 __host__ __device__ inline void sample_buckets(double gap, uint32_t target, uint32_t bmax, SWin* w) {
   const uint32_t q0 = w->a ? w->a : 1u, top = w->a ? 0u : kSTop;
   const uint32_t groups = (w->r - q0 + kSGroup - 1) / kSGroup;
-  uint32_t P = 0;
+  uint32_t P = 0, P2 = 0;
   if (6.0 * gap > (double)target) {
     P = 4;
     while (P < 64 && (double)kSGroup * gap > (double)target * P) P <<= 1;
     const uint32_t thin = w->a ? 0u : groups < kSThin ? groups : kSThin;
-    const uint64_t B = top + (uint64_t)thin * thin_splits(P) + (uint64_t)(groups - thin) * P;
+    uint64_t B = 0;
+    for (P2 = 2 * P; P2 >= P; P2 >>= 1) {
+      B = top + (uint64_t)thin * thin_splits(P2) + (uint64_t)(groups - thin) * P;
+      if (B <= bmax || P2 == P) break;
+    }
     w->B = (uint32_t)B;
     if (B > bmax) P = 0;
   }
   w->P = P;
+  w->P2 = P2;
   if (P) {
     w->s = groups;
     return;
