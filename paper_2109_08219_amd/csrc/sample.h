@@ -475,15 +475,13 @@ __device__ __forceinline__ void sfill_splitters(C* split, const SWin& w, uint32_
     // more than a workgroup sorts).  Where that would leave buckets of single
     // gaps, twice as wide parts and every second sample divide the keys together,
     // at most two parts and two gaps whichever it is; else the parts do.
-    bool tight = false, crowded = false;
+    C least = ~(C)0;  // width of seven samples
 #pragma unroll
     for (uint32_t i = 0; i + 6 <= kSGroup; ++i)
-      if (qa + i + 6 <= qb) {
-        crowded = crowded || x[i] - x[i + 6] < step;
-        tight = tight || x[i] - x[i + 6] < (step >> 2);
-      }
+      if (qa + i + 6 <= qb && x[i] - x[i + 6] < least) least = x[i] - x[i + 6];
+    const bool tight = least < (step >> 2);
     for (uint32_t f = 1; f < w.P; ++f) out[f - 1] = x[0] - step * f;
-    if (crowded && !tight && w.P >= kSGroup) {
+    if (least < step && !tight && w.P >= kSGroup) {
       const uint32_t half = w.P >> 1;
       for (uint32_t f = 1; f < half; ++f) {
         const C v = x[0] - step * (2 * f);
