@@ -82,7 +82,9 @@ typedef enum {
  *   stream   hipStream_t or NULL
  * Calls with k > 1 (8-byte keys: any k) split the work by a sample of the keys
  * (one workgroup with a cut for few keys; else a filter pass and buckets sorted
- * independently); the result is exact whatever the sample. */
+ * independently); the result is exact whatever the sample.  The sampled places
+ * of the latter are other ones in each process, so no input can be laid out to
+ * be misjudged by them. */
 int topk_select(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals,
                 uint32_t* out_idx, void* stream);
 
@@ -409,6 +411,11 @@ int drtopk_set_survivor_cap(uint64_t cap);
  * are dropped, flags 16 and 2 raised, and every kernel exits normally.
  * Process-wide; not for production use. */
 int drtopk_set_run_cap(uint32_t cap);
+
+/* Testing hook: with on != 0 the sampled places of the calls made after it are
+ * those of `salt`, so that a test can lay out an input that they misjudge; on = 0
+ * restores the process's own.  Process-wide; not for production use. */
+int drtopk_fix_sample(int on, uint32_t salt);
 
 /* Human-readable name of a status code (static string). */
 const char* drtopk_status_string(int status);

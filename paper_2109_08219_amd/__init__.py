@@ -121,6 +121,7 @@ def lib() -> ctypes.CDLL:
             "drtopk_check": [vp, ctypes.POINTER(u32)],
             "drtopk_set_survivor_cap": [u64],
             "drtopk_set_run_cap": [u32],
+            "drtopk_fix_sample": [i32, u32],
         }
         for name, args in sig.items():
             f = getattr(L, name)
@@ -220,6 +221,11 @@ def set_run_cap(cap: int) -> None:
     """Testing hook: caps what the sampled path collects at a time where a sample misjudges the
     keys or a bucket is larger than a workgroup (0 = the workgroup's capacity)."""
     _check(lib().drtopk_set_run_cap(int(cap)), "drtopk_set_run_cap")
+
+
+def fix_sample(salt) -> None:
+    """Testing hook: the places that calls sample are those of `salt` (None: the process's own)."""
+    _check(lib().drtopk_fix_sample(0 if salt is None else 1, int(salt or 0)), "drtopk_fix_sample")
 
 
 def topk_select(keys, k: int, out_vals=None, out_idx=None, *, dtype=None, largest: bool = True, alpha=None,

@@ -1365,6 +1365,11 @@ int drtopk_set_run_cap(uint32_t cap) {
   return DRTOPK_OK;
 }
 
+int drtopk_fix_sample(int on, uint32_t salt) {
+  sample_fix_salt(on != 0, salt);
+  return DRTOPK_OK;
+}
+
 const char* drtopk_status_string(int status) {
   switch (status) {
     case DRTOPK_OK: return "ok";

@@ -132,7 +132,20 @@ __device__ __forceinline__ uint32_t shash(uint32_t x) {
 }
 
 // ---------------------------------------------------------------------------
+// The stratum of sample i of M = mask + 1 (a power of two): a permutation that
+// scatters strata over the workgroups, another one for another salt.
+__device__ __forceinline__ uint32_t sscatter(uint32_t i, uint32_t mask, uint32_t salt) {
+  i = (i + salt) * 0x9E3779B1u & mask;
+  i ^= i >> 7;
+  i = i * (salt | 1u) & mask;
+  i ^= i >> 9;
+  return i * 0x85EBCA6Bu & mask;
+}
+
 // Sampling, M samples (a multiple of 256) from a source of at least M elements.
+// The sampled places depend on a salt of the process, so no input can be laid
+// out to be misjudged (its rescue reads the input many times by few workgroups;
+// see sbucket_rare).
 // ARR: the source is level 1's candidates (their number is on the device);
 // otherwise the input.  TOP: of each 256 samples the 16 largest are kept.  When
 // the window's r is a few per workgroup, its top r samples are all kept but
@@ -150,15 +163,15 @@ constexpr uint32_t kSKeep = 16;
 template <typename K, bool ARR, bool TOP>
 __global__ __launch_bounds__(TOP ? 1024 : 256) void k_sgather(const K* __restrict__ keys,
                                                  const typename STraits<K>::Comp* __restrict__ arr, uint64_t n,
-                                                 uint32_t cap1, uint32_t k, uint32_t M, SCodec<K> cd, int L,
-                                                 SWin win, int kth, uint32_t bmax, SCtl* ctl,
+                                                 uint32_t cap1, uint32_t k, uint32_t M, uint32_t salt,
+                                                 SCodec<K> cd, int L, SWin win, int kth, uint32_t bmax, SCtl* ctl,
                                                  typename STraits<K>::Comp* __restrict__ smp,
                                                  typename STraits<K>::Comp* __restrict__ sorted) {
   typedef typename STraits<K>::Comp C;
   uint32_t i = blockIdx.x * 256 + (threadIdx.x & 255u);
-  // M is a power of two here: a permutation that scatters neighbouring strata
-  // over the workgroups, so that a sorted input's top samples do not meet in one
-  if constexpr (TOP) i = (i * 0x9E3779B1u) & (M - 1);
+  // neighbouring strata in different workgroups, so that a sorted input's top
+  // samples do not meet in one
+  if constexpr (TOP) i = sscatter(i, M - 1, salt);
   uint64_t count = n;
   if constexpr (ARR) {
     count = (uint32_t)ctl->alloc1;
@@ -182,7 +195,7 @@ __global__ __launch_bounds__(TOP ? 1024 : 256) void k_sgather(const K* __restric
   if (!TOP || threadIdx.x < 256) {
     const uint64_t lo = (uint64_t)i * count / M, hi = (uint64_t)(i + 1) * count / M;
     if (hi > lo) {
-      const uint64_t p = lo + (uint64_t)(((uint64_t)shash(i) * (hi - lo)) >> 32);
+      const uint64_t p = lo + (uint64_t)(((uint64_t)shash(i + salt) * (hi - lo)) >> 32);
       if constexpr (ARR) x = arr[p];
       else x = scomp<K>(senc<K>(keys[p], cd), (uint32_t)p, L, posmask);
     }

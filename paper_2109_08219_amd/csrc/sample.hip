@@ -1,6 +1,8 @@
 // The sampled path: planner and kernel sequence.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cmath>
 
 #include "host.h"
@@ -175,10 +177,10 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
   pm.start(s);  // the timed pass: the sample and the one pass over the input
   if (p.top)
     hipLaunchKernelGGL((k_sgather<K, false, true>), dim3(p.m / kSKeep), dim3(1024), 0, s, keys, (const C*)nullptr, p.n,
-                       0u, p.k, p.m * 16, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
+                       0u, p.k, p.m * 16, p.salt, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
   else
     hipLaunchKernelGGL((k_sgather<K, false, false>), dim3(p.m / 256), dim3(256), 0, s, keys, (const C*)nullptr, p.n,
-                       0u, p.k, p.m, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
+                       0u, p.k, p.m, p.salt, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
   rank(p.m);
   if (p.plain || p.levels == 2) {
     constexpr uint64_t load = (uint64_t)64 * (16 / sizeof(K)) * (kSFilterThreads / 64);
@@ -201,7 +203,7 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
   pm.mid(s);
   if (p.levels == 2) {
     hipLaunchKernelGGL((k_sgather<K, true, false>), dim3(kSLevel2 / 256), dim3(256), 0, s, keys, c1, p.n, p.cap1, p.k,
-                       kSLevel2, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
+                       kSLevel2, p.salt, cd, p.L, p.win, kth, p.bmax, ctl, smp, sorted);
     rank(kSLevel2);
     const unsigned g = grid_for(p.cap1, T::kTile, 256);
     hipLaunchKernelGGL((k_spart<K, true>), dim3(g), dim3(kSPartThreads), 0, s, keys, c1, p.n, 0u, p.cap1, p.k,
@@ -225,6 +227,33 @@ void enqueue_for(const SPlan& p, const void* keys_v, void* ws, K* out_vals, uint
 }
 
 }  // namespace
+
+namespace {
+
+std::atomic<uint64_t> g_fixed_salt{0};  // testing hook: 2^32 + salt, or 0
+
+// The sampled places' salt: another one in each process, so that no input can be
+// laid out to be misjudged.  (Another one for each call would do as well, but
+// the sampled lines that one call leaves in the caches then serve no later call
+// on the same keys: 2 to 4% of a call of 2^20 to 2^24 keys.)
+uint32_t sample_salt() {
+  if (const uint64_t f = g_fixed_salt.load(std::memory_order_relaxed)) return (uint32_t)f;
+  static const uint32_t salt = [] {
+    uint64_t z = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+    z ^= (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull;
+    z ^= (uint64_t)reinterpret_cast<uintptr_t>(&g_fixed_salt);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;  // SplitMix64's output function
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return (uint32_t)(z >> 32);
+  }();
+  return salt;
+}
+
+}  // namespace
+
+void sample_fix_salt(bool on, uint32_t salt) {
+  g_fixed_salt.store(on ? (uint64_t(1) << 32) | salt : 0, std::memory_order_relaxed);
+}
 
 void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, SPlan* out) {
   SPlan p;
@@ -257,6 +286,7 @@ void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_o
     else if (p.wide) plan_for<uint64_t>(p);
     else plan_for<uint32_t>(p);
   }
+  if (p.on && !p.one) p.salt = sample_salt();
   *out = p;
 }
 

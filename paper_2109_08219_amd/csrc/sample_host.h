@@ -28,6 +28,7 @@ struct SPlan {
   int L = 1;              // position bits of a composite
   bool top = false;       // 16 m samples, the top 16 of each 256 kept
   uint32_t m = 0;         // samples kept
+  uint32_t salt = 0;      // of the sampled places
   SWin win = {};          // level 1's window
   uint32_t bmax = 1;      // most buckets of the partitioned level
   uint32_t cap1 = 0, cap = 0;    // candidates kept by level 1, by the partitioned level
@@ -40,6 +41,9 @@ struct SPlan {
 
 // Fills *out (out->on false: the path does not take this call).
 void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_only, SPlan* out);
+
+// Testing hook: the salt of every call planned after it (off: the process's own).
+void sample_fix_salt(bool on, uint32_t salt);
 
 // Enqueues the whole path on `s` over the workspace `ws` (p.total bytes); failed
 // internal checks are recorded in `rec` (nullptr: nowhere).

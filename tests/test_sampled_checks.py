@@ -29,10 +29,12 @@ def say(*a):
 def capped():
     drt.check()  # nothing left over from earlier tests on this stream
     drt.set_run_cap(50)
+    drt.fix_sample(0)
     try:
         yield
     finally:
         drt.set_run_cap(0)
+        drt.fix_sample(None)
 
 
 def misjudged(n, M, dt="u32"):
