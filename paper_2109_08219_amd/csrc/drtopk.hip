@@ -414,7 +414,7 @@ constexpr size_t kSampledFree = size_t(4) << 20;
 // in it, so the sampled path needs no more than that or a small part of that
 // limit.
 bool take_sampled(const SPlan& sp, size_t total) {
-  return sp.on && (sp.k > 1 || sp.wide) && sp.total <= (total > kSampledFree ? total : kSampledFree) &&
+  return sp.on && (sp.k > 1 || sp.wide) && sp.planned <= (total > kSampledFree ? total : kSampledFree) &&
          g_cap_override.load(std::memory_order_relaxed) == 0;
 }
 
@@ -430,7 +430,7 @@ SPlan sampled_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth
                    F&& other) {
   SPlan sp;
   sample_plan(keys, n, k, dtype, kth_only, &sp);
-  sp.on = take_sampled(sp, sp.on && sp.total > kSampledFree ? other() : 0);
+  sp.on = take_sampled(sp, sp.on && sp.planned > kSampledFree ? other() : 0);
   sp.pay = pay;
   hook_run_cap(sp);
   return sp;
@@ -897,7 +897,7 @@ int topk_select_noalloc(const void* keys, uint64_t n, uint32_t k, int dtype, voi
     SPlan sp;
     sample_plan(keys, n, k, dtype, false, &sp);
     hook_run_cap(sp);
-    if (take_sampled(sp, wide ? wp.total : p.total))
+    if (take_sampled(sp, wide ? wp.total : p.total) && sp.total <= kScratchBytes - kScratchRec)
       return sample_enqueue(sp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, s, false);
     if (wide) return wide_enqueue(wp, keys, ws, static_cast<uint32_t*>(base), out_vals, out_idx, nullptr, false, s);
     p.rec = static_cast<uint32_t*>(base);

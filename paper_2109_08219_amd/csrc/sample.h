@@ -24,8 +24,9 @@
 // The sample only decides how the work is split.  A sample that misjudges the
 // input (fewer than k elements at or above its cut, or more candidates than
 // the buffer holds) is noticed from exact counts, and k_sbucket then answers
-// from the input itself (rescue); the window's margin makes that rarer than
-// 10^-10 for inputs laid out without regard to the sampled positions.
+// from the input itself (rescue).  The window's margin and the buffers' room
+// make either rarer than exp(-24) for inputs laid out without regard to the
+// sampled positions.
 #pragma once
 
 #include "internal.h"

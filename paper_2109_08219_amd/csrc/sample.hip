@@ -1,6 +1,7 @@
 // The sampled path: planner and kernel sequence.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -27,8 +28,17 @@ uint32_t small_rank(double lam) {
   return r + 1;
 }
 
-// Candidates at or above the r-th sample, but for six standard deviations.
+// Candidates from the first sample down to the `span`-th, planned for: but for
+// six standard deviations.
 double span_cap(double span, double gap) { return (span + 6.0 * std::sqrt(span) + 10.0) * gap; }
+
+// Room for them: more with probability below exp(-24) (Chernoff's bound of
+// fewer than `span` samples among as many elements).
+double span_room(double span, double gap) {
+  double lam = span + 6.0 * std::sqrt(span) + 10.0;
+  while (lam - span - span * std::log(lam / span) < 24.0) lam += 0.125 * std::sqrt(span) + 0.5;
+  return lam * gap;
+}
 
 template <typename K>
 void plan_for(SPlan& p) {
@@ -36,7 +46,8 @@ void plan_for(SPlan& p) {
   typedef typename T::Comp C;
   const double n = (double)p.n, k = (double)p.k;
   SWin w = {};
-  uint64_t cap1 = 0, cap = 0;
+  uint64_t cap1 = 0, cap = 0;             // room for the candidates
+  uint64_t planned1 = 0, planned = 0;     // as many as are planned for
   double cap_top = 0, gap = 0;
   // the r-th of 16 m samples, of which the top 16 of each 256 are kept, when
   // r is at most a fifth of what is kept
@@ -65,61 +76,73 @@ void plan_for(SPlan& p) {
     p.plain = 1;
     w.a = 0;
     w.B = p.bmax = 1;
-    cap = T::kCap;
+    planned = T::kCap;
+    cap = std::max<uint64_t>((uint64_t)span_room(w.r, gap), T::kCap);
   } else if (p.top && gap <= 2.0 * T::kTarget && cap_top <= T::kList) {
     // few enough that each bucket's workgroup can read all of them
     p.plain = 1;
     sample_buckets(gap, T::kTarget, T::kMaxB, &w);
-    cap = (uint64_t)cap_top;
+    planned = (uint64_t)cap_top;
+    cap = (uint64_t)span_room(w.r, gap);
     p.bmax = w.B;
   } else if (p.top) {
     // few of many: the streaming filter, and its candidates partitioned; the
     // partition's own pass over the input (2.2 us per 32 KB and CU) is for
     // windows that keep a share of it
     p.levels = 2;
-    cap1 = (uint64_t)cap_top;
-    if (cap1 > p.n) cap1 = p.n;
-    if (cap1 > (1u << 24)) return;
+    planned1 = std::min<uint64_t>((uint64_t)cap_top, p.n);
+    if (planned1 > (1u << 24)) return;
     SWin w2 = {};
+    sample_window((double)planned1, k, kSLevel2, false, &w2);
+    planned = std::min<uint64_t>((uint64_t)span_cap(w2.r, (double)planned1 / kSLevel2), planned1);
+    const uint64_t b = 4 * planned / T::kTarget + 64;
+    cap1 = std::min<uint64_t>((uint64_t)span_room(w.r, gap), p.n);
     sample_window((double)cap1, k, kSLevel2, false, &w2);
-    cap = (uint64_t)span_cap(w2.r, (double)cap1 / kSLevel2);
-    if (cap > cap1) cap = cap1;
-    const uint64_t b = 4 * cap / T::kTarget + 64;
+    cap = std::min<uint64_t>((uint64_t)span_room(w2.r, (double)cap1 / kSLevel2), cap1);
     p.bmax = b < (uint64_t)T::kMaxB ? (uint32_t)b : (uint32_t)T::kMaxB;
   } else if (gap <= 2.0 * T::kTarget) {
     sample_buckets(gap, T::kTarget, T::kMaxB, &w);
-    cap = (uint64_t)span_cap(w.r - w.a, gap);
+    planned = (uint64_t)span_cap(w.r - w.a, gap);
+    cap = (uint64_t)span_room(w.r - w.a, gap);
     p.bmax = w.B;
   } else {
     return;
   }
   p.win = w;
   if (cap > p.n) cap = p.n;
-  // rows: a workgroup's last, and those written because a tile did not fit
-  const uint64_t rows = grid_for(p.levels == 2 ? cap1 : p.n, T::kTile, 256) + cap / (T::kStage - T::kTile) + 1;
-  if (!p.plain && rows > (uint64_t)kSMaxRows) return;
-  p.rows = (uint32_t)rows;
-  p.cap1 = (uint32_t)cap1;
-  p.cap = (uint32_t)cap;
-  p.pitch = (p.bmax + 1 + 31) & ~31u;
-  size_t off = 0;
-  auto seg = [&](size_t bytes) {
-    const size_t o = off;
-    off = salign(off + bytes);
-    return o;
+  // rows: a workgroup's last, and those written because a tile did not fit (two of
+  // these in a row hold more than a stage, so the limit leaves enough for `cap`)
+  if (planned > p.n) planned = p.n;
+  auto rows = [&](uint64_t c1, uint64_t c) {
+    return grid_for(p.levels == 2 ? c1 : p.n, T::kTile, 256) + c / (T::kStage - T::kTile) + 1;
   };
-  p.off_ctl = seg(sizeof(SCtl));
-  const size_t ms = p.levels == 2 && p.m < kSLevel2 ? kSLevel2 : p.m;
-  p.off_smp = seg(ms * sizeof(C));
-  p.off_sorted = seg(ms * sizeof(C));
-  if (p.levels == 2) p.off_c1 = seg((size_t)p.cap1 * sizeof(C));
-  p.off_cand = seg(((size_t)p.cap + 1) * sizeof(C));  // whole 16-byte pieces
-  if (!p.plain) {
-    p.off_rows = seg(p.rows * sizeof(SRow));
-    p.off_bounds = seg((size_t)p.bmax * sizeof(C));
-    p.off_offs = seg((size_t)p.rows * p.pitch * sizeof(uint16_t));
-  }
-  p.total = off;
+  if (!p.plain && rows(planned1, planned) > (uint64_t)kSMaxRows) return;
+  p.pitch = (p.bmax + 1 + 31) & ~31u;
+  auto layout = [&](uint64_t c1, uint64_t c) {
+    p.cap1 = (uint32_t)c1;
+    p.cap = (uint32_t)c;
+    p.rows = (uint32_t)std::min<uint64_t>(rows(c1, c), kSMaxRows);
+    size_t off = 0;
+    auto seg = [&](size_t bytes) {
+      const size_t o = off;
+      off = salign(off + bytes);
+      return o;
+    };
+    p.off_ctl = seg(sizeof(SCtl));
+    const size_t ms = p.levels == 2 && p.m < kSLevel2 ? kSLevel2 : p.m;
+    p.off_smp = seg(ms * sizeof(C));
+    p.off_sorted = seg(ms * sizeof(C));
+    if (p.levels == 2) p.off_c1 = seg((size_t)p.cap1 * sizeof(C));
+    p.off_cand = seg(((size_t)p.cap + 1) * sizeof(C));  // whole 16-byte pieces
+    if (!p.plain) {
+      p.off_rows = seg(p.rows * sizeof(SRow));
+      p.off_bounds = seg((size_t)p.bmax * sizeof(C));
+      p.off_offs = seg((size_t)p.rows * p.pitch * sizeof(uint16_t));
+    }
+    return off;
+  };
+  p.planned = layout(planned1, planned);
+  p.total = layout(cap1, cap);
   p.on = true;
 }
 

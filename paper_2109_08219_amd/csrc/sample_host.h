@@ -37,6 +37,7 @@ struct SPlan {
   uint64_t codec_a = 0, codec_c = 0;
   size_t off_ctl = 0, off_smp = 0, off_sorted = 0, off_c1 = 0, off_cand = 0, off_rows = 0, off_offs = 0, off_bounds = 0;
   size_t total = 0;
+  size_t planned = 0;     // of that, without the room for more candidates than are planned for
 };
 
 // Fills *out (out->on false: the path does not take this call).

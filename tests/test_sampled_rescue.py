@@ -98,3 +98,22 @@ def test_graph_replays_keep_their_places(fixed):
         g.replay()
         torch.cuda.synchronize()
         check_exact(x, k, "u32", to_np(vals).view(np.uint32), to_np(idx), f"replay {rep}")
+
+
+@pytest.mark.parametrize("dt,n,k,high", [("u32", 2_400_000, 2048, 7715), ("u64", 1_120_000, 1024, 3650)])
+def test_more_candidates_than_a_workgroup_sorts(dt, n, k, high, fixed):
+    # one bucket by the plan; its buffer holds some more than a workgroup sorts at
+    # once, and the cut lets `high` through: the lowest of them are 129 sampled keys
+    rng = np.random.default_rng(3)
+    x, _ = synth.keys(f"uniform_{dt}", n, 31)
+    bit = np.array(1 << (63 if dt == "u64" else 31), x.dtype)
+    x &= ~bit
+    p = sampled_positions(n, 65536)
+    x[rng.choice(p, 129, replace=False)] = bit
+    rest = rng.choice(np.setdiff1d(np.arange(n), p), high - 129, replace=False)
+    x[rest] |= bit | np.array(1, x.dtype)
+    t = torch.from_numpy(x).cuda()
+    say("one bucket in runs", dt, n, k)
+    assert rescued(lambda: drt.topk_select(t, k))  # (the cap shows runs as well)
+    v, i = drt.topk_select(t, k, check=True)
+    check_exact(x, k, dt, to_np(v), to_np(i), f"one bucket in runs {dt}")
