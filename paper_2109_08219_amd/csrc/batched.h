@@ -1,10 +1,11 @@
 // Many independent top-k problems in one launch.
 //
 // A workgroup (kBT threads, two share a CU, so one streams keys while the other
-// sorts) takes one problem:
-//   of at most kBSmallN keys: sorted in LDS, or selected first (the k-th by
-//     radix select, then the k at or above it sorted; see b_whole);
-//   of more: one pass over its keys (b_stream).
+// sorts) takes one problem, by the rule in routes.h one of two ways:
+//   b_stream: up to kBSmallN keys are sorted in LDS, more in one pass over them;
+//   b_problem: up to kBSmallN keys are selected first (the k-th by radix select,
+//     then the k at or above it sorted), more by the delegate method in one
+//     workgroup's LDS.
 // Problems of more than a slot's share of the batch's keys are split, and run
 // the delegate method over several workgroups:
 //   delegate vector (Rules 1 and 3): the top beta (1 or 2) of each subrange
@@ -17,8 +18,7 @@
 //     the other subranges;
 //   output: survivors sorted in registers, the first k written.
 // When there are many tiles of split problems (k_batched_split), and for one
-// problem alone (k_one), whole problems run the delegate method in one
-// workgroup's LDS too.  One whose survivors overflow the LDS (adversarial
+// problem alone (k_one), whole problems take b_problem too.  One whose survivors overflow the LDS (adversarial
 // inputs), or whose delegate vector would not exceed k, takes a block-level MSD
 // radix select over its keys.  No workgroup ever waits for another.
 #pragma once
@@ -31,7 +31,6 @@ namespace drtopk {
 constexpr int kBT = 512;                  // threads per workgroup (two workgroups per CU)
 constexpr int kBWaves = kBT / 64;
 constexpr uint32_t kBSmallN = 4096;       // problems this small are selected in LDS directly
-constexpr uint32_t kBShortN = 1024;       // problems this small are sorted whole, whatever k
 constexpr uint32_t kBMaxS = 4096;         // delegate vector capacity (LDS)
 constexpr uint32_t kBMaxSG = 32768;       // delegate vector of a split problem (global memory)
 constexpr uint32_t kBSurv = 4096;         // survivor capacity (LDS)
@@ -57,7 +56,7 @@ struct BatchDesc {
   uint32_t dtype;
   uint16_t alpha;  // subrange exponent, >= 2; 0 = radix select without delegates
   uint16_t beta;   // delegates per subrange (Rule 3): 1 or 2
-  uint32_t tiles;  // > 1: the delegate vector is built by this many workgroups
+  uint32_t tiles;  // > 1: the delegate vector is built by this many workgroups; 0: whole, by b_problem
   uint32_t* out_vals;
   uint32_t* out_idx;
   uint32_t* out_kth;
@@ -1125,19 +1124,22 @@ union BatchLds {
   BStreamSmem s;
 };
 
-// By the descriptor's alpha and beta.
-template <bool VEC>
-__device__ inline void b_problem_v(const BatchDesc& d, BatchSmem& sm, uint32_t* rec) {
+// By the descriptor's alpha and beta.  OVER: survivors that overflow the LDS
+// (ordered or tied keys) are left to the caller, who gets false.
+template <bool VEC, bool OVER>
+__device__ inline bool b_problem_v(const BatchDesc& d, BatchSmem& sm, uint32_t* rec) {
   if (d.n <= kBSmallN) {
     b_small<VEC>(d, sm);
-    return;
+    return true;
   }
   if (d.alpha >= 2) {
     const uint64_t E = ((d.n + (1ull << d.alpha) - 1) >> d.alpha) * d.beta;
-    if (E <= kBMaxS && E > d.k && (d.beta == 2 ? b_delegate<VEC, 2>(d, sm) : b_delegate<VEC, 1>(d, sm))) return;
+    if (E <= kBMaxS && E > d.k && (d.beta == 2 ? b_delegate<VEC, 2>(d, sm) : b_delegate<VEC, 1>(d, sm))) return true;
     __syncthreads();
+    if constexpr (OVER) return false;
   }
   b_radix<VEC>(d, sm, rec);
+  return true;
 }
 
 template <bool VEC, int BETA>
@@ -1182,21 +1184,20 @@ __device__ inline void b_tile(const BatchDesc& d, uint32_t tile, uint32_t* arriv
   b_radix<VEC>(d, sm, rec);
 }
 
-__device__ inline void b_problem(const BatchDesc& d, BatchSmem& sm, uint32_t* rec) {
+template <bool OVER = false>
+__device__ inline bool b_problem(const BatchDesc& d, BatchSmem& sm, uint32_t* rec) {
   const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
-  if (vec) b_problem_v<true>(d, sm, rec);
-  else b_problem_v<false>(d, sm, rec);
+  return vec ? b_problem_v<true, OVER>(d, sm, rec) : b_problem_v<false, OVER>(d, sm, rec);
 }
 
-// One problem of a batch.  Up to kBSmallN keys are sorted whole where few are
-// wanted or there are few (us a call: 30 problems of 64..4000 keys, k <= 64, 8.2
-// against 10.2 by a select first; of 64..500, k <= 100, 6.5 / 8.6); most of
-// more (float keys of both signs crowd the sort's bins) are selected first and
-// sorted by a network (4096 of 2000..4096, k <= 2048: 207 / 211).
+// One whole problem of a batch.  WAYS: which of the two ways some item takes: 1
+// b_problem, for items with tiles = 0; 2 b_stream; 3 both.  What overflows the
+// delegate method is streamed (two lists of 65536 ordered float32, k = 4: 34 us
+// where a radix select of the keys took 108).
+template <int WAYS>
 __device__ __forceinline__ void b_whole(const BatchDesc& d, BatchLds& lds, uint32_t* rec) {
-  if (d.n > kBSmallN || d.n <= kBShortN || (uint64_t)d.k * 8 <= d.n) b_stream(d, lds.s, rec);
-  else if ((reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0) b_small<true>(d, lds.b);
-  else b_small<false>(d, lds.b);
+  if ((WAYS == 1 || (WAYS == 3 && d.tiles == 0)) && b_problem<true>(d, lds.b, rec)) return;
+  b_stream(d, lds.s, rec);
 }
 
 __device__ inline void b_tile_any(const BatchDesc& d, uint32_t tile, uint32_t* arrive, uint64_t* Dg, BatchSmem& sm,
@@ -1220,6 +1221,7 @@ __device__ inline void b_tile_any(const BatchDesc& d, uint32_t tile, uint32_t* a
 // A workgroup per item.  (In a loop over items the whole problems' many
 // indices made from the thread's number are carried through it in registers:
 // 4000 of them spilled; and the code of a call costs 20 us a launch.)
+template <int WAYS>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched(
     const BatchDesc* __restrict__ descs, const uint32_t* __restrict__ items, uint32_t* arrive, uint64_t* Dg,
     uint32_t* rec) {
@@ -1228,7 +1230,7 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k
   const uint32_t i = it >> 8;
   const BatchDesc d = descs[i];
   if (d.tiles > 1) b_tile_any(d, it & 0xFFu, &arrive[i], Dg, lds.b, rec);
-  else b_whole(d, lds, rec);
+  else b_whole<WAYS>(d, lds, rec);
 }
 
 // Items claimed from *counter (starts at 0), any grid size: for more tiles of
@@ -1260,10 +1262,11 @@ constexpr uint32_t kBInline = 32;
 struct BatchInline {
   BatchDesc d[kBInline];
 };
+template <int WAYS>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched_inline(BatchInline b, uint32_t* rec) {
   __shared__ BatchLds lds;
   const BatchDesc d = b.d[blockIdx.x];
-  b_whole(d, lds, rec);
+  b_whole<WAYS>(d, lds, rec);
 }
 
 // One problem, descriptor by value: the single-problem path for small inputs.

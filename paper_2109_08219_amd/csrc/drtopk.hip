@@ -28,6 +28,7 @@
 #include "drtopk.h"
 #include "host.h"
 #include "batched.h"
+#include "routes.h"
 #include "sample_host.h"
 #include "wide_host.h"
 
@@ -640,16 +641,28 @@ uint32_t batched_tiles(const BatchDesc& d) {
   return (uint32_t)((d.n + (1ull << tlog) - 1) >> tlog);
 }
 
+constexpr int kMaxDevices = 64;
+
 size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
+
+// Compute units of a device, asked for once (the query takes a tenth of a small
+// batch's call).
+int cu_count(int dev) {
+  static std::atomic<int> known[kMaxDevices];
+  std::atomic<int>* k = dev >= 0 && dev < kMaxDevices ? &known[dev] : nullptr;
+  int cus = k ? k->load(std::memory_order_relaxed) : 0;
+  if (cus > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  if (k) k->store(cus, std::memory_order_relaxed);
+  return cus;
+}
 
 // Device layout of a staged launch: claim counter | descriptors | per-problem
 // arrival counters | work items | delegate vectors of split problems (device
 // only).  Everything before the delegate vectors is copied from the pinned
 // buffer, counters zeroed.
-int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_t s, Workspace* ws) {
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const size_t slots = 2 * (size_t)cus;  // two workgroups fit a CU's LDS and registers
+int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_t s, Workspace* ws, int dev) {
+  const size_t slots = 2 * (size_t)cu_count(dev);  // two workgroups fit a CU's LDS and registers
   std::vector<BatchDesc> descs(items.size());
   bool split = false;
   uint64_t dg_entries = 0;
@@ -668,20 +681,35 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
     if (descs[i].tiles > 1) ntiles += descs[i].tiles;
   }
   // (a grid holds fewer than 2^32 threads)
-  const bool claim = ntiles > 2 * slots || items.size() > (size_t(1) << 22);
+  bool claim = ntiles > 2 * slots || items.size() > (size_t(1) << 22);
+  int ways = 0;        // of the whole problems (see b_whole)
+  bool radix = false;  // one of them runs a radix select
+  for (size_t i = 0; i < items.size() && !claim; ++i)
+    if (descs[i].tiles <= 1) {
+      const bool streams = batch_streams(descs[i].n, descs[i].k, items.size());
+      descs[i].tiles = streams ? 1 : 0;
+      ways |= streams ? 2 : 1;
+      radix = radix || (!streams && descs[i].n > kBSmallN && descs[i].alpha == 0);
+    }
+  // Nothing to stream, and radix selects among many whole problems: the claimed
+  // grid (2000 of 5000, k = 2048: 183 us, 230 with a workgroup each; 100 of them,
+  // k = 24: 19.0 / 17.6).
+  claim = claim || (ways < 2 && radix && items.size() >= slots / 2);
   for (size_t i = 0; i < items.size(); ++i) {
     if (claim) descs[i].tiles = batched_tiles(descs[i]);
-    if (descs[i].tiles > 1) {
+    const bool several = descs[i].tiles > 1;
+    if (several) {
       split = true;
       descs[i].doff = dg_entries;
       dg_entries += ((descs[i].n + (1ull << descs[i].alpha) - 1) >> descs[i].alpha) * descs[i].beta;
     }
-    nwork += descs[i].tiles;
+    nwork += several ? descs[i].tiles : 1;
   }
   if (items.size() <= kBInline && !split) {  // descriptors as kernel arguments
     BatchInline b{};
     for (size_t i = 0; i < items.size(); ++i) b.d[i] = descs[i];
-    hipLaunchKernelGGL(k_batched_inline, dim3((unsigned)items.size()), dim3(kBT), 0, s, b, ws->rec);
+    const auto kernel = ways == 1 ? k_batched_inline<1> : ways == 2 ? k_batched_inline<2> : k_batched_inline<3>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)items.size()), dim3(kBT), 0, s, b, ws->rec);
     return hipGetLastError() == hipSuccess ? (int)DRTOPK_OK : (int)DRTOPK_EDEVICE;
   }
   const size_t off_desc = 64;
@@ -699,7 +727,7 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
   uint32_t* work = reinterpret_cast<uint32_t*>(h + off_items);
   size_t w = 0;
   for (size_t i = 0; i < descs.size(); ++i)  // longest first; a split problem's tiles adjacent
-    for (uint32_t t = 0; t < descs[i].tiles; ++t) work[w++] = ((uint32_t)i << 8) | t;
+    for (uint32_t t = 0; t < (descs[i].tiles > 1 ? descs[i].tiles : 1u); ++t) work[w++] = ((uint32_t)i << 8) | t;
   if (hipMemcpyAsync(ws->bdev, ws->bhost, need, hipMemcpyHostToDevice, s) != hipSuccess) return DRTOPK_EDEVICE;
   if (hipEventRecord(ws->bev, s) != hipSuccess) return DRTOPK_EDEVICE;
   ws->bev_pending = true;
@@ -712,7 +740,8 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
     hipLaunchKernelGGL(k_batched_split, dim3((unsigned)(nwork < slots ? nwork : slots)), dim3(kBT), 0, s, dd, di,
                        (uint32_t)nwork, reinterpret_cast<uint32_t*>(dv), da, dg, ws->rec);
   else
-    hipLaunchKernelGGL(k_batched, dim3((unsigned)nwork), dim3(kBT), 0, s, dd, di, da, dg, ws->rec);
+    hipLaunchKernelGGL(ways & 1 ? k_batched<3> : k_batched<2>, dim3((unsigned)nwork), dim3(kBT), 0, s, dd, di, da, dg,
+                       ws->rec);
   if (hipGetLastError() != hipSuccess) return DRTOPK_EDEVICE;
   return DRTOPK_OK;
 }
@@ -788,7 +817,6 @@ __global__ void k_zero_words(uint32_t* p, uint32_t n) {
 // hipGetSymbolAddress, once per device with that device current.
 constexpr size_t kScratchBytes = size_t(128) << 20;
 constexpr size_t kScratchRec = 256;
-constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_scratch_mu;
@@ -946,7 +974,7 @@ int topk_select_batched(const drtopk_problem_t* problems, uint32_t count, void* 
       std::lock_guard<std::mutex> lock(ws->mu);
       int st = ensure_record(ws);
       if (st) return st;
-      st = launch_batched(small, reinterpret_cast<hipStream_t>(stream), ws);
+      st = launch_batched(small, reinterpret_cast<hipStream_t>(stream), ws, dev);
       if (st) return st;
     }
     for (const drtopk_problem_t* q : large) {
