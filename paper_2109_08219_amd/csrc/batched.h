@@ -1088,24 +1088,33 @@ __device__ __forceinline__ void b_stream_write(const BatchDesc& d, uint64_t (&c)
   });
 }
 
+// Sorts all of at most N keys.  (Up to the LDS's capacity: streamed with a cut
+// that keeps every key, a wave's region of 960 overflowed in its first chunk, and
+// every problem of 4097 to 7680 keys dealt its elements out anew: 8 of 5000, k = 24,
+// 14.8 us, so 10.1; by the delegate method 11.5.)
+template <uint32_t N>
+__device__ __forceinline__ void b_sort_all(const BatchDesc& d, Codec cx, int L, uint32_t posmask, BStreamSmem& sm) {
+  constexpr int E = N / kBT;
+  static_assert(N % kBT == 0 && N <= kBStreamCap, "whole rows of the workgroup, in its LDS");
+  const uint32_t n = (uint32_t)d.n;
+  uint64_t c[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t p = e * kBT + threadIdx.x;
+    if (p < n) c[e] = scomp<uint32_t>(cx.enc(d.keys[p]), p, L, posmask);
+  }
+  b_stream_write<E>(d, c, n, cx, L, posmask, sm);
+}
+
 __device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm, uint32_t* rec) {
   const uint32_t n = (uint32_t)d.n, k = d.k;
   const Codec cx = codec_of(d.dtype);
   const int L = n > 1 ? 32 - __clz((int)(n - 1)) : 1;
   const uint32_t posmask = (1u << L) - 1;
-  if (n <= kBSmallN) {  // all of them
-    constexpr int E = kBSmallN / kBT;
-    uint64_t c[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const uint32_t p = e * kBT + threadIdx.x;
-      if (p < n) c[e] = scomp<uint32_t>(cx.enc(d.keys[p]), p, L, posmask);
-    }
-    b_stream_write<E>(d, c, n, cx, L, posmask, sm);
-    return;
-  }
+  if (n <= kBSmallN) return b_sort_all<kBSmallN>(d, cx, L, posmask, sm);
+  if (n <= kBStreamCap) return b_sort_all<kBStreamCap>(d, cx, L, posmask, sm);
   const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
-  const uint64_t cut = n <= kBStreamCap ? 0 : b_stream_sample(d.keys, n, k, cx, L, posmask, sm, rec);
+  const uint64_t cut = b_stream_sample(d.keys, n, k, cx, L, posmask, sm, rec);
   if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm, rec);
   else b_stream_keys<false>(d.keys, n, k, cx, L, posmask, cut, sm, rec);
   const uint32_t N = b_stream_gather(sm);

@@ -31,7 +31,7 @@ SLOWER = [(64, 64, 8), (200, 200, 30), (500, 500, 8), (1000, 512, 30), (1000, 38
           (100000, 8, 100), (200000, 1, 60)]
 # a tenth or more faster at each of them
 FASTER = [(64, 8, 30), (500, 62, 8), (1000, 16, 8), (1000, 128, 2000), (1024, 768, 30), (2000, 96, 8), (4096, 32, 30),
-          (4096, 64, 2000), (7681, 512, 500), (8192, 2048, 8), (16000, 2048, 30), (16000, 1024, 2000), (20000, 48, 30),
+          (4096, 64, 2000), (4097, 24, 8), (5000, 24, 30), (6000, 32, 2000), (7681, 512, 500), (8192, 2048, 8), (16000, 2048, 30), (16000, 1024, 2000), (20000, 48, 30),
           (31000, 512, 8), (31000, 16, 2000), (50000, 1024, 60), (65536, 512, 500), (65536, 2048, 8), (100000, 64, 500)]
 
 
