@@ -1227,19 +1227,35 @@ __device__ inline void b_tile_any(const BatchDesc& d, uint32_t tile, uint32_t* a
 // arrive[problem] (starts at 0) counting finished tiles.  No workgroup waits for
 // another.
 //
-// A workgroup per item.  (In a loop over items the whole problems' many
-// indices made from the thread's number are carried through it in registers:
-// 4000 of them spilled; and the code of a call costs 20 us a launch.)
-template <int WAYS>
+// Tiles come first.  CLAIM: `claimers` workgroups take one each and claim the others
+// from *counter (starts at 0); otherwise claimers = tiles.  With a workgroup each, those beyond what runs at
+// once were not started before workgroups that finish problems had ended
+// (150 problems of 400000 float32, k = 2048, 600 tiles: 160 us; claimed 110).
+// Up to one round the loop only costs registers (400 tiles: 94 us, 90 without).
+// Whole problems have a workgroup each.  (In a loop over them their many indices
+// made from the thread's number are carried through it in registers: 4000 of
+// them spilled; and the code of a call costs 20 us a launch.)
+template <int WAYS, bool CLAIM>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void k_batched(
-    const BatchDesc* __restrict__ descs, const uint32_t* __restrict__ items, uint32_t* arrive, uint64_t* Dg,
-    uint32_t* rec) {
+    const BatchDesc* __restrict__ descs, const uint32_t* __restrict__ items, uint32_t claimers, uint32_t tiles,
+    uint32_t* counter, uint32_t* arrive, uint64_t* Dg, uint32_t* rec) {
   __shared__ BatchLds lds;
-  const uint32_t it = items[blockIdx.x];
-  const uint32_t i = it >> 8;
-  const BatchDesc d = descs[i];
-  if (d.tiles > 1) b_tile_any(d, it & 0xFFu, &arrive[i], Dg, lds.b, rec);
-  else b_whole<WAYS>(d, lds, rec);
+  if (blockIdx.x >= claimers) {
+    const BatchDesc d = descs[items[tiles + (blockIdx.x - claimers)] >> 8];
+    b_whole<WAYS>(d, lds, rec);
+    return;
+  }
+  for (uint32_t w = blockIdx.x; w < tiles;) {
+    const uint32_t it = items[w], i = it >> 8;
+    const BatchDesc d = descs[i];
+    b_tile_any(d, it & 0xFFu, &arrive[i], Dg, lds.b, rec);
+    if constexpr (!CLAIM) return;
+    __syncthreads();
+    if (threadIdx.x == 0) lds.b.item = atomicAdd(counter, 1u);
+    __syncthreads();
+    w = claimers + lds.b.item;
+    __syncthreads();
+  }
 }
 
 // Items claimed from *counter (starts at 0), any grid size: for more tiles of

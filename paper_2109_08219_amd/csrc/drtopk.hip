@@ -725,9 +725,15 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
   std::memcpy(h + off_desc, descs.data(), descs.size() * sizeof(BatchDesc));
   std::memset(h + off_arrive, 0, off_items - off_arrive);
   uint32_t* work = reinterpret_cast<uint32_t*>(h + off_items);
-  size_t w = 0;
-  for (size_t i = 0; i < descs.size(); ++i)  // longest first; a split problem's tiles adjacent
-    for (uint32_t t = 0; t < (descs[i].tiles > 1 ? descs[i].tiles : 1u); ++t) work[w++] = ((uint32_t)i << 8) | t;
+  // longest first, a split problem's tiles adjacent; unless all are claimed, the
+  // tiles before the whole problems
+  size_t w = 0, tiles = 0;
+  for (int pass = claim ? 1 : 0; pass < 2; ++pass) {
+    for (size_t i = 0; i < descs.size(); ++i)
+      if (claim || (descs[i].tiles > 1) == (pass == 0))
+        for (uint32_t t = 0; t < (descs[i].tiles > 1 ? descs[i].tiles : 1u); ++t) work[w++] = ((uint32_t)i << 8) | t;
+    if (pass == 0) tiles = w;
+  }
   if (hipMemcpyAsync(ws->bdev, ws->bhost, need, hipMemcpyHostToDevice, s) != hipSuccess) return DRTOPK_EDEVICE;
   if (hipEventRecord(ws->bev, s) != hipSuccess) return DRTOPK_EDEVICE;
   ws->bev_pending = true;
@@ -739,9 +745,14 @@ int launch_batched(const std::vector<const drtopk_problem_t*>& items, hipStream_
   if (claim)
     hipLaunchKernelGGL(k_batched_split, dim3((unsigned)(nwork < slots ? nwork : slots)), dim3(kBT), 0, s, dd, di,
                        (uint32_t)nwork, reinterpret_cast<uint32_t*>(dv), da, dg, ws->rec);
-  else
-    hipLaunchKernelGGL(ways & 1 ? k_batched<3> : k_batched<2>, dim3((unsigned)nwork), dim3(kBT), 0, s, dd, di, da, dg,
-                       ws->rec);
+  else {
+    const bool more = tiles > slots;
+    const size_t claimers = more ? slots : tiles;
+    const auto kernel = ways & 1 ? (more ? k_batched<3, true> : k_batched<3, false>)
+                                 : (more ? k_batched<2, true> : k_batched<2, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nwork - tiles + claimers)), dim3(kBT), 0, s, dd, di, (uint32_t)claimers,
+                       (uint32_t)tiles, reinterpret_cast<uint32_t*>(dv), da, dg, ws->rec);
+  }
   if (hipGetLastError() != hipSuccess) return DRTOPK_EDEVICE;
   return DRTOPK_OK;
 }
