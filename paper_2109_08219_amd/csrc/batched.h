@@ -1044,7 +1044,7 @@ __device__ __forceinline__ void b_stream_keys(const uint32_t* keys, uint32_t n, 
   }
 }
 
-// The first cut: of 2048 or 6144 keys, in runs of 16 (a line of memory) at
+// The first cut: of 2048 or 6144 keys (of more than kBSmallN), in runs of 16 (a line of memory) at
 // hashed places of equal strata, about the one that as many are expected above
 // as of the k largest, and four and a half standard deviations more.  Fewer
 // than k above it means a second pass, so no more margin is needed.
@@ -1088,6 +1088,10 @@ __device__ __forceinline__ void b_stream_write(const BatchDesc& d, uint64_t (&c)
   });
 }
 
+// Lists above kBSmallN of which more than this by n * k is wanted are cut before
+// they are sorted: most of a list that is wanted crowds the sort's bins.
+constexpr uint32_t kBSortWork = 3u << 17;
+
 // Sorts all of at most N keys.  (Up to the LDS's capacity: streamed with a cut
 // that keeps every key, a wave's region of 960 overflowed in its first chunk, and
 // every problem of 4097 to 7680 keys dealt its elements out anew: 8 of 5000, k = 24,
@@ -1112,7 +1116,7 @@ __device__ __forceinline__ void b_stream(const BatchDesc& d, BStreamSmem& sm, ui
   const int L = n > 1 ? 32 - __clz((int)(n - 1)) : 1;
   const uint32_t posmask = (1u << L) - 1;
   if (n <= kBSmallN) return b_sort_all<kBSmallN>(d, cx, L, posmask, sm);
-  if (n <= kBStreamCap) return b_sort_all<kBStreamCap>(d, cx, L, posmask, sm);
+  if (n <= kBStreamCap && n * k <= kBSortWork) return b_sort_all<kBStreamCap>(d, cx, L, posmask, sm);
   const bool vec = (reinterpret_cast<uintptr_t>(d.keys) & 15u) == 0;
   const uint64_t cut = b_stream_sample(d.keys, n, k, cx, L, posmask, sm, rec);
   if (vec) b_stream_keys<true>(d.keys, n, k, cx, L, posmask, cut, sm, rec);

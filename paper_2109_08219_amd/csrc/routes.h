@@ -17,7 +17,8 @@ namespace drtopk {
 // work counts, which streaming has less of.  us a call, this way / the other:
 //   8 lists of 1000: k = 128 6.7 / 8.6, k = 512 11.0 / 8.9
 //   8 of 4096: k = 64 9.8 / 11.0, k = 128 13.3 / 12.5, k = 512 21 / 12
-//   8 of 6000: k = 32 10.5 / 11.6, k = 512 28 / 15
+//   4 of 6000: k = 32 10.7 / 11.7, k = 512 14.5 / 15; of 7680: k = 8 12.1 / 11.2
+//   30 of 4500: k = 2048 32 / 19
 //   8 of 8192: k = 8 12.8 / 10.4, k = 64 13.5 / 13.8
 //   8 of 16000: k = 64 15.4 / 12.8, k = 512 17.7 / 17.7; 500 of them: 12 and 18% faster
 //   8 of 50000: k = 2 18.6 / 15.7, k = 16 20 / 21
@@ -28,8 +29,8 @@ inline bool batch_streams(uint64_t n, uint32_t k, size_t items) {
   if (n <= 512) return many == 2 || (uint64_t)k * 8 <= n * 7;
   if (n <= 1024) return many == 2 || (uint64_t)k * 5 <= n || (k > 512 && k < n);
   if (k == 1 && n > 4096) return false;
-  if (n <= 6144) return (uint64_t)k * 5 <= n && n * k <= (many == 0 ? 3u << 17 : many == 1 ? 9u << 16 : 6u << 17);
-  if (n <= 7680) return many == 2 && k <= 64;
+  if (n <= 4096) return (uint64_t)k * 5 <= n && n * k <= (many == 0 ? 3u << 17 : many == 1 ? 9u << 16 : 6u << 17);
+  if (n <= 7680) return (uint64_t)k * 5 <= n * 2 && (many || n <= 6144 || k >= 64);
   if (n < 9000) return k >= (many ? 32u : 64u);
   if (n < 18000) return k >= (many == 0 ? 512u : many == 1 ? 96u : 32u);
   if (n <= 65536) return k >= (many == 2 ? 4u : 16u);
