@@ -8,6 +8,28 @@
 
 namespace drtopk {
 
+// A single call of 4-byte keys that the batched form's kernel takes (k_one: sorted
+// by a network up to 4096 keys, then by the delegate method or a radix select),
+// where one workgroup's sort or cut (k_sone) is slower: most of a few keys, which
+// crowd the bins of a sort where they lie in clusters or, floats, on both sides
+// of zero (2048 of 4096 normal float32: 12.7 against 19.9 us), and a handful of
+// many (4 of 50000 uint32: 14.8 / 19.3; 64 of them: 21.5 / 19.1; 24 of 8193: 10.6 /
+// 11.2, but 31 / 11.1 where they are tied).
+inline bool one_delegates(uint64_t n, uint32_t k) {
+  if (n <= 8192) return k <= 2048 && (uint64_t)k * 8 > n;
+  return n <= 65536 && k <= 16;
+}
+
+// Whether one workgroup cuts even a list that fits its LDS by a sample before it
+// sorts: where so much is wanted that the sort's bins are crowded.  us a call of
+// normal float32 / uint32 / 16-bit values, sorted whole, cut, by k_one:
+//   4096 keys, k = 256  11.2 9.4 11.8,  10.6 10.8 10.7,  11.0 10.7 16.0
+//   4096 keys, k = 512  14.1 9.9 13.8,  11.2 10.9 11.4,  11.0  9.0 15.9
+//   6000 keys, k = 256  13.2 11.1 13.2, 10.8 10.9 11.0,  13.5 13.4 13.6
+//   8192 keys, k = 96   11.8 10.6 12.0, 11.4 11.2 11.2,  13.3 12.2 13.3
+//   8192 keys, k = 512  21.2 14.9 21.3, 11.5 11.6 12.3,  14.8 14.2 15.0
+inline bool one_cuts(uint64_t n, uint32_t k) { return n * n * k > 1ull << 32 && (uint64_t)k * 8 <= n; }
+
 // A problem of a batch of `items`, whole in one workgroup: sorted whole or
 // streamed once (b_stream), or else selected first (n <= 4096) or by the delegate
 // method (b_problem).  Sorting all of a short list loses where so many are wanted

@@ -7,6 +7,7 @@
 #include <cmath>
 
 #include "host.h"
+#include "routes.h"
 #include "sample.h"
 #include "sample_host.h"
 #include "wide_host.h"
@@ -153,7 +154,7 @@ template <typename K>
 bool one_fits(uint64_t n, uint32_t k, uint32_t* r) {
   const uint32_t cap = n <= 1024 ? 1024u : SOne<K>::kCap;
   *r = 0;
-  if (n <= cap) return true;
+  if (n <= cap && !one_cuts(n, k)) return true;
   if (n > 65536) return false;
   const double lam = (double)k * kSSplit / n, q = lam + 4.5 * std::sqrt(lam) + 6.0;
   *r = (uint32_t)q;
@@ -296,12 +297,7 @@ void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_o
   const uint32_t word = p.wide ? 8 : 4;
   p.head = (uint32_t)(((16 - (reinterpret_cast<uintptr_t>(keys) & 15u)) & 15u) / word);
   if ((reinterpret_cast<uintptr_t>(keys) & (word - 1)) == 0) {
-    // left to the batched form's kernel: most of a few keys, which crowd the
-    // bins of a sort where they lie in clusters or, floats, on both sides of
-    // zero (2048 of 4096 normal float32: 12.7 against 19.9 us), and a handful
-    // of many (4 of 50000 uint32: 14.8 against 19.3; 64 of them: 21.5 / 19.1)
-    const bool old = !p.wide && ((n <= 8192 && k <= 2048 && (uint64_t)k * 8 > n) ||
-                                 (n > 8192 && n <= 65536 && k <= 16));
+    const bool old = !p.wide && one_delegates(n, k);
     p.one = (k > 1 || p.wide) && !old &&
             (p.wide ? one_fits<uint64_t>(n, k, &p.win.r) : one_fits<uint32_t>(n, k, &p.win.r));
     if (p.one) p.on = true;

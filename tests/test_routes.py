@@ -37,6 +37,20 @@ FASTER = [(64, 8, 30), (500, 62, 8), (1000, 16, 8), (1000, 128, 2000), (1024, 76
           (65536, 2048, 8), (100000, 64, 500)]
 
 
+# (n, k) of single calls of 4-byte keys: by the batched form's kernel; cut by a sample where all keys fit the LDS
+SINGLE = [(1000, 100, 0, 0), (1000, 126, 1, 0), (3000, 375, 0, 0), (4096, 256, 0, 0), (4096, 512, 0, 1),
+          (4096, 2048, 1, 0), (4097, 16, 0, 0), (6000, 256, 0, 1), (8192, 64, 0, 0), (8192, 512, 0, 1),
+          (8192, 1024, 0, 1), (8192, 1025, 1, 0), (8192, 2049, 0, 0), (8193, 16, 1, 0), (8193, 64, 0, 0),
+          (50000, 4, 1, 0), (50000, 64, 0, 0), (65537, 4, 0, 0)]
+
+
+def test_single_rules(tmp_path):
+    got = ask(tmp_path, lambda c: f"one_delegates({c[0]}, {c[1]})", SINGLE)
+    assert got == [c[2] for c in SINGLE]
+    small = [c for c in SINGLE if c[0] <= 8192 and not c[2]]
+    assert ask(tmp_path, lambda c: f"one_cuts({c[0]}, {c[1]})", small) == [c[3] for c in small]
+
+
 def test_batch_rule(tmp_path):
     got = ask(tmp_path, lambda c: f"batch_streams({c[0]}, {c[1]}, {c[2]})", SLOWER + FASTER)
     assert got == [0] * len(SLOWER) + [1] * len(FASTER), [c for c, g in zip(SLOWER + FASTER, got) if g != (c in FASTER)]
