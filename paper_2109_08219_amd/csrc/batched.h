@@ -1079,7 +1079,7 @@ template <int E>
 __device__ __forceinline__ void b_stream_write(const BatchDesc& d, uint64_t (&c)[E], uint32_t N, Codec cx, int L,
                                                uint32_t posmask, BStreamSmem& sm) {
   const uint32_t k = d.k;
-  ssort<uint64_t, kBStreamCap, kBT, E>(sm, c, N, k, [&](uint32_t r, uint64_t x) {
+  ssort<uint64_t, kBStreamCap, kBT, E>(sm, c, N, d.out_vals || d.out_idx ? 0 : k - 1, k, [&](uint32_t r, uint64_t x) {
     if (r >= k) return;
     const uint32_t val = cx.dec((uint32_t)(x >> L));
     if (d.out_vals) d.out_vals[r] = val;

@@ -512,10 +512,14 @@ __device__ __forceinline__ void sfill_splitters(C* split, const SWin& w, uint32_
       }
       for (uint32_t f = half - 1 + kSGroup / 2; f < w.P; ++f) out[f] = x[kSGroup];
     } else if (tight) {
-      if (w.P >= kSGroup) {
-        for (uint32_t f = kSGroup; f < w.P; ++f) out[f] = x[kSGroup];
+      if (w.P >= kSGroup) {  // as many equal pieces of each gap as there are bounds
+        const uint32_t lgq = lgP - 4, q = 1u << lgq;
 #pragma unroll
-        for (uint32_t i = 1; i <= kSGroup; ++i) out[i - 1] = x[i];
+        for (uint32_t i = 1; i <= kSGroup; ++i) {
+          const C piece = (x[i - 1] - x[i]) >> lgq;
+          for (uint32_t f = 1; f < q; ++f) out[(i - 1) * q + f - 1] = x[i - 1] - piece * f;
+          out[i * q - 1] = x[i];
+        }
       } else {
 #pragma unroll
         for (uint32_t i = 1; i <= kSGroup; ++i)
@@ -974,16 +978,16 @@ __device__ __forceinline__ uint32_t scount(uint32_t* hist, uint32_t b) {
 }
 
 // Sorts the N (<= CAP) composites held N = e * T + thread in c[] descending
-// and calls emit(slot, composite) for each of the first `need` slots (and
-// perhaps a few after them).  Linear bins over [min, max] (logarithmic from the
+// and calls emit(slot, composite) for each of the slots from `from` up to `need`
+// (and perhaps a few around them).  Linear bins over [min, max] (logarithmic from the
 // top when at most a quarter is needed: the top of both float and integer keys
 // is then spread over many bins whatever lies below), a scatter into LDS bin by
 // bin, then each element's rank inside its bin; bins that start past `need`
-// are left alone.  When a bin that counts is crowded (keys in far-apart
+// or end before `from` are left alone.  When a bin that counts is crowded (keys in far-apart
 // clusters, floats of both signs) bins between samples instead.
 template <typename C, uint32_t CAP, int T, int E, typename F>
-__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint64_t need, F&& emit,
-                                      C mn = 0, C mx = ~(C)0) {
+__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint32_t from, uint64_t need,
+                                      F&& emit, C mn = 0, C mx = ~(C)0) {
   for (int b = threadIdx.x; b <= kSBins; b += T) sm.hist[b] = 0;
   if (threadIdx.x == 0) sm.misc[0] = 0;
   if (mx == ~(C)0) {  // uniform
@@ -1022,7 +1026,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
 #pragma unroll
   for (int j = 0; j < BP; ++j) {
     sm.hist[threadIdx.x * BP + j] = ex;
-    if (h[j] > kSCrowd && ex < need) sm.misc[0] = 1;
+    if (h[j] > kSCrowd && ex < need && ex + h[j] > from) sm.misc[0] = 1;
     ex += h[j];
   }
   if (threadIdx.x == 0) sm.hist[kSBins] = N;
@@ -1040,7 +1044,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
       if (e * T + threadIdx.x < N) {
         const uint32_t b = at[e] >> 16;
         const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
-        if (lo < need) {
+        if (lo < need && hi > from) {
           emit(srank_in(sm.buf, lo, hi, c[e]), c[e]);
         }
       }
@@ -1110,7 +1114,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
     if (e * T + threadIdx.x < N) {
       const uint32_t b = at[e] >> 16;
       const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
-      if (lo < need) {
+      if (lo < need && hi > from) {
         emit(srank_in(sm.buf, lo, hi, c[e]), c[e]);
       }
     }
@@ -1244,6 +1248,10 @@ struct SOut {
   int L;
   uint32_t posmask;
   SPayload pay;
+  // First slot that is wanted, from slot `base` on: a k-th value alone needs no other.
+  __device__ __forceinline__ uint32_t from(uint64_t base) const {
+    return kth_only && k - 1 > base ? (uint32_t)(k - 1 - base) : 0u;
+  }
   __device__ __forceinline__ void operator()(uint64_t slot, typename STraits<K>::Comp c) const {
     if (slot >= k) return;
     const K v = sdec<K>((K)(c >> L), cd);
@@ -1345,7 +1353,7 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
       more = cut > low;
       upto = cut - 1;
     }
-    ssort<C, CAP, T, E>(sm, c, N, k - base, [&](uint32_t rk, C x) { out(base + rk, x); });
+    ssort<C, CAP, T, E>(sm, c, N, out.from(base), k - base, [&](uint32_t rk, C x) { out(base + rk, x); });
     base = next;
   }
   // the runs are the whole bucket, or reach the last slot
@@ -1511,7 +1519,9 @@ __global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu
     return;
   }
   if (second) return;
-  ssort<C, CAP, T, E>(sm, c, count, k - start, [&](uint32_t rk, C x) { out(start + rk, x); }, low, upto);
+  // (the lowest bucket may reach down to composite 0, far below its elements)
+  ssort<C, CAP, T, E>(sm, c, count, out.from(start), k - start, [&](uint32_t rk, C x) { out(start + rk, x); }, low,
+                      low ? upto : ~(C)0);
 }
 
 // The whole problem in one workgroup.  n <= CAP: every element goes into the
@@ -1625,7 +1635,7 @@ __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t
     __syncthreads();
   }
   const SOut<K> out{out_vals, out_idx, out_kth, k, kth_only, cd, L, posmask, pay};
-  ssort<C, CAP, T, E>(sm, c, N, k, [&](uint32_t slot, C x) { out(slot, x); });
+  ssort<C, CAP, T, E>(sm, c, N, out.from(0), k, [&](uint32_t slot, C x) { out(slot, x); });
 }
 
 }  // namespace drtopk
