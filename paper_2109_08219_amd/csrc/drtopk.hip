@@ -410,12 +410,11 @@ constexpr size_t kSampledFree = size_t(4) << 20;
 // n = 3 * 10^6, k = 100: 24.4 / 47.6; n = 2^24, k = 2^21: 90 / 641, its median:
 // 59 / 261; n = 2^29 of 16 values, k = 16384: 350 / 446; n = 2^30, k = 1024:
 // 660 / 679, k = 131072: 667 / 796; float64, n = 2^28, k = 131072: 364 / 799).
-// k = 1 of 32-bit keys stays with the delegate pass, which alone answers it.
 // `total` is the workspace of the other path: the no-allocation limit is stated
 // in it, so the sampled path needs no more than that or a small part of that
 // limit.
 bool take_sampled(const SPlan& sp, size_t total) {
-  return sp.on && (sp.k > 1 || sp.wide) && sp.planned <= (total > kSampledFree ? total : kSampledFree) &&
+  return sp.on && sp.planned <= (total > kSampledFree ? total : kSampledFree) &&
          g_cap_override.load(std::memory_order_relaxed) == 0;
 }
 

@@ -296,9 +296,10 @@ void sample_plan(const void* keys, uint64_t n, uint32_t k, int dtype, bool kth_o
   while (p.L < 32 && ((n - 1) >> p.L)) ++p.L;
   const uint32_t word = p.wide ? 8 : 4;
   p.head = (uint32_t)(((16 - (reinterpret_cast<uintptr_t>(keys) & 15u)) & 15u) / word);
-  if ((reinterpret_cast<uintptr_t>(keys) & (word - 1)) == 0) {
+  // (k = 1 of 4-byte keys: the delegate pass alone answers it)
+  if ((k > 1 || p.wide) && (reinterpret_cast<uintptr_t>(keys) & (word - 1)) == 0) {
     const bool old = !p.wide && one_delegates(n, k);
-    p.one = (k > 1 || p.wide) && !old &&
+    p.one = !old &&
             (p.wide ? one_fits<uint64_t>(n, k, &p.win.r) : one_fits<uint32_t>(n, k, &p.win.r));
     if (p.one) p.on = true;
     else if (old) ;
