@@ -176,6 +176,11 @@ int drtopk_tune_get(drtopk_tune_t* out, uint32_t cap, uint32_t* count);
  * Route 2 falls back to route 3 on the device when the survivors of an
  * input exceed the workgroup's capacity (4096). */
 int drtopk_batched_alpha(uint64_t n, uint32_t k, int32_t* route, int32_t* alpha, int32_t* beta);
+/* Whether a problem that one workgroup of a batch of `items` problems owns whole
+ * is sorted or streamed in one pass (*streams = 1, the table is not looked at) or
+ * run as drtopk_batched_alpha says (0).  No device work; DRTOPK_EINVAL for a shape
+ * that a batch runs through the single-problem path. */
+int drtopk_batched_streams(uint64_t n, uint32_t k, uint32_t items, int32_t* streams);
 
 /* Explicit method parameters (for tests, tuning and ablations).
  *   alpha  subrange = 2^alpha elements (Section 5.1), at most 24; -1 = planner's choice

@@ -106,6 +106,7 @@ def lib() -> ctypes.CDLL:
             "drtopk_tune_get": [ctypes.POINTER(Tune), u32, ctypes.POINTER(u32)],
             "drtopk_batched_alpha": [u64, u32, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
                                      ctypes.POINTER(ctypes.c_int32)],
+            "drtopk_batched_streams": [u64, u32, u32, ctypes.POINTER(ctypes.c_int32)],
             "drtopk_footprint": [u64, u32, i32, ctypes.POINTER(u64)],
             "drtopk_read_probe": [vp, u64, vp, vp],
             "topk_select_host": [vp, u64, u32, i32, u64, vp, vp, vp],
@@ -455,6 +456,14 @@ def batched_plan(n: int, k: int) -> tuple[int, int, int]:
     _check(lib().drtopk_batched_alpha(n, k, ctypes.byref(r), ctypes.byref(a), ctypes.byref(b)),
            "drtopk_batched_alpha")
     return r.value, a.value, b.value
+
+
+def batched_streams(n: int, k: int, items: int) -> bool:
+    """Whether a problem that one workgroup of a batch of `items` owns whole runs in one pass (or
+    one sort), whatever the tuning table says, rather than as batched_plan says."""
+    s = ctypes.c_int32()
+    _check(lib().drtopk_batched_streams(n, k, items, ctypes.byref(s)), "drtopk_batched_streams")
+    return bool(s.value)
 
 
 def batched_route(n: int, k: int) -> tuple[int, int]:

@@ -1077,6 +1077,12 @@ int drtopk_batched_alpha(uint64_t n, uint32_t k, int32_t* route, int32_t* alpha,
   return DRTOPK_OK;
 }
 
+int drtopk_batched_streams(uint64_t n, uint32_t k, uint32_t items, int32_t* streams) {
+  if (!streams || n == 0 || k == 0 || k > n || items == 0 || !batched_eligible(n, k)) return DRTOPK_EINVAL;
+  *streams = batch_streams(n, k, items) ? 1 : 0;
+  return DRTOPK_OK;
+}
+
 int drtopk_delegates(const void* keys, uint64_t n, int dtype, int alpha, int beta, void* out_dkeys,
                      uint32_t* out_didx, void* stream) {
   if (!out_dkeys || !out_didx) return DRTOPK_EINVAL;

@@ -1,12 +1,14 @@
 """Autotuner: subrange size (Rule 4) and delegates per subrange (Rule 3), measured.
 
 Batched form:
-For every bucket (floor(log2 n), floor(log2 k)) that the batched kernel owns,
-a batch of synthetic problems of that bucket (half uint32 uniform, half
-float32 normal, lengths and k uniform inside the bucket) is timed with each
+For every bucket (floor(log2 n), floor(log2 k)) whose problems a batch runs by
+the table (whole problems that a batch streams in one pass do not look at it and
+get no entry), a batch of synthetic problems of that bucket (half uint32 uniform,
+half float32 normal, lengths and k uniform inside the bucket; 30 of up to 2^16 keys,
+64 of more, which are then split over workgroups) is timed with each
 candidate (alpha, beta): Rule 4's alpha and its neighbours with one or two
-delegates per subrange, as the kernel would actually run them (raised to
-fit its delegate vector, lowered to keep more delegates than k), the
+delegates per subrange, raised to fit the kernel's delegate vector and lowered
+to keep more delegates than k, the
 workgroup radix select without delegates (written as alpha 0), and no
 entry (Rule 4 itself, beta 1); each is timed twice,
 interleaved, keeping the faster run.  A bucket gets an entry only when an
@@ -14,14 +16,15 @@ alternative beats Rule 4.  The table is written to tuning.json,
 which the binding loads when it opens the library.  Every alpha gives the
 same results; only the time changes.
 
-Single problems (--single): for n = 2^20 .. 2^30 and k = 2^0 .. 2^17 where
-the planner takes the delegate method, its (alpha, beta) against alpha
+Single problems (--single): the delegate method, which calls with counters or
+explicit parameters and those at k = 1 take, for n = 2^20 .. 2^30 and k = 2^0 ..
+2^17 where it is planned: its (alpha, beta) against alpha
 within 2 of it and beta in {1, 2, 4}, on uint32 uniform and float32 normal
 keys of n = 2^lg_n (the sum of both times; three interleaved rounds, the
 fastest run counts); an entry is written only where a candidate beats the
 planner by more than 3%.
 
-    python -m paper_2109_08219_amd.tune [--out PATH] [--problems 512] [--reps 10] [--single | --keep-single | --keep-batched]
+    python -m paper_2109_08219_amd.tune [--out PATH] [--problems 64] [--reps 10] [--single | --keep-single | --keep-batched]
 """
 from __future__ import annotations
 
@@ -73,13 +76,13 @@ def tune_batched(drt, torch, problems, reps, log=print):
     drt.tune_set([])
     for lg_n in range(12, 22):
         for lg_k in range(0, 12):
-            probs = _bucket_problems(torch, lg_n, lg_k, problems, gen)
+            probs = _bucket_problems(torch, lg_n, lg_k, min(problems, 30 if lg_n < 16 else 64), gen)
             if probs is None:
                 continue
             # the alpha the kernel runs for a problem of this bucket under a table entry a
             rep_n, rep_k = probs[0][0].numel(), probs[0][1]
             base = drt.batched_plan(rep_n, rep_k)
-            if base[0] != 2:
+            if base[0] != 2 or (rep_n <= 1 << 16 and drt.batched_streams(rep_n, rep_k, len(probs))):
                 continue
             cands = {}
             for b in (1, 2):
@@ -133,8 +136,8 @@ def tune_single(drt, torch, reps, log=print):
             def time_opts(alpha, beta):
                 tot = 0.0
                 for t, v in zip(keys, vals):
-                    run = (lambda: drt.topk_select(t, k, v, idx)) if alpha is None else \
-                        (lambda: drt.topk_select(t, k, v, idx, alpha=alpha, beta=beta, mode=1))
+                    def run():
+                        drt.topk_select(t, k, v, idx, alpha=alpha, beta=beta, mode=1)
                     for _ in range(2):
                         run()
                     torch.cuda.synchronize()
@@ -150,7 +153,7 @@ def tune_single(drt, torch, reps, log=print):
             cands = [(a, b) for b in (1, 2, 4) for a in range(max(2, base.alpha - 2), min(24, base.alpha + 2) + 1)]
             times = {}
             for _ in range(3):  # three rounds, interleaved; the fastest run counts
-                for name, (a, b) in [("plan", (None, None))] + [(f"a{a}b{b}", (a, b)) for a, b in cands]:
+                for name, (a, b) in [("plan", (base.alpha, base.beta))] + [(f"a{a}b{b}", (a, b)) for a, b in cands]:
                     t = time_opts(a, b)
                     times[name] = min(times.get(name, t), t)
             best = min(times, key=times.get)
@@ -170,7 +173,7 @@ def tune_single(drt, torch, reps, log=print):
 def main(argv=None):
     ap = argparse.ArgumentParser(description=__doc__.splitlines()[0])
     ap.add_argument("--out", default=os.path.join(HERE, "tuning.json"))
-    ap.add_argument("--problems", type=int, default=512)
+    ap.add_argument("--problems", type=int, default=64, help="at most so many problems a bucket")
     ap.add_argument("--reps", type=int, default=10)
     ap.add_argument("--single", action="store_true", help="also tune single problems (alpha, beta)")
     ap.add_argument("--keep-single", action="store_true",
