@@ -18,9 +18,10 @@
 //     the other subranges;
 //   output: survivors sorted in registers, the first k written.
 // When there are many tiles of split problems (k_batched_split), and for one
-// problem alone (k_one), whole problems take b_problem too.  One whose survivors overflow the LDS (adversarial
-// inputs), or whose delegate vector would not exceed k, takes a block-level MSD
-// radix select over its keys.  No workgroup ever waits for another.
+// problem alone (k_one), whole problems take b_problem too.  One whose delegate
+// vector would not exceed k takes a block-level MSD radix select over its keys; one
+// whose survivors overflow the LDS (adversarial inputs) is streamed after all, or
+// radix-selected if split or claimed.  No workgroup ever waits for another.
 #pragma once
 
 #include "sample.h"
@@ -1079,7 +1080,7 @@ template <int E>
 __device__ __forceinline__ void b_stream_write(const BatchDesc& d, uint64_t (&c)[E], uint32_t N, Codec cx, int L,
                                                uint32_t posmask, BStreamSmem& sm) {
   const uint32_t k = d.k;
-  ssort<uint64_t, kBStreamCap, kBT, E>(sm, c, N, d.out_vals || d.out_idx ? 0 : k - 1, k, [&](uint32_t r, uint64_t x) {
+  ssort<uint64_t, kBStreamCap, kBT, E>(sm, c, N, k, [&](uint32_t r, uint64_t x) {
     if (r >= k) return;
     const uint32_t val = cx.dec((uint32_t)(x >> L));
     if (d.out_vals) d.out_vals[r] = val;

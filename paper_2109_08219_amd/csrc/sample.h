@@ -978,16 +978,16 @@ __device__ __forceinline__ uint32_t scount(uint32_t* hist, uint32_t b) {
 }
 
 // Sorts the N (<= CAP) composites held N = e * T + thread in c[] descending
-// and calls emit(slot, composite) for each of the slots from `from` up to `need`
-// (and perhaps a few around them).  Linear bins over [min, max] (logarithmic from the
+// and calls emit(slot, composite) for each of the first `need` slots (and perhaps
+// a few more).  Linear bins over [min, max] (logarithmic from the
 // top when at most a quarter is needed: the top of both float and integer keys
 // is then spread over many bins whatever lies below), a scatter into LDS bin by
 // bin, then each element's rank inside its bin; bins that start past `need`
-// or end before `from` are left alone.  When a bin that counts is crowded (keys in far-apart
+// are left alone.  When a bin that counts is crowded (keys in far-apart
 // clusters, floats of both signs) bins between samples instead.
 template <typename C, uint32_t CAP, int T, int E, typename F>
-__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint32_t from, uint64_t need,
-                                      F&& emit, C mn = 0, C mx = ~(C)0) {
+__device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint64_t need, F&& emit,
+                                      C mn = 0, C mx = ~(C)0) {
   for (int b = threadIdx.x; b <= kSBins; b += T) sm.hist[b] = 0;
   if (threadIdx.x == 0) sm.misc[0] = 0;
   if (mx == ~(C)0) {  // uniform
@@ -1026,7 +1026,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
 #pragma unroll
   for (int j = 0; j < BP; ++j) {
     sm.hist[threadIdx.x * BP + j] = ex;
-    if (h[j] > kSCrowd && ex < need && ex + h[j] > from) sm.misc[0] = 1;
+    if (h[j] > kSCrowd && ex < need) sm.misc[0] = 1;
     ex += h[j];
   }
   if (threadIdx.x == 0) sm.hist[kSBins] = N;
@@ -1044,7 +1044,7 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
       if (e * T + threadIdx.x < N) {
         const uint32_t b = at[e] >> 16;
         const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
-        if (lo < need && hi > from) {
+        if (lo < need) {
           emit(srank_in(sm.buf, lo, hi, c[e]), c[e]);
         }
       }
@@ -1114,11 +1114,93 @@ __device__ __forceinline__ void ssort(SSortShared<C, CAP, T>& sm, C (&c)[E], uin
     if (e * T + threadIdx.x < N) {
       const uint32_t b = at[e] >> 16;
       const uint32_t lo = sm.hist[b], hi = sm.hist[b + 1];
-      if (lo < need && hi > from) {
+      if (lo < need) {
         emit(srank_in(sm.buf, lo, hi, c[e]), c[e]);
       }
     }
   __syncthreads();
+}
+
+// The element of rank `rank` (from 0, descending) among the N (<= CAP) composites held as
+// in ssort; emit(rank, composite) if there is one.  Bins as there, but only the
+// one that holds the rank goes on: into LDS, and divided again between its own
+// extremes while it is crowded (they lie in different bins, so each round leaves
+// fewer, and a range of no more than a bin's width).  Bound by the chain of LDS passes,
+// two barriers each: normal float64, the median of 500000 44.5 us a call, where
+// sorting all of a crowded bucket by samples took 53; the 1000th of 4000 16 / 42.
+template <typename C, uint32_t CAP, int T, int E, typename F>
+__device__ __forceinline__ void skth(SSortShared<C, CAP, T>& sm, C (&c)[E], uint32_t N, uint64_t rank, F&& emit,
+                                     C mn = 0, C mx = ~(C)0) {
+  for (uint32_t off = 0;;) {  // elements above those that are left
+    for (int b = threadIdx.x; b < kSBins; b += T) sm.hist[b] = 0;
+    if (threadIdx.x == 0) sm.misc[7] = 0;
+    if (mx == ~(C)0) {  // uniform
+      mx = 0;
+      mn = ~(C)0;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * T + threadIdx.x < N) {
+          mx = c[e] > mx ? c[e] : mx;
+          mn = c[e] < mn ? c[e] : mn;
+        }
+      sblock_minmax<C, T>(mx, mn, sm.red);
+    } else {
+      __syncthreads();
+    }
+    const uint32_t bl = sbits((C)(mx - mn));
+    const int sh = bl > 11 ? (int)bl - 11 : 0;
+    const bool logb = off == 0 && rank < N / 4;
+    uint32_t at[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e * T + threadIdx.x < N) {
+        const uint32_t b = logb ? slog_bin<C>(mx - c[e]) : (uint32_t)((mx - c[e]) >> sh);
+        at[e] = (b << 16) | scount(sm.hist, b);
+      }
+    __syncthreads();
+    constexpr int BP = kSBins / T;
+    uint32_t h[BP], sum = 0;
+#pragma unroll
+    for (int j = 0; j < BP; ++j) {
+      h[j] = sm.hist[threadIdx.x * BP + j];
+      sum += h[j];
+    }
+    uint32_t tot;
+    uint32_t ex = sblock_scan<T>(sum, sm.s_w, &tot);
+#pragma unroll
+    for (int j = 0; j < BP; ++j) {
+      if (ex <= rank && rank < ex + h[j]) {
+        sm.misc[5] = threadIdx.x * BP + j;
+        sm.misc[6] = ex;
+        sm.misc[7] = h[j];
+      }
+      ex += h[j];
+    }
+    __syncthreads();
+    const uint32_t bin = sm.misc[5], lo = sm.misc[6], cnt = sm.misc[7];
+    if (cnt) {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * T + threadIdx.x < N && at[e] >> 16 == bin) sm.buf[at[e] & 0xFFFFu] = c[e];
+    }
+    __syncthreads();
+    off += lo;
+    rank -= lo;
+    if (cnt <= kSCrowd) {
+      if (threadIdx.x < cnt) {
+        const C x = sm.buf[threadIdx.x];
+        const uint32_t rk = srank_in(sm.buf, 0, cnt, x);
+        if (rk == rank) emit(off + rk, x);
+      }
+      __syncthreads();
+      return;
+    }
+    N = cnt;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e * T + threadIdx.x < N) c[e] = sm.buf[e * T + threadIdx.x];
+    mx = ~(C)0;
+  }
 }
 
 template <typename K>
@@ -1248,10 +1330,6 @@ struct SOut {
   int L;
   uint32_t posmask;
   SPayload pay;
-  // First slot that is wanted, from slot `base` on: a k-th value alone needs no other.
-  __device__ __forceinline__ uint32_t from(uint64_t base) const {
-    return kth_only && k - 1 > base ? (uint32_t)(k - 1 - base) : 0u;
-  }
   __device__ __forceinline__ void operator()(uint64_t slot, typename STraits<K>::Comp c) const {
     if (slot >= k) return;
     const K v = sdec<K>((K)(c >> L), cd);
@@ -1353,7 +1431,9 @@ __device__ __forceinline__ void sbucket_rare(SBucketShared<K>& sm, const K* keys
       more = cut > low;
       upto = cut - 1;
     }
-    ssort<C, CAP, T, E>(sm, c, N, out.from(base), k - base, [&](uint32_t rk, C x) { out(base + rk, x); });
+    const auto emit = [&](uint32_t rk, C x) { out(base + rk, x); };
+    if (out.kth_only) skth<C, CAP, T, E>(sm, c, N, k - 1 - base, emit);
+    else ssort<C, CAP, T, E>(sm, c, N, k - base, emit);
     base = next;
   }
   // the runs are the whole bucket, or reach the last slot
@@ -1520,8 +1600,9 @@ __global__ __launch_bounds__(kSBucketThreads) __attribute__((amdgpu_waves_per_eu
   }
   if (second) return;
   // (the lowest bucket may reach down to composite 0, far below its elements)
-  ssort<C, CAP, T, E>(sm, c, count, out.from(start), k - start, [&](uint32_t rk, C x) { out(start + rk, x); }, low,
-                      low ? upto : ~(C)0);
+  const auto emit = [&](uint32_t rk, C x) { out(start + rk, x); };
+  if (kth_only) skth<C, CAP, T, E>(sm, c, count, k - 1 - start, emit, low, low ? upto : ~(C)0);
+  else ssort<C, CAP, T, E>(sm, c, count, k - start, emit, low, low ? upto : ~(C)0);
 }
 
 // The whole problem in one workgroup.  n <= CAP: every element goes into the
@@ -1538,7 +1619,7 @@ struct SOne {
   static constexpr uint32_t kCap = 65536 / sizeof(C);
 };
 
-template <typename K, int T>
+template <typename K, int T, bool KTH>
 __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t n, uint32_t k, uint32_t r,
                                             int kth_only, SCodec<K> cd, int L, K* __restrict__ out_vals,
                                             uint32_t* __restrict__ out_idx, K* __restrict__ out_kth, SPayload pay,
@@ -1635,7 +1716,9 @@ __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t
     __syncthreads();
   }
   const SOut<K> out{out_vals, out_idx, out_kth, k, kth_only, cd, L, posmask, pay};
-  ssort<C, CAP, T, E>(sm, c, N, out.from(0), k, [&](uint32_t slot, C x) { out(slot, x); });
+  const auto emit = [&](uint32_t slot, C x) { out(slot, x); };
+  if constexpr (KTH) skth<C, CAP, T, E>(sm, c, N, k - 1, emit);
+  else ssort<C, CAP, T, E>(sm, c, N, k, emit);
 }
 
 }  // namespace drtopk

@@ -168,12 +168,18 @@ void enqueue_one(const SPlan& p, const void* keys_v, K* out_vals, uint32_t* out_
   const SCodec<K> cd{(K)p.codec_a, (K)p.codec_c};
   const uint32_t n = (uint32_t)p.n;
   const int kth = p.kth_only ? 1 : 0;
-  if (n <= 1024)
-    hipLaunchKernelGGL((k_sone<K, 256>), dim3(1), dim3(256), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, out_idx,
-                       out_kth, p.pay, ck);
-  else
-    hipLaunchKernelGGL((k_sone<K, 1024>), dim3(1), dim3(1024), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, out_idx,
-                       out_kth, p.pay, ck);
+#define DRTOPK_ONE(T, KTH)                                                                                       \
+  hipLaunchKernelGGL((k_sone<K, T, KTH>), dim3(1), dim3(T), 0, s, keys, n, p.k, p.win.r, kth, cd, p.L, out_vals, \
+                     out_idx, out_kth, p.pay, ck)
+  if (n <= 1024) {
+    if (kth) DRTOPK_ONE(256, true);
+    else DRTOPK_ONE(256, false);
+  } else if (kth) {
+    DRTOPK_ONE(1024, true);
+  } else {
+    DRTOPK_ONE(1024, false);
+  }
+#undef DRTOPK_ONE
 }
 
 template <typename K>
