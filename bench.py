@@ -161,7 +161,7 @@ def bench_small(drt, synth, torch, args):
     v = torch.empty(1024, dtype=t.dtype, device="cuda")
     ix = torch.empty(1024, dtype=torch.int32, device="cuda")
     r = _median_ms(torch, lambda: drt.topk_select(t, 1024, v, ix), max(20, args.steps), max(3, args.warmup))
-    r.update(n=1 << 20, k=1024, keys_per_s=(1 << 20) / (r["ms_median"] / 1e3), mode=drt.plan(1 << 20, 1024).mode)
+    r.update(n=1 << 20, k=1024, keys_per_s=(1 << 20) / (r["ms_median"] / 1e3))
     return r
 
 
@@ -176,8 +176,7 @@ def bench_smallest_i32(drt, torch, t_u, t_f):
             v = torch.empty(k, dtype=t.dtype, device="cuda")
             ix = torch.empty(k, dtype=torch.int32, device="cuda")
             r = _median_ms(torch, lambda: drt.topk_select(t, k, v, ix, largest=largest), 10, 2)
-            _, _, st = drt.topk_select(t, k, v, ix, largest=largest, stats=True)
-            r.update(dtype=name, order="largest" if largest else "smallest", k=k, alpha=st.alpha, beta=st.beta,
+            r.update(dtype=name, order="largest" if largest else "smallest", k=k,
                      keys_per_s=t.numel() / (r["ms_median"] / 1e3))
             out.append(r)
     return out
@@ -263,8 +262,7 @@ def bench_wide(drt, torch):
             v = torch.empty(k, dtype=t.dtype, device="cuda")
             ix = torch.empty(k, dtype=torch.int32, device="cuda")
             r = _median_ms(torch, lambda: drt.topk_select(t, k, v, ix), 10, 2)
-            p = drt.plan(n, k, name)
-            r.update(dtype=name, k=k, mode=p.mode, alpha=p.alpha, keys_per_s=n / (r["ms_median"] / 1e3),
+            r.update(dtype=name, k=k, keys_per_s=n / (r["ms_median"] / 1e3),
                      GBps=8 * n / (r["ms_median"] / 1e3) / 1e9)
             out.append(r)
         del t
@@ -319,8 +317,8 @@ def bench_adversarial(drt, torch, args):
     vh = torch.empty(k, dtype=h.dtype, device="cuda")
     r = _median_ms(torch, lambda: drt.topk_select(h, k, vh, ix), 10, 2)
     _, _, st = drt.topk_select(h, k, vh, ix, stats=True)
-    r.update(alpha=st.alpha, beta=st.beta, scanned=int(st.scanned), candidates=int(st.candidates),
-             keys_per_s=n / (r["ms_median"] / 1e3))
+    r.update(delegates_run={"alpha": st.alpha, "beta": st.beta, "scanned": int(st.scanned),
+                            "candidates": int(st.candidates)}, keys_per_s=n / (r["ms_median"] / 1e3))
     out["heavydup_u32"] = r
     del h
     torch.cuda.empty_cache()
@@ -443,15 +441,16 @@ def main() -> int:
     def call(c):
         drt.topk_select(c["keys"], c["k"], c["vals"], c["idx"], stream=stream)
 
-    # plan / counters of each case (outside the timed region; calls with counters run the
-    # delegate method, the timed ones the sampled path at k > 1)
+    # plan / counters of each case, from a separate run outside the timed region: calls with
+    # counters run the delegate method, the timed ones the sampled path at k > 1
     for c in cases:
         _, _, st = drt.topk_select(c["keys"], c["k"], c["vals"], c["idx"], stats=True, stream=stream)
-        c.update(alpha=st.alpha, beta=st.beta, scanned=int(st.scanned), candidates=int(st.candidates),
-                 # the method's own traffic beyond the 4n-byte read (not counted as useful bytes):
-                 # delegate vector written, qualifying subranges re-read, survivors written
-                 overhead_bytes={"delegates": 8 * int(st.delegates), "reread": 4 * (int(st.scanned) << st.alpha),
-                                 "survivors": 8 * int(st.candidates)})
+        c["delegates_run"] = {
+            "alpha": st.alpha, "beta": st.beta, "scanned": int(st.scanned), "candidates": int(st.candidates),
+            # the method's own traffic beyond the 4n-byte read (not counted as useful bytes):
+            # delegate vector written, qualifying subranges re-read, survivors written
+            "overhead_bytes": {"delegates": 8 * int(st.delegates), "reread": 4 * (int(st.scanned) << st.alpha),
+                               "survivors": 8 * int(st.candidates)}}
 
     # per-case latency (events around single calls)
     reps = max(3, args.steps)
@@ -578,8 +577,7 @@ def main() -> int:
         "adversarial": adversarial,
         "batched": batched,
         "serving": serving,
-        "cases": [{k: c[k] for k in ("dtype", "k", "alpha", "beta", "scanned", "candidates", "ms_median", "ms_min",
-                                     "ms_max", "ms_mean", "overhead_bytes")}
+        "cases": [{k: c[k] for k in ("dtype", "k", "ms_median", "ms_min", "ms_max", "ms_mean", "delegates_run")}
                   | {"keys_per_s": N / (c["ms_median"] / 1e3), "GBps": 4 * N / (c["ms_median"] / 1e3) / 1e9}
                   for c in case_rows],
     }

@@ -82,9 +82,13 @@ typedef enum {
  *   stream   hipStream_t or NULL
  * Calls with k > 1 (8-byte keys: any k) split the work by a sample of the keys
  * (one workgroup with a cut for few keys; else a filter pass and buckets sorted
- * independently); the result is exact whatever the sample.  The sampled places
- * of the latter are other ones in each process, so no input can be laid out to
- * be misjudged by them. */
+ * independently) where what the sample leaves is at most about 3 million keys
+ * (8-byte keys: 1.5 million); the others (a median of 2^26 keys, say) run the
+ * delegate method or a radix select, and so do a few of the small ones.  The
+ * result is exact whatever the sample.  The sampled places of calls over several
+ * workgroups are other ones in each process, so no input can be laid out to be
+ * misjudged by them; a misjudged call is right too, but one workgroup may then
+ * read the input many times. */
 int topk_select(const void* keys, uint64_t n, uint32_t k, int dtype, void* out_vals,
                 uint32_t* out_idx, void* stream);
 
@@ -131,9 +135,9 @@ typedef struct {
  * call (the caller may reuse it on return).  Each problem obeys topk_select's
  * rules, except that out_vals may be NULL when out_kth is not (k-selection
  * only).  Results equal topk_select / kth_select on each problem alone, bit
- * for bit.  Problems with n <= 2^22 and k <= 2048 run in one launch,
- * a workgroup per problem, largest first, each in one pass over its keys;
- * larger ones run one
+ * for bit.  Problems with n <= 2^22 and k <= 2048 run in one launch, largest first:
+ * a workgroup per problem, each sorted or read in one pass, or by the delegate
+ * method where that is faster (drtopk_batched_streams); larger ones run one
  * after another through the single-problem path, on the same stream.  Any
  * invalid descriptor, or count >= 2^24, fails the whole call with
  * DRTOPK_EINVAL before any work is enqueued.  Problems of more than 2^16 keys and
@@ -144,10 +148,12 @@ int topk_select_batched(const drtopk_problem_t* problems, uint32_t count, void* 
 /* Autotuner table (Rule 4's subrange size and Rule 3's beta, measured rather
  * than modelled).  An entry applies to problems of one form whose
  * floor(log2 n) and floor(log2 k) equal lg_n and lg_k:
- *   form 0 (DRTOPK_FORM_SINGLE): topk_select / kth_select planning, alpha and
- *          beta as in drtopk_options_t (explicit options still win);
+ *   form 0 (DRTOPK_FORM_SINGLE): the delegate method of single problems (calls
+ *          with counters, and those that no sample splits, see topk_select),
+ *          alpha and beta as in drtopk_options_t (explicit options still win);
  *   form 1 (DRTOPK_FORM_BATCHED): the subrange exponent and delegates per
  *          subrange (beta 2; any other value means 1) of a batched problem
+ *          that is split or that drtopk_batched_streams does not name
  *          (the planner raises alpha until the delegate vector, S * beta
  *          entries, fits the workgroup's LDS or, for a problem split across
  *          workgroups, its global buffer).
@@ -167,18 +173,19 @@ int drtopk_tune_set(const drtopk_tune_t* entries, uint32_t count);
 int drtopk_tune_get(drtopk_tune_t* out, uint32_t cap, uint32_t* count);
 
 /* How the delegate method would run a batched problem of this shape (no device
- * work; alpha and beta are those of split problems, and of whole ones where a
- * batch splits many):
+ * work; it applies to split problems, to whole ones that drtopk_batched_streams
+ * does not name, and to all where a batch splits many):
  *   *route 0 = single-problem path, 1 = sorted outright in the workgroup,
  *          2 = delegate method in the workgroup with subrange exponent
  *          *alpha and *beta delegates per subrange (1 or 2; beta may be
  *          NULL), 3 = workgroup radix select without delegates.
- * Route 2 falls back to route 3 on the device when the survivors of an
- * input exceed the workgroup's capacity (4096). */
+ * Where the survivors of an input exceed the workgroup's capacity (4096), route
+ * 2 goes on, on the device, as route 3 or, whole problems, in one pass. */
 int drtopk_batched_alpha(uint64_t n, uint32_t k, int32_t* route, int32_t* alpha, int32_t* beta);
 /* Whether a problem that one workgroup of a batch of `items` problems owns whole
  * is sorted or streamed in one pass (*streams = 1, the table is not looked at) or
- * run as drtopk_batched_alpha says (0).  No device work; DRTOPK_EINVAL for a shape
+ * run as drtopk_batched_alpha says (0, and all problems of a batch that splits
+ * many).  No device work; DRTOPK_EINVAL for a shape
  * that a batch runs through the single-problem path. */
 int drtopk_batched_streams(uint64_t n, uint32_t k, uint32_t items, int32_t* streams);
 
@@ -256,7 +263,9 @@ int drtopk_delegates(const void* keys, uint64_t n, int dtype, int alpha, int bet
 int drtopk_candidates(const void* keys, uint64_t n, uint32_t k, int dtype, int alpha, int beta, int variant,
                       uint32_t* out_pos, uint64_t cap, uint64_t* count, uint32_t* t_out, void* stream);
 
-/* The planner's choice for a problem (no device work). */
+/* The planner's choice of the delegate method's parameters and mode for a problem
+ * (no device work): what calls with counters run, and those that no sample
+ * splits (see topk_select). */
 int drtopk_plan(uint64_t n, uint32_t k, int dtype, drtopk_options_t* out);
 
 /* Phase timing with HIP events, for measurement runs.  While enabled, every
@@ -405,7 +414,8 @@ int drtopk_check(void* stream, uint32_t* flags);
  * method (topk_select, kth_select, and the single-problem part of the other
  * entry points) at `cap` entries for calls planned after it; 0 restores the
  * planner's bound.  With a cap below what an input needs, kernels drop the
- * writes past it, raise flag 16 (and usually 2) and exit normally.
+ * writes past it, raise flag 16 (and usually 2) and exit normally.  While it
+ * is set, no single call is split by a sample.
  * Process-wide; not for production use. */
 int drtopk_set_survivor_cap(uint64_t cap);
 

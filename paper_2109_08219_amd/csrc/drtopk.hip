@@ -404,12 +404,14 @@ int enqueue_plan(const Plan& p, const void* keys, void* ws, void* out_vals, uint
 constexpr size_t kSampledFree = size_t(4) << 20;
 
 // Whether a call with the planner's choices (no explicit options, no counters
-// asked for) takes the sampled path: wherever it can be planned, since it was
-// the faster one at every size measured (us a call, against the other path;
+// asked for) takes the sampled path: wherever it is planned (us a call, against
+// the other path;
 // 50000 float32, k = 64: 19.9 / 21.9; n = 2^20, k = 1024 uint32: 23.9 / 39.6;
-// n = 3 * 10^6, k = 100: 24.4 / 47.6; n = 2^24, k = 2^21: 90 / 641, its median:
+// n = 3 * 10^6, k = 100: 24.5 / 41 to 46; n = 2^24, k = 2^21: 90 / 641, its median:
 // 59 / 261; n = 2^29 of 16 values, k = 16384: 350 / 446; n = 2^30, k = 1024:
 // 660 / 679, k = 131072: 667 / 796; float64, n = 2^28, k = 131072: 364 / 799).
+// Up to a tenth slower is the median of 16384 to 500000 float64 keys of both signs,
+// half of whose digit passes found nothing to do (44.5 / 40.9).
 // `total` is the workspace of the other path: the no-allocation limit is stated
 // in it, so the sampled path needs no more than that or a small part of that
 // limit.
