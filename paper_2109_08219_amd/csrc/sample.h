@@ -1717,7 +1717,10 @@ __global__ __launch_bounds__(T) void k_sone(const K* __restrict__ keys, uint32_t
   }
   const SOut<K> out{out_vals, out_idx, out_kth, k, kth_only, cd, L, posmask, pay};
   const auto emit = [&](uint32_t slot, C x) { out(slot, x); };
-  if constexpr (KTH) skth<C, CAP, T, E>(sm, c, N, k - 1, emit);
+  // (a k-th value near the top of what a cut left of 4-byte keys: bins are not
+  // crowded there, and the sort is the shorter chain; 24 of 12000 11.5 us a call
+  // against 12.5; of lists sorted whole, 250 of 4000, 10.8 against 8.9)
+  if (KTH && (sizeof(K) == 8 || r == 0 || k > N / 8)) skth<C, CAP, T, E>(sm, c, N, k - 1, emit);
   else ssort<C, CAP, T, E>(sm, c, N, k, emit);
 }
 
