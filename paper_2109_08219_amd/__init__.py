@@ -191,10 +191,10 @@ def _stream(stream):
     torch = _torch()
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-    if raw is None or device is None:  # names that torch does not promise
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:  # names that torch does not promise
         return torch.cuda.current_stream().cuda_stream
-    return raw(device())
 
 
 def _opts(alpha, beta, mode, variant=0):
